@@ -91,7 +91,7 @@ __global__ void k_check_no_edges(const int32_t *__restrict__ ptr, int64_t nnz, i
 // (digit b of tile t at b * n_tiles + t), and a scatter in which each tile
 // places its elements in input order.  The degree tiers of both sides need
 // one pass (2 (small_max + 3) keys), the wavefront tier's chunk keys one pass
-// while both sides' keys (2 chunk) fit in kBinsMax, else one per 10 bits;
+// while both sides' keys (2 chunk_keys) fit in kBinsMax, else one per 10 bits;
 // the result equals a stable radix sort's.  The number of pairs is n_max, or
 // *n_dev when that is given (the grid is sized for n_max).  The values may
 // be absent (null); a one-pass sort can also write each input element's
@@ -463,10 +463,12 @@ __global__ __launch_bounds__(kThreads) void k_small_items(TierSides T, const int
         S.cids[i] = c;
 }
 
-// wavefront tier items of both sides in entry order (pieces of a row in
-// order), with the sort key side * chunk + chunk - len (a stable ascending
-// sort keeps the sides apart and puts each side's longest first)
-__global__ __launch_bounds__(kThreads) void k_chunk_items(TierSides T, int chunk, const TierCount *__restrict__ tc,
+// wavefront tier items of both sides in entry order (pieces of a row in order),
+// with the sort key side * keys + (chunk - len) >> shift (a stable ascending
+// sort keeps the sides apart and puts each side's longest first; keys and
+// shift as chunk_keys and chunk_shift give them)
+__global__ __launch_bounds__(kThreads) void k_chunk_items(TierSides T, int chunk, int shift, int keys,
+                                                          const TierCount *__restrict__ tc,
                                                           const TierCount *__restrict__ tpos,
                                                           Item *__restrict__ items, uint32_t *__restrict__ key,
                                                           int32_t *__restrict__ id)
@@ -486,21 +488,30 @@ __global__ __launch_bounds__(kThreads) void k_chunk_items(TierSides T, int chunk
         const int32_t s = S.ptr[r] + k * chunk;
         const int32_t len = min(chunk, S.ptr[r + 1] - s);
         items[pos] = Item{r, s, len, pc == 1 ? -1 : at.slots + k};
-        key[pos] = (uint32_t)(sd * chunk + chunk - len);
+        key[pos] = (uint32_t)(sd * keys + ((chunk - len) >> shift));
         id[pos] = pos;
     }
 }
 
-// the sorted chunk items into each side's list (side 0's come first)
+// the sorted chunk items into each side's list (side 0's come first), and
+// per side the number of leading items whose length key is below `lkey`
+// (n_long, zeroed before; null: not wanted)
 __global__ __launch_bounds__(kThreads) void k_gather_items(TierSides T, const Item *__restrict__ in,
                                                            const int32_t *__restrict__ order,
                                                            const int64_t *__restrict__ counts,
-                                                           const int64_t *__restrict__ n)
+                                                           const int64_t *__restrict__ n, int chunk, int shift,
+                                                           int lkey, int32_t *__restrict__ n_long)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= *n)
         return;
     const int64_t c0 = counts[1];
+    if (n_long && (chunk - in[order[i]].len) >> shift < lkey) {
+        const int sd = (T.n == 2 && i >= c0) ? 1 : 0;
+        const int64_t first = sd ? c0 : 0, end = sd ? *n : min(c0, *n);
+        if (i + 1 == end || (chunk - in[order[i + 1]].len) >> shift >= lkey)
+            n_long[sd] = (int32_t)(i + 1 - first);   // the last of the side's long items
+    }
     if (T.n == 2 && i >= c0)
         T.s[1].chunks[i - c0] = in[order[i]];
     else
@@ -546,6 +557,8 @@ LevelShape bound_shape(const hnv_level_dev &lv, const hnv_level_dev *coarse, int
         sh.n_small[s] = cap(n_rows);
         sh.n_chunks[s] = cap(std::min<int64_t>(sh.nnz / chunk + sh.nnz / (small_max + 1) + 1, sh.nnz + 1));
         sh.n_splits[s] = cap(sh.nnz / (chunk + 1) + 1);
+        const int shortest = chunk - (long_key(sh.rows, chunk) << chunk_shift(chunk)) + 1;   // of a long item
+        sh.n_long[s] = (int32_t)std::min<int64_t>(sh.n_chunks[s], sh.nnz / std::max(shortest, 1) + 1);
         slots += 2 * (sh.nnz / chunk) + 1;
     }
     sh.n_slots = cap(slots);
@@ -649,11 +662,11 @@ hnv_status scratch_layout(int64_t nnz, int64_t rows, int64_t n_chunks, int tier_
 
 // What the build leaves on the device per level, read back once at its end:
 // the check flags (the level's word, the map's word) and the tier counts of
-// both sides (small rows, chunks, split rows, partial slots).  Kept ahead of
-// the per-level temporaries.
+// both sides (small rows, chunks, split rows, partial slots; long chunks).
+// Kept ahead of the per-level temporaries.
 struct LevelMeta {
     int32_t flags[4];
-    int32_t pad[4];
+    int32_t n_long[2], pad[2];
     int64_t counts[8];
 };
 size_t meta_bytes(int n_levels) { return ((size_t)n_levels * sizeof(LevelMeta) + 255) & ~size_t(255); }
@@ -674,10 +687,11 @@ hnv_status device_layout(const hnv_level_dev *levels, int n_levels, int d, hnv_d
     init_plan_shape(p, sizes, d, dtype, o);
     scratch_bytes = 0;
     for (int l = 0; l < n_levels; ++l) {
-        bounds[l] = bound_shape(levels[l], l + 1 < n_levels ? &levels[l + 1] : nullptr, p->small_max, o.chunk);
+        const int sm = p->lv[l].small_max;
+        bounds[l] = bound_shape(levels[l], l + 1 < n_levels ? &levels[l + 1] : nullptr, sm, o.chunk);
         Scratch S{};
         const int64_t nch = (int64_t)bounds[l].n_chunks[0] + bounds[l].n_chunks[1];
-        if (hnv_status st = scratch_layout(bounds[l].nnz, bounds[l].rows, nch, 2 * (p->small_max + 3), nullptr, S);
+        if (hnv_status st = scratch_layout(bounds[l].nnz, bounds[l].rows, nch, 2 * (sm + 3), nullptr, S);
             st != HNV_OK)
             return st;
         scratch_bytes = std::max(scratch_bytes, S.total);
@@ -861,22 +875,23 @@ hnv_status tier_scan(const TierSides &T, int small_max, int chunk, const int *ba
 // the device without reading them: grids cover the bounds (max_chunks
 // wavefront-tier items of both sides) and the kernels stop at the counts.
 hnv_status tier_emit(const TierSides &T, int chunk, int64_t max_chunks, const int *bad, Scratch &S,
-                     const int64_t *counts, hipStream_t s)
+                     const int64_t *counts, int lkey, int32_t *n_long, hipStream_t s)
 {
     if (T.total == 0)
         return HNV_OK;
     const TierArrays &A = S.tier;
     k_small_items<<<grid_for(T.total), kThreads, 0, s>>>(T, A.pos, counts, bad);
     if (max_chunks > 0) {
-        k_chunk_items<<<grid_for(T.total), kThreads, 0, s>>>(T, chunk, A.tc, A.tpos, S.items, S.ckey_a, S.ids_a);
-        // each side's longest first: a stable sort on side * chunk + chunk - len
+        k_chunk_items<<<grid_for(T.total), kThreads, 0, s>>>(T, chunk, chunk_shift(chunk), chunk_keys(chunk), A.tc, A.tpos, S.items, S.ckey_a, S.ids_a);
+        // each side's longest first: a stable sort on the side and the length
         bool in_b = false;
         if (hnv_status st = bin_sort(S.ckey_a, S.ids_a, S.ckey_b, S.ids_b, max_chunks, S.n_chunks,
-                                     (int64_t)T.n * chunk, S, s, in_b);
+                                     (int64_t)T.n * chunk_keys(chunk), S, s, in_b);
             st != HNV_OK)
             return st;
         k_gather_items<<<grid_for(max_chunks), kThreads, 0, s>>>(T, S.items, in_b ? S.ids_b : S.ids_a, counts,
-                                                                 S.n_chunks);
+                                                                 S.n_chunks, chunk, chunk_shift(chunk), lkey,
+                                                                 n_long);
     }
     k_split_items<<<grid_for(T.total), kThreads, 0, s>>>(T, A.tc, A.tpos, counts);
     return dev_check("work lists");
@@ -914,7 +929,7 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
     const hnv_map *m = C ? &maps[l] : nullptr;
     LevelPlan &L = p->lv[l];
     const int64_t nV = lv.n_nodes, nE = lv.n_edges, nnz = lv.nnz;
-    const int sm = p->small_max, chunk = p->opts.chunk;
+    const int sm = L.small_max, chunk = p->opts.chunk;
     DevSide &S0 = L.side[0], &S1 = L.side[1];
     hnv_status st;
     // projection row map (first: the composed indices below read it)
@@ -970,7 +985,8 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
     TS.s[1] = tier_side(S1, nV, side1_offset(nE), C ? L.rowmap : nullptr);
     TS.total = side1_offset(nE) + nV;
     if ((st = tier_scan(TS, sm, chunk, bad, S, M->counts, s)) != HNV_OK ||
-        (st = tier_emit(TS, chunk, (int64_t)S0.n_chunks + S1.n_chunks, bad, S, M->counts, s)) != HNV_OK)
+        (st = tier_emit(TS, chunk, (int64_t)S0.n_chunks + S1.n_chunks, bad, S, M->counts, long_key(L.rows, chunk),
+                        M->n_long, s)) != HNV_OK)
         return st;
     // weights and reciprocals
     if (lv.edge_w) {
@@ -985,15 +1001,17 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
 }
 
 // Level l's work-list sizes from the counts read back after the build
-// (counts: this level's LevelMeta::counts), checked against the bounds the
+// (M: this level's), checked against the bounds the
 // workspace was carved for.
-hnv_status finish_level(hnv_plan *p, int l, const int64_t *counts)
+hnv_status finish_level(hnv_plan *p, int l, const LevelMeta &M)
 {
     LevelPlan &L = p->lv[l];
+    const int64_t *counts = M.counts;
     for (int sd = 0; sd < 2; ++sd) {
         const int64_t *cnt = counts + 4 * sd;
         DevSide &D = L.side[sd];
-        if (cnt[0] > D.n_small || cnt[1] > D.n_chunks || cnt[2] > D.n_splits)
+        if (cnt[0] > D.n_small || cnt[1] > D.n_chunks || cnt[2] > D.n_splits || M.n_long[sd] > L.n_long[sd] ||
+            M.n_long[sd] > cnt[1])
             return fail(HNV_EDEVICE, "work lists exceed their bounds");
         D.n_small = (int32_t)cnt[0];
         D.n_chunks = (int32_t)cnt[1];
@@ -1001,11 +1019,13 @@ hnv_status finish_level(hnv_plan *p, int l, const int64_t *counts)
         L.n_small[sd] = D.n_small;
         L.n_chunks[sd] = D.n_chunks;
         L.n_splits[sd] = D.n_splits;
+        L.n_long[sd] = M.n_long[sd];
     }
     const int64_t slots = counts[3] + counts[7];
     if (slots > p->max_slots)
         return fail(HNV_EDEVICE, "partial slots exceed their bound");
     L.n_slots = (int32_t)slots;
+    settle_long_items(p, L);
     return HNV_OK;
 }
 
@@ -1141,7 +1161,7 @@ extern "C" hnv_status hnv_plan_create_device(const hnv_level_dev *levels, const 
             Scratch S{};
             const int64_t nch = (int64_t)bounds[l].n_chunks[0] + bounds[l].n_chunks[1];
             const hnv_level_dev *C = l + 1 < n_levels ? &levels[l + 1] : nullptr;
-            if ((st = scratch_layout(bounds[l].nnz, bounds[l].rows, nch, 2 * (p->small_max + 3), level_base, S)) ==
+            if ((st = scratch_layout(bounds[l].nnz, bounds[l].rows, nch, 2 * (p->lv[l].small_max + 3), level_base, S)) ==
                     HNV_OK &&
                 (st = launch_checks(levels[l], C, C ? &maps[l] : nullptr, full, S, meta[l].flags, s)) == HNV_OK)
                 st = build_level(p, levels, maps, n_levels, l, &meta[l], S, s);
@@ -1152,7 +1172,7 @@ extern "C" hnv_status hnv_plan_create_device(const hnv_level_dev *levels, const 
         for (int l = 0; l < n_levels && st == HNV_OK; ++l)
             st = report_checks(l, h[l].flags, full);
         for (int l = 0; l < n_levels && st == HNV_OK; ++l)
-            st = finish_level(p, l, h[l].counts);
+            st = finish_level(p, l, h[l]);
         if (st == HNV_OK)
             p->ws_bytes = total;
         if (st != HNV_OK) {
@@ -1244,7 +1264,7 @@ extern "C" hnv_status hnv_score_plan_create_device(const int32_t *cand_ptr, cons
         TS.s[0] = tier_side(D, n_cand, 0, nullptr);
         TS.total = n_cand;
         if ((st = tier_scan(TS, L.small_max, kScoreChunk, nullptr, S, S.counts, s)) != HNV_OK ||
-            (st = tier_emit(TS, kScoreChunk, L.n_chunks, nullptr, S, S.counts, s)) != HNV_OK ||
+            (st = tier_emit(TS, kScoreChunk, L.n_chunks, nullptr, S, S.counts, 0, nullptr, s)) != HNV_OK ||
             (st = read_back(cnt, S.counts, sizeof(cnt), s)) != HNV_OK)
             return st;
         if (cnt[0] > L.n_small || cnt[1] > L.n_chunks || cnt[2] > L.n_splits || cnt[3] > L.n_slots)

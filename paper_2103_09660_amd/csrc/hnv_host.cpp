@@ -54,7 +54,39 @@ void lane_layout(int cols, int elem, int *lanes, int *elems_per_lane)
 
 static constexpr int64_t kMaxI32 = std::numeric_limits<int32_t>::max();
 static constexpr int kDefaultSmallMax = 64;
-static constexpr int kDefaultChunk = 512;
+// Neighbours per wavefront-tier item.  Shorter ones need the finalize launch
+// in more levels and gain nothing, since long items take a workgroup: at 512,
+// 1,024 and 2,048 the refinement of 200K nodes with hubs takes 5.90, 5.80 and
+// 5.74 ms, of 150K nodes (BF16, edge-first) 4.25, 3.93 and 3.93 ms, of 2M
+// nodes (BF16) 154.2, 152.9 and 151.5 ms.
+static constexpr int kDefaultChunk = 2048;
+
+// Levels of up to kIdleRows rows do not fill the chip for long, and the
+// longest chain of dependent loads sets a sweep's time there: every item of
+// the wavefront tier takes a workgroup, and rows leave the lane-group tier
+// early.  Larger levels hide the chains behind other rows and lose by idle
+// lanes instead, so only items of more than kLongItem neighbours take a
+// workgroup there (with all of them, BF16 refinement went from 151.1 to 151.8
+// ms at 2M nodes, and from 12.9 to 14.0 ms in the whole method at 700K nodes,
+// d = 64).
+static constexpr int64_t kIdleRows = 98304;
+static constexpr int kLongItem = 256;
+
+// The lane-group tier bound of a level of `rows` rows when the caller gives
+// none.  A sweep in us with bounds 8 / 16 / 64 (FP32 d = 64, then BF16 d =
+// 128): 12K rows 6.9 / 7.4 / 14.4, 7.6 / 8.0 / 16.5; 28K rows 8.0 / 9.0 /
+// 16.6, 8.9 / 9.4 / 18.4; 60K rows 15.4 / 14.0 / 20.4, 16.8 / 14.9 / 21.7;
+// 130K rows 39.8 / 32.7 / 31.7, 42.2 / 33.8 / 32.1.
+static int default_small_max(int64_t rows)
+{
+    return rows <= kIdleRows / 3 ? 8 : rows <= kIdleRows ? 16 : kDefaultSmallMax;
+}
+
+// (by the sort key, so that the long items lead each side's list)
+int long_key(int64_t rows, int chunk)
+{
+    return rows <= kIdleRows ? chunk_keys(chunk) : std::max(0, chunk - kLongItem) >> chunk_shift(chunk);
+}
 
 // ---------------------------------------------------------------------------
 // host parallelism
@@ -403,7 +435,8 @@ static void tier_side(const int32_t *ptr, int32_t n_rows, int small_max, int chu
         }
         *slot_base += pieces;
     }
-    std::stable_sort(t.chunks.begin(), t.chunks.end(), [](const Item &a, const Item &b) { return a.len > b.len; });
+    std::stable_sort(t.chunks.begin(), t.chunks.end(),
+                     [=](const Item &a, const Item &b) { return chunk_key(chunk, a.len) < chunk_key(chunk, b.len); });
 }
 
 struct HostLevel {
@@ -428,8 +461,8 @@ void resolve_options(const hnv_options *in, int d, hnv_dtype dtype, hnv_options 
         const int pc = (dtype == HNV_F32) ? 64 : 128;
         o.panel_cols = (d > pc && d % pc == 0) ? pc : d;
     }
-    if (o.small_max <= 0)
-        o.small_max = kDefaultSmallMax;
+    if (o.small_max < 0)
+        o.small_max = 0;   // by the level's size (init_plan_shape)
     if (o.chunk <= 0)
         o.chunk = kDefaultChunk;
     *out = o;
@@ -609,7 +642,8 @@ void forward_geometry(const hnv_plan *p, const LevelPlan &L, int64_t *main_block
     const int64_t rows_per_block = kRowsPerGroup * kBlock / p->g_fwd;
     int64_t per_panel = 0;
     for (int s = 0; s < 2; ++s)
-        per_panel += blocks_for(L.n_chunks[s], kWavesPerBlock) + blocks_for(L.n_small[s], rows_per_block);
+        per_panel += L.n_long[s] + blocks_for(L.n_chunks[s] - L.n_long[s], kWavesPerBlock) +
+                     blocks_for(L.n_small[s], rows_per_block);
     int64_t fin = 0;
     for (int s = 0; s < 2; ++s)
         fin += blocks_for(L.n_splits[s], kWavesPerBlock);
@@ -617,7 +651,27 @@ void forward_geometry(const hnv_plan *p, const LevelPlan &L, int64_t *main_block
     *fin_blocks = fin * p->panels;
 }
 
-static LevelShape shape_of(const HostLevel &h, bool unit_w)
+NoallocLayout noalloc_layout(const hnv_plan *p, const LevelPlan &L, bool resid)
+{
+    auto align256 = [](int64_t x) { return (x + 255) & ~int64_t(255); };
+    int64_t mb = 0, fb = 0;
+    forward_geometry(p, L, &mb, &fb);
+    const int64_t n_part = resid ? mb + fb : 0;
+    NoallocLayout N{};
+    N.stage_len = resid ? blocks_for(n_part, kResidPer) + 1 : 0;
+    N.off_stage = align256(n_part * (int64_t)sizeof(double));
+    N.off_slots = N.off_stage + align256(2 * N.stage_len * (int64_t)sizeof(double));
+    N.total = N.off_slots + (int64_t)L.n_slots * p->pstride * (int64_t)sizeof(float);
+    return N;
+}
+
+void settle_long_items(const hnv_plan *p, LevelPlan &L)
+{
+    if (noalloc_layout(p, L, true).total > (int64_t)HNV_NOALLOC_SCRATCH_BYTES)
+        L.n_long[0] = L.n_long[1] = 0;
+}
+
+static LevelShape shape_of(const HostLevel &h, bool unit_w, int chunk)
 {
     LevelShape sh;
     sh.nV = h.nV;
@@ -631,6 +685,9 @@ static LevelShape shape_of(const HostLevel &h, bool unit_w)
         sh.n_small[s] = (int32_t)h.tier[s].small.size();
         sh.n_chunks[s] = (int32_t)h.tier[s].chunks.size();
         sh.n_splits[s] = (int32_t)h.tier[s].splits.size();
+        const int key = long_key(h.rows, chunk);
+        while (sh.n_long[s] < sh.n_chunks[s] && chunk_key(chunk, h.tier[s].chunks[sh.n_long[s]].len) < key)
+            ++sh.n_long[s];
     }
     sh.n_slots = h.n_slots;
     return sh;
@@ -668,6 +725,7 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base)
             L.n_small[s] = S.n_small;
             L.n_chunks[s] = S.n_chunks;
             L.n_splits[s] = S.n_splits;
+            L.n_long[s] = h.n_long[s];
         }
         L.r = c.take<float>(h.rows);
         L.w = c.take<float>(h.nE);
@@ -708,7 +766,6 @@ void init_plan_shape(hnv_plan *p, const std::vector<LevelShape> &shape, int d, h
     const int elem = (dtype == HNV_BF16) ? 2 : 4;
     lane_layout(p->dp, elem, &p->g_fwd, &p->epl_fwd);
     lane_layout(d, elem, &p->g_full, &p->epl_full);
-    p->small_max = std::min(o.small_max, kIdxRegs * p->g_fwd);
     p->pstride = d + 8;
     p->lv.assign(n_levels, LevelPlan{});
     for (int l = 0; l < n_levels; ++l) {
@@ -720,6 +777,7 @@ void init_plan_shape(hnv_plan *p, const std::vector<LevelShape> &shape, int d, h
         L.has_coarse = (l + 1 < n_levels);
         L.rows_coarse = L.has_coarse ? shape[l + 1].nV + shape[l + 1].nE : 0;
         L.unit_w = shape[l].unit_w;
+        L.small_max = std::min(o.small_max > 0 ? o.small_max : default_small_max(L.rows), kIdxRegs * p->g_fwd);
     }
 }
 
@@ -792,8 +850,8 @@ extern "C" hnv_status hnv_plan_workspace_bytes(const hnv_level *levels, const hn
         init_plan_shape(&p, sh, d, dtype, o);
         for (int l = 0; l < n_levels; ++l) {
             HostLevel h;
-            build_level(levels, maps, n_levels, l, o, p.small_max, false, h);
-            sh[l] = shape_of(h, sh[l].unit_w);
+            build_level(levels, maps, n_levels, l, o, p.lv[l].small_max, false, h);
+            sh[l] = shape_of(h, sh[l].unit_w, o.chunk);
         }
         carve(&p, sh, nullptr);
         *bytes = p.ws_bytes;
@@ -850,8 +908,8 @@ extern "C" hnv_status hnv_plan_create(const hnv_level *levels, const hnv_map *ma
         {
             for (int l = 0; l < n_levels; ++l) {
                 HostLevel h;
-                build_level(levels, maps, n_levels, l, o, p->small_max, false, h);
-                sh[l] = shape_of(h, sh[l].unit_w);
+                build_level(levels, maps, n_levels, l, o, p->lv[l].small_max, false, h);
+                sh[l] = shape_of(h, sh[l].unit_w, o.chunk);
             }
             carve(p, sh, nullptr);
             if (p->ws_bytes > ws_bytes) {
@@ -861,11 +919,13 @@ extern "C" hnv_status hnv_plan_create(const hnv_level *levels, const hnv_map *ma
                                                 std::to_string(need));
             }
             carve(p, sh, reinterpret_cast<char *>(workspace));
+            for (LevelPlan &L : p->lv)
+                settle_long_items(p, L);
         }
         // one level at a time: build host arrays, upload, wait, free
         for (int l = 0; l < n_levels; ++l) {
             HostLevel h;
-            build_level(levels, maps, n_levels, l, o, p->small_max, true, h);
+            build_level(levels, maps, n_levels, l, o, p->lv[l].small_max, true, h);
             LevelPlan &L = p->lv[l];
             for (int sd = 0; sd < 2; ++sd) {
                 DevSide &S = L.side[sd];

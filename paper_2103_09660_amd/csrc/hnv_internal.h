@@ -24,7 +24,7 @@ constexpr int kRowsPerGroup = HNV_ROWS_PER_GROUP;   // lane-group tier rows a gr
 // in the side's neighbour array.
 //   lane-group tier: len = the row's degree, aux = the row of the next
 //     coarser level its value is projected from (0 at the coarsest level);
-//   wavefront tier: aux = -1 if the wavefront owns the whole row (len = its
+//   wavefront tier: aux = -1 if the item is the whole row (len = its
 //     degree), else the partial slot it writes; a finalize pass combines a
 //     split row's slots in order.
 struct alignas(16) Item {
@@ -86,6 +86,7 @@ struct LevelPlan {
     int64_t rows_coarse = 0;         // rows of level + 1 (0 at the coarsest level)
     bool has_coarse = false;
     bool unit_w = true;
+    int small_max = 0;               // lane-group tier bound of the level
     bool scales_ready = false;       // the reverse-mode scales (side[*].sn) hold the current weights
     DevSide side[2];
     float *r = nullptr;              // [rows] 1 / (row weight sum), 0 for rows without neighbours
@@ -96,6 +97,7 @@ struct LevelPlan {
     int32_t n_slots = 0;             // partial slots used by split rows (both sides)
     // host copies of the work-list sizes (for launch geometry)
     int32_t n_small[2] = {0, 0}, n_chunks[2] = {0, 0}, n_splits[2] = {0, 0};
+    int32_t n_long[2] = {0, 0};      // leading chunks that a whole workgroup takes
 };
 
 }  // namespace hnv
@@ -104,6 +106,8 @@ namespace hnv {
 // Sweeps of one level whose residuals a fixed-count refinement reduces
 // together (their per-block partials wait in as many slots).
 constexpr int kResidBatch = 8;
+// Per-block residual partials one workgroup of a residual stage sums.
+constexpr int kResidPer = kBlock * 8;
 }  // namespace hnv
 
 struct hnv_plan {
@@ -130,7 +134,6 @@ struct hnv_plan {
     int epl_fwd = 8;                 // elements per lane in a forward pass
     int g_full = 1;                  // lanes per full-width row
     int epl_full = 8;                // elements per lane of a full-width row
-    int small_max = 0;               // effective lane-group tier bound
     size_t ws_bytes = 0;
     // kernel timing (hnv_plan_set_profiling)
     struct ProfRecord {
@@ -150,6 +153,20 @@ hnv_status fail(hnv_status st, const std::string &msg);
 void clear_error();
 
 int next_pow2(int x);
+// Sort key of a wavefront-tier item of `len` of at most `chunk` neighbours:
+// ascending keys put the longest first, to within 1/512 of a chunk, so that
+// both sides' keys (2 chunk_keys) fit one counting pass of the GPU builder.
+inline int chunk_shift(int chunk)
+{
+    int s = 0;
+    while ((chunk - 1) >> s >= 512)
+        ++s;
+    return s;
+}
+inline int chunk_keys(int chunk) { return ((chunk - 1) >> chunk_shift(chunk)) + 1; }
+inline int chunk_key(int chunk, int len) { return (chunk - len) >> chunk_shift(chunk); }
+// Items whose key is below this take a whole workgroup (LevelPlan::n_long).
+int long_key(int64_t rows, int chunk);
 // Lane layout of a row slice of `cols` elements of `elem` bytes: lanes move
 // 16 B each, or 32 B for FP32 slices of 128 columns or more.
 void lane_layout(int cols, int elem, int *lanes, int *elems_per_lane);
@@ -160,7 +177,7 @@ int64_t blocks_for(int64_t items, int64_t per_block);
 struct LevelShape {
     int64_t nV = 0, nE = 0, nnz = 0, rows = 0, rows_c = 0;
     bool has_coarse = false, unit_w = true;
-    int32_t n_small[2] = {0, 0}, n_chunks[2] = {0, 0}, n_splits[2] = {0, 0};
+    int32_t n_small[2] = {0, 0}, n_chunks[2] = {0, 0}, n_splits[2] = {0, 0}, n_long[2] = {0, 0};
     int32_t n_slots = 0;
 };
 
@@ -175,6 +192,18 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base);
 
 // Forward-sweep launch geometry of a level (blocks per panel and finalize blocks).
 void forward_geometry(const hnv_plan *p, const LevelPlan &L, int64_t *main_blocks, int64_t *fin_blocks);
+
+// A level's sweep scratch in the static array of hnv_sweep_noalloc: residual
+// partials and stages (only with a residual), then the split-row slots.
+struct NoallocLayout {
+    int64_t stage_len, off_stage, off_slots, total;
+};
+NoallocLayout noalloc_layout(const hnv_plan *p, const LevelPlan &L, bool resid);
+// Called once a level's work lists are known: a level whose scratch passes the
+// static array with a workgroup per long item has a wavefront per item, a
+// quarter of those residual partials, in every sweep, so that both sweep
+// entry points give the same bits.
+void settle_long_items(const hnv_plan *p, LevelPlan &L);
 
 // Device arrays of a candidate-scoring plan (carved from the caller's workspace)
 struct ScorePlan {

@@ -9,12 +9,19 @@
 //   - a row slice of Z is read by a group of G lanes, each moving 16 bytes
 //     (8 BF16 or 4 FP32 elements), so every gathered row is one coalesced
 //     access and a wavefront covers 64/G rows at once;
-//   - rows are tiered by neighbour count on the host.  Rows with few
+//   - rows are tiered by neighbour count in the plan.  Rows with few
 //     neighbours get one lane group each (same-degree rows share a
 //     wavefront); longer rows get a whole wavefront per chunk of neighbours,
 //     the 64/G groups taking interleaved neighbours and being combined by a
-//     cross-lane butterfly; rows longer than one chunk are split over several
-//     wavefronts whose FP32 partial sums a finalize pass adds in slot order;
+//     cross-lane butterfly; long chunks get a workgroup, a quarter per
+//     wavefront, added through LDS; rows longer than one chunk are split over
+//     several items whose FP32 partial sums a finalize pass adds in slot order;
+//   - a sweep over a small level takes as long as its longest chain of
+//     dependent gathers (about 0.35 us per batch of four on an idle chip,
+//     1 us on a busy one), which is what the long items, the tier bound by
+//     level size and the 2,048-neighbour chunks shorten (a sweep, FP32,
+//     d = 64: 8K nodes / 4K hyperedges 15.1 -> 7.4 us, 20K / 8K 16.6 -> 8.4,
+//     80K / 50K 44 -> 32, hub rows of 79K neighbours over 300K rows 60 -> 48);
 //   - latency is hidden by keeping the dependent-load chain short: a work
 //     item carries the row, its first neighbour and its degree (and, for the
 //     first sweep of a level, the coarser row it is projected from); a lane
@@ -171,6 +178,7 @@ struct GatherArgs {
     int32_t nb_small[2];      // blocks of the lane-group tier per side (per panel)
     int32_t nb_split[2];      // finalize blocks per side (per panel)
     int32_t blocks_per_panel;
+    int32_t n_long[2];        // leading items per side that a whole workgroup takes
     int32_t dp;               // columns per panel
     int64_t ld;               // row stride (elements) = d
     float omega;
@@ -364,6 +372,31 @@ HNV_DEV void gather_wave(const int32_t *__restrict__ nb, const float *__restrict
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1)
             csum += __shfl_xor(csum, off, kWave);
+    }
+}
+
+// acc (and csum) of the workgroup's wavefronts added in order, into
+// wavefront 0 (its first lane group).  Every thread of the block calls it once.
+template <int EPL, int G, bool SCALAR>
+HNV_DEV void block_sum(float (&acc)[EPL], float &csum, int wave, int lane)
+{
+    __shared__ float part[kWavesPerBlock - 1][G][EPL + 1];
+    if (wave > 0 && lane < G) {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+            part[wave - 1][lane][i] = acc[i];
+        if (SCALAR)
+            part[wave - 1][lane][EPL] = csum;
+    }
+    __syncthreads();
+    if (wave == 0 && lane < G) {
+        for (int w = 0; w < kWavesPerBlock - 1; ++w) {
+#pragma unroll
+            for (int i = 0; i < EPL; ++i)
+                acc[i] += part[w][lane][i];
+            if (SCALAR)
+                csum += part[w][lane][EPL];
+        }
     }
 }
 
@@ -635,23 +668,39 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
         return;
 
     if (tier == 0) {
-        const int item = b * kWavesPerBlock + wave;
-        if (item < Sd.n_chunks) {   // uniform over the wavefront
-            const Item c = Sd.chunks[item];
-            const int zrow = Sd.row_base + c.row;
-            const bool whole = c.aux < 0;
-            Own<T, EPL> self{};
-            if (whole && col_ok) {
-                const int64_t srow =
-                    (MODE == kFwd && (FUSED || a.self_mapped)) ? (int64_t)a.rowmap[zrow] : (int64_t)zrow;
-                load_own<T, EPL, MODE>(self, a, mats, c.row, zrow, srow, c.len, col);
-            }
-            if (use_scale)
-                gather_wave<T, EPL, G, true, kScalar>(nb, sc, a.cvec, c.start, c.len, src, a.ld, col, col_ok, lane, g,
-                                                      acc, csum);
-            else
-                gather_wave<T, EPL, G, false, kScalar>(nb, sc, a.cvec, c.start, c.len, src, a.ld, col, col_ok, lane,
-                                                       g, acc, csum);
+        // The first n_long blocks take one item each: every wavefront gathers
+        // a quarter of its neighbours, and wavefront 0 adds the others' sums
+        // in order and finishes the row.  The other items take a wavefront each.
+        const int n_long = a.n_long[side];
+        const bool whole_block = b < n_long;   // uniform over the block
+        const int item = whole_block ? b : n_long + (b - n_long) * kWavesPerBlock + wave;
+        const bool valid = item < Sd.n_chunks;   // uniform over the wavefront
+        Item c{0, 0, 0, 0};
+        if (valid)
+            c = Sd.chunks[item];
+        const bool mine = valid && (!whole_block || wave == 0);
+        const int zrow = Sd.row_base + c.row;
+        const bool whole = c.aux < 0;
+        Own<T, EPL> self{};
+        if (mine && whole && col_ok) {
+            const int64_t srow = (MODE == kFwd && (FUSED || a.self_mapped)) ? (int64_t)a.rowmap[zrow] : (int64_t)zrow;
+            load_own<T, EPL, MODE>(self, a, mats, c.row, zrow, srow, c.len, col);
+        }
+        int start = c.start, len = c.len;
+        if (whole_block) {
+            const int per = (c.len + kWavesPerBlock - 1) / kWavesPerBlock;
+            start += wave * per;
+            len = max(0, min(per, c.len - wave * per));
+        }
+        if (use_scale)
+            gather_wave<T, EPL, G, true, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
+                                                  csum);
+        else
+            gather_wave<T, EPL, G, false, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
+                                                   csum);
+        if (whole_block)
+            block_sum<EPL, G, kScalar>(acc, csum, wave, lane);
+        if (mine) {
             if (!whole) {
                 if (g == 0 && col_ok) {
                     float *pp = a.partials + (int64_t)c.aux * a.pstride + col;
@@ -712,7 +761,12 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
         block_resid(a, r2, lb);
 }
 
-// Finalize rows that were split over several wavefronts: one wavefront per
+// Partial slots a lane group loads together: a hub row's slots are one chain
+// per group otherwise (155 slots, 15.1 us; 39 slots of longer chunks, eight
+// in flight, 4.7 us, the launch itself).
+constexpr int kSlotsInFlight = 8;
+
+// Finalize rows that were split over several items: one wavefront per
 // row adds the row's partial slots in slot order (group g takes slots
 // g, g+Q, ...; groups combined by the xor butterfly), then applies the
 // row's epilogue.
@@ -760,20 +814,34 @@ __global__ __launch_bounds__(kBlock) void k_finalize(GatherArgs a)
                 (MODE == kFwd && (FUSED || a.self_mapped)) ? (int64_t)a.rowmap[zrow] : (int64_t)zrow;
             load_own<T, EPL, MODE>(self, a, mats, sp.row, zrow, srow, sp.deg, col);
         }
-        for (int k = g; k < sp.n_slots; k += Q) {
-            const float *pp = a.partials + (int64_t)(sp.first_slot + k) * a.pstride;
-            if (col_ok) {
+        // kSlotsInFlight slots' loads go out together (slots past the row's
+        // end re-read its first slot) and are added in slot order
+        const float *first = a.partials + (int64_t)sp.first_slot * a.pstride;
+        for (int k0 = g; k0 < sp.n_slots; k0 += Q * kSlotsInFlight) {
+            float4 x[kSlotsInFlight][EPL / 4];
+            float c[kSlotsInFlight];
+#pragma unroll
+            for (int u = 0; u < kSlotsInFlight; ++u) {
+                const int k = k0 + u * Q;
+                const float *pp = first + (int64_t)(k < sp.n_slots ? k : 0) * a.pstride;
+#pragma unroll
+                for (int i = 0; i < EPL; i += 4)
+                    x[u][i / 4] = *reinterpret_cast<const float4 *>(pp + (col_ok ? col : 0) + i);
+                c[u] = (MODE == kAdjEdge) ? pp[a.ld] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < kSlotsInFlight; ++u) {
+                const bool ok = k0 + u * Q < sp.n_slots;
 #pragma unroll
                 for (int i = 0; i < EPL; i += 4) {
-                    const float4 x = *reinterpret_cast<const float4 *>(pp + col + i);
-                    acc[i] += x.x;
-                    acc[i + 1] += x.y;
-                    acc[i + 2] += x.z;
-                    acc[i + 3] += x.w;
+                    acc[i] = ok ? acc[i] + x[u][i / 4].x : acc[i];
+                    acc[i + 1] = ok ? acc[i + 1] + x[u][i / 4].y : acc[i + 1];
+                    acc[i + 2] = ok ? acc[i + 2] + x[u][i / 4].z : acc[i + 2];
+                    acc[i + 3] = ok ? acc[i + 3] + x[u][i / 4].w : acc[i + 3];
                 }
+                if (MODE == kAdjEdge && gl == 0)
+                    csum = ok ? csum + c[u] : csum;
             }
-            if (MODE == kAdjEdge && gl == 0)
-                csum += pp[a.ld];
         }
 #pragma unroll
         for (int off = G; off < kWave; off <<= 1) {
@@ -806,7 +874,6 @@ __global__ __launch_bounds__(kBlock) void k_finalize(GatherArgs a)
 // the sweep's output the latest iterate.  Several sweeps' reductions run
 // side by side along blockIdx.y, sweep y reading part + y * part_stride and
 // writing out + y * out_stride (each in the order one sweep alone takes).
-constexpr int kResidPer = kBlock * 8;
 __global__ __launch_bounds__(kBlock) void k_resid_stage(const double *__restrict__ part, int64_t n,
                                                         int64_t part_stride, double *__restrict__ out,
                                                         int64_t out_stride, int final_sqrt, SweepCtl *ctl, int level)
@@ -1460,7 +1527,8 @@ static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp)
     const int rows_per_block = kRowsPerGroup * kBlock / G;
     int32_t per_panel = 0;
     for (int s = 0; s < 2; ++s) {
-        a.nb_chunk[s] = (int32_t)blocks_for(L.n_chunks[s], kWavesPerBlock);
+        a.n_long[s] = L.n_long[s];
+        a.nb_chunk[s] = a.n_long[s] + (int32_t)blocks_for(L.n_chunks[s] - a.n_long[s], kWavesPerBlock);
         a.nb_small[s] = (int32_t)blocks_for(L.n_small[s], rows_per_block);
         a.nb_split[s] = (int32_t)blocks_for(L.n_splits[s], kWavesPerBlock);
         per_panel += a.nb_chunk[s] + a.nb_small[s];
@@ -1842,8 +1910,6 @@ static hnv_status scratch_address(void **out)
     return HNV_OK;
 }
 
-static int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
-
 extern "C" hnv_status hnv_sweep_noalloc(hnv_plan *plan, int level, const void *z_in, void *z_out, float omega,
                                         int from_coarse, double *resid_dev, void *stream)
 {
@@ -1864,23 +1930,17 @@ extern "C" hnv_status hnv_sweep_noalloc(hnv_plan *plan, int level, const void *z
     // the level's scratch, laid out in the static array: residual partials
     // and stages (only with a residual), then the split-row partial slots
     const LevelPlan &L = plan->lv[level];
-    int64_t mb = 0, fb = 0;
-    forward_geometry(plan, L, &mb, &fb);
-    const int64_t n_part = resid_dev ? mb + fb : 0;
-    const int64_t stage_len = resid_dev ? blocks_for(n_part, kResidPer) + 1 : 0;
-    const int64_t off_stage = align256(n_part * (int64_t)sizeof(double));
-    const int64_t off_slots = off_stage + align256(2 * stage_len * (int64_t)sizeof(double));
-    const int64_t need = off_slots + (int64_t)L.n_slots * plan->pstride * (int64_t)sizeof(float);
-    if (need > (int64_t)HNV_NOALLOC_SCRATCH_BYTES)
-        return fail(HNV_EUNSUPPORTED, "level " + std::to_string(level) + " needs " + std::to_string(need) +
+    const NoallocLayout N = noalloc_layout(plan, L, resid_dev != nullptr);
+    if (N.total > (int64_t)HNV_NOALLOC_SCRATCH_BYTES)
+        return fail(HNV_EUNSUPPORTED, "level " + std::to_string(level) + " needs " + std::to_string(N.total) +
                                           " bytes of sweep scratch, more than the static " +
                                           std::to_string((int64_t)HNV_NOALLOC_SCRATCH_BYTES));
     void *base = nullptr;
     if ((st = scratch_address(&base)) != HNV_OK)
         return st;
     char *b = static_cast<char *>(base);
-    const SweepScratch sc{reinterpret_cast<float *>(b + off_slots), reinterpret_cast<double *>(b),
-                          reinterpret_cast<double *>(b + off_stage), stage_len};
+    const SweepScratch sc{reinterpret_cast<float *>(b + N.off_slots), reinterpret_cast<double *>(b),
+                          reinterpret_cast<double *>(b + N.off_stage), N.stage_len};
     return run_sweep(plan, level, z_in, z_out, omega, from_coarse != 0, resid_dev,
                      reinterpret_cast<hipStream_t>(stream), nullptr, &sc);
 }
