@@ -517,24 +517,52 @@ __global__ void k_sizes(const int32_t *__restrict__ gflag, const int32_t *__rest
 // feature-based assignment (bag-of-words counts, int32 [rows x k], k % 4 == 0)
 // ---------------------------------------------------------------------------
 
-// counts must be >= 0 (flag bit 4) and their total below 2^31 (checked on
-// the host from `total`); with that bound every sum, product and dot below
-// fits its integer type exactly
-__global__ __launch_bounds__(kThreads) void k_fcheck(const int4 *__restrict__ x, int64_t n4, int *__restrict__ flag,
-                                                     unsigned long long *__restrict__ total)
+// Counts must be >= 0 (flag bit 4) and their total below 2^31 (checked on the
+// host from `total`); with that bound every sum, product and dot below fits
+// its integer type exactly.  The same pass takes the largest count and writes
+// every count's low byte to x8 (rows of kp bytes, the columns past k zero;
+// null: not wanted), which holds the counts themselves when the largest is at
+// most 255.  Bound by the 4 bytes read per count.
+__global__ __launch_bounds__(kThreads) void k_fcheck(const int4 *__restrict__ x, int64_t n_rows, int k4, int kp4,
+                                                     int *__restrict__ flag, int *__restrict__ largest,
+                                                     unsigned long long *__restrict__ total,
+                                                     uint32_t *__restrict__ x8)
 {
     __shared__ unsigned long long part[kThreads / kWave];
     unsigned long long sum = 0;
-    int neg = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n4; i += (int64_t)gridDim.x * kThreads) {
-        const int4 v = x[i];
-        neg |= (v.x | v.y | v.z | v.w) < 0;
-        sum += (unsigned long long)(uint32_t)v.x + (uint32_t)v.y + (uint32_t)v.z + (uint32_t)v.w;
+    int neg = 0, most = 0;
+    // thread i takes word i of the byte matrix, then every stride-th
+    const int64_t n = n_rows * kp4, stride = (int64_t)gridDim.x * kThreads;
+    int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    int64_t row = i / kp4, step_rows = stride / kp4;
+    int col = (int)(i - row * kp4), step_cols = (int)(stride - step_rows * kp4);
+    for (; i < n; i += stride) {
+        uint32_t w = 0;
+        if (col < k4) {
+            const int4 v = x[row * k4 + col];
+            neg |= (v.x | v.y | v.z | v.w) < 0;
+            most = max(max(most, max(v.x, v.y)), max(v.z, v.w));
+            sum += (unsigned long long)(uint32_t)v.x + (uint32_t)v.y + (uint32_t)v.z + (uint32_t)v.w;
+            w = (v.x & 255) | (v.y & 255) << 8 | (v.z & 255) << 16 | (uint32_t)(v.w & 255) << 24;
+        }
+        if (x8)
+            x8[i] = w;
+        row += step_rows;
+        col += step_cols;
+        if (col >= kp4) {
+            col -= kp4;
+            ++row;
+        }
     }
-    for (int o = kWave / 2; o > 0; o >>= 1)
+    for (int o = kWave / 2; o > 0; o >>= 1) {
         sum += __shfl_xor(sum, o);
-    if ((threadIdx.x & (kWave - 1)) == 0)
+        most = max(most, __shfl_xor(most, o));
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
         part[threadIdx.x / kWave] = sum;
+        if (most > *largest)   // an earlier read bounds the maximum from below
+            atomicMax(largest, most);
+    }
     if (neg)
         atomicOr(flag, 16);
     __syncthreads();
@@ -803,6 +831,357 @@ void launch_group_sums(dim3 grid, hipStream_t st, const int32_t *gptr, const int
     k_rowsum<false, NC><<<grid, kThreads, 0, st>>>(gptr, gnodes, x, k, n_rows, limit, out, nullptr);
 }
 
+// ---------------------------------------------------------------------------
+// feature-based assignment on counts of at most 255: rows of kp bytes
+//
+// The member rows are gathered once, as bytes, by the wavefront that sums
+// them, and the scores are taken there too, while the sum is in registers: a
+// quarter of the bytes of the int32 rows, read once (short hyperedges) or
+// again from cache, and no sum matrix written and read back.  Bound by the
+// gather of kp bytes per incidence.  A row is read by a group of G lanes of
+// 16 bytes (kp <= 16 G); the 64 / G groups of a wavefront take interleaved
+// members.  Sums and dot products are integer, so their order is free.
+// Measured at 1M nodes, 600K hyperedges, 4.5M incidences, k = 512, a step's
+// average over 6: member sums and scores 2.84 -> 0.62 ms, X' 0.26 -> 0.20 ms,
+// and the checking pass over X, which now writes the bytes too, 0.18 -> 0.24 ms.
+// ---------------------------------------------------------------------------
+
+constexpr int kByteCols = 1024;     // widest row of the byte path: one 16-byte piece per lane
+constexpr int kByteSmall = 64;      // members of a hyperedge one wavefront takes
+constexpr int kByteRows = 4;        // member rows in flight per lane group
+
+inline int byte_stride(int k) { return (k + 15) / 16 * 16; }
+
+// 16 counts of a lane as sums of bytes: s[i] holds columns 4 i and 4 i + 2 of
+// the lane's piece in its low and high half (ev) and columns 4 i + 1 and
+// 4 i + 3 (od); exact for at most 257 rows.
+struct ByteSum {
+    uint32_t ev[4], od[4];
+    __device__ void zero()
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            ev[i] = od[i] = 0;
+    }
+    __device__ void add(const uint4 &r)
+    {
+        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ev[i] += w[i] & 0x00ff00ffu;
+            od[i] += (w[i] >> 8) & 0x00ff00ffu;
+        }
+    }
+};
+
+__device__ inline uint32_t dot4(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_udot4(a, b, c, false); }
+
+// dot of two 16-byte pieces
+__device__ inline uint32_t dot16(const uint32_t (&p)[4], const uint4 &r)
+{
+    return dot4(p[3], r.w, dot4(p[2], r.z, dot4(p[1], r.y, dot4(p[0], r.x, 0u))));
+}
+
+__device__ inline uint32_t dot16(const uint32_t (&p)[4], const uint32_t (&q)[4])
+{
+    return dot4(p[3], q[3], dot4(p[2], q[2], dot4(p[1], q[1], dot4(p[0], q[0], 0u))));
+}
+
+// sum over the G lanes of a group
+template <int G, typename V>
+__device__ inline V lanes_sum(V v)
+{
+#pragma unroll
+    for (int o = 1; o < G; o <<= 1)
+        v += __shfl_xor(v, o);
+    return v;
+}
+
+// The sums of d[0..3] over the G lanes of a group, d[u] returned to the lanes
+// gl with slot_of<G>(gl) == u (the exchanges halve the values left, so four
+// sums cost little more than one).
+template <int G>
+__device__ inline int slot_of(int gl)
+{
+    return G >= 4 ? ((gl & 1) << 1 | ((gl >> 1) & 1)) : -1;
+}
+
+template <int G, typename V>
+__device__ inline V lanes_sum4(const V (&d)[4], int gl)
+{
+    const bool b0 = gl & 1, b1 = gl & 2;
+    V a = b0 ? d[2] : d[0], b = b0 ? d[3] : d[1];
+    a += __shfl_xor(b0 ? d[0] : d[2], 1);
+    b += __shfl_xor(b0 ? d[1] : d[3], 1);
+    V v = b1 ? b : a;
+    v += __shfl_xor(b1 ? a : b, 2);
+#pragma unroll
+    for (int o = 4; o < G; o <<= 1)
+        v += __shfl_xor(v, o);
+    return v;
+}
+
+// the score of incidence j (node v), as k_qscore writes it
+__device__ inline void put_score(int64_t j, int32_t v, int64_t d, int64_t s2, double *__restrict__ q,
+                                 unsigned long long *__restrict__ bestq)
+{
+    const double sc = cosine_score(d, s2);
+    q[j] = sc;
+    const unsigned long long ob = ordered_bits(sc);
+    if (ob > bestq[v])   // an earlier read bounds the maximum from below
+        atomicMax(bestq + v, ob);
+}
+
+// Hyperedges of at most kByteSmall members, a wavefront each.
+template <int G>
+__global__ __launch_bounds__(kThreads) void k_byte_scores(const int32_t *__restrict__ ptr,
+                                                          const int32_t *__restrict__ idx,
+                                                          const unsigned char *__restrict__ x8, int kp,
+                                                          int64_t n_edges, double *__restrict__ q,
+                                                          unsigned long long *__restrict__ bestq)
+{
+    constexpr int Q = kWave / G, U = kByteRows;
+    const int64_t e = linear_block() * (kThreads / kWave) + threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), g = lane / G, gl = lane % G;
+    if (e >= n_edges)
+        return;   // uniform over the wavefront
+    const int32_t a = ptr[e], m = ptr[e + 1] - a;
+    if (m > kByteSmall)
+        return;
+    const bool col_ok = gl * 16 < kp;
+    const int32_t my_v = lane < m ? idx[a + lane] : 0;
+    auto load_rows = [&](uint4 (&r)[U], int t) {   // members t + u Q + g
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = t + u * Q + g;
+            const int32_t v = __shfl(my_v, j & (kWave - 1));
+            r[u] = make_uint4(0, 0, 0, 0);
+            if (j < m && col_ok)
+                r[u] = *reinterpret_cast<const uint4 *>(x8 + (int64_t)v * kp + gl * 16);
+        }
+    };
+    uint4 first[U];
+    load_rows(first, 0);
+    ByteSum s;
+    s.zero();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        s.add(first[u]);
+    for (int t = U * Q; t < m; t += U * Q) {
+        uint4 r[U];
+        load_rows(r, t);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            s.add(r[u]);
+    }
+#pragma unroll
+    for (int o = G; o < kWave; o <<= 1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s.ev[i] += __shfl_xor(s.ev[i], o);
+            s.od[i] += __shfl_xor(s.od[i], o);
+        }
+    }
+    // the sums as byte planes: s = lo + 256 hi
+    uint32_t lo[4], hi[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        lo[i] = (s.ev[i] & 0x00ff00ffu) | (s.od[i] & 0x00ff00ffu) << 8;
+        hi[i] = ((s.ev[i] >> 8) & 0x00ff00ffu) | (s.od[i] & 0xff00ff00u);
+    }
+    const uint32_t l2 = lanes_sum<G>(dot16(lo, lo)), lh = lanes_sum<G>(dot16(lo, hi)), h2 = lanes_sum<G>(dot16(hi, hi));
+    const int64_t s2 = (int64_t)l2 + 512 * (int64_t)lh + 65536 * (int64_t)h2;
+    for (int t = 0; t < m; t += U * Q) {
+        if (t > 0)
+            load_rows(first, t);
+        uint32_t dl[4], dh[4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            dl[u] = dot16(lo, first[u]);
+            dh[u] = dot16(hi, first[u]);
+        }
+        if constexpr (G >= 4) {
+            const uint32_t tl = lanes_sum4<G>(dl, gl);
+            const uint32_t th = h2 ? lanes_sum4<G>(dh, gl) : 0u;   // uniform: h2 = 0 iff every high byte is 0
+            const int j = t + slot_of<G>(gl) * Q + g;
+            const int32_t v = __shfl(my_v, j & (kWave - 1));
+            if (gl < 4 && j < m)
+                put_score(a + j, v, (int64_t)tl + 256 * (int64_t)th, s2, q, bestq);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t d = (int64_t)lanes_sum<G>(dl[u]) + 256 * (int64_t)lanes_sum<G>(dh[u]);
+                const int j = t + u * Q + g;
+                const int32_t v = __shfl(my_v, j & (kWave - 1));
+                if (gl == 0 && j < m)
+                    put_score(a + j, v, d, s2, q, bestq);
+            }
+        }
+    }
+}
+
+// Longer hyperedges: each workgroup finds those of a window of kByteWindow
+// hyperedges and takes them one after the other, members interleaved over
+// its wavefronts' lane groups, the sum in LDS (counts total below 2^31, so
+// every sum fits 32 bits) and then as four byte planes in registers.
+constexpr int kByteWindow = 32;
+
+template <int G>
+__global__ __launch_bounds__(kThreads) void k_byte_scores_long(const int32_t *__restrict__ ptr,
+                                                               const int32_t *__restrict__ idx,
+                                                               const unsigned char *__restrict__ x8, int kp,
+                                                               int64_t n_edges, double *__restrict__ q,
+                                                               unsigned long long *__restrict__ bestq)
+{
+    constexpr int U = kByteRows, P = kThreads / G;   // lane groups of the workgroup
+    __shared__ uint32_t sum[G * 16];
+    const int64_t e0 = linear_block() * kByteWindow;
+    const int lane = threadIdx.x & (kWave - 1), gl = threadIdx.x % G, p = threadIdx.x / G;
+    int32_t my_a = 0, my_m = 0;
+    if (lane < kByteWindow && e0 + lane < n_edges) {
+        my_a = ptr[e0 + lane];
+        my_m = ptr[e0 + lane + 1] - my_a;
+    }
+    const bool col_ok = gl * 16 < kp;
+    for (uint64_t todo = __ballot(my_m > kByteSmall); todo; todo &= todo - 1) {   // the same in every wavefront
+        const int w = __ffsll((long long)todo) - 1;
+        const int32_t a = __shfl(my_a, w), m = __shfl(my_m, w);
+        __syncthreads();
+        for (int c = threadIdx.x; c < G * 16; c += kThreads)
+            sum[c] = 0;
+        __syncthreads();
+        auto load_rows = [&](uint4 (&r)[U], int32_t t) {   // members t + u P + p
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t j = t + u * P + p;
+                r[u] = make_uint4(0, 0, 0, 0);
+                if (j < m && col_ok)
+                    r[u] = *reinterpret_cast<const uint4 *>(x8 + (int64_t)idx[a + j] * kp + gl * 16);
+            }
+        };
+        // at most 256 rows per lane group before its sums move to LDS
+        for (int32_t t0 = 0; t0 < m; t0 += 256 * P) {
+            ByteSum s;
+            s.zero();
+            const int32_t end = min(m, t0 + 256 * P);
+            for (int32_t t = t0; t < end; t += U * P) {
+                uint4 r[U];
+                load_rows(r, t);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    s.add(r[u]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                atomicAdd(&sum[gl * 16 + 4 * i], s.ev[i] & 0xffffu);
+                atomicAdd(&sum[gl * 16 + 4 * i + 1], s.od[i] & 0xffffu);
+                atomicAdd(&sum[gl * 16 + 4 * i + 2], s.ev[i] >> 16);
+                atomicAdd(&sum[gl * 16 + 4 * i + 3], s.od[i] >> 16);
+            }
+        }
+        __syncthreads();
+        uint32_t plane[4][4];
+        int64_t s2 = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t c[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                c[b] = sum[gl * 16 + 4 * i + b];
+                s2 += (int64_t)c[b] * (int64_t)c[b];
+            }
+#pragma unroll
+            for (int y = 0; y < 4; ++y)
+                plane[y][i] = ((c[0] >> (8 * y)) & 255u) | ((c[1] >> (8 * y)) & 255u) << 8 |
+                              ((c[2] >> (8 * y)) & 255u) << 16 | ((c[3] >> (8 * y)) & 255u) << 24;
+        }
+        s2 = lanes_sum<G>(s2);
+        for (int32_t t = 0; t < m; t += U * P) {
+            uint4 r[U];
+            load_rows(r, t);
+            int64_t d[4];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                d[u] = (int64_t)dot16(plane[0], r[u]) + ((int64_t)dot16(plane[1], r[u]) << 8) +
+                       ((int64_t)dot16(plane[2], r[u]) << 16) + ((int64_t)dot16(plane[3], r[u]) << 24);
+            if constexpr (G >= 4) {
+                const int64_t v = lanes_sum4<G>(d, gl);
+                const int32_t j = t + slot_of<G>(gl) * P + p;
+                if (gl < 4 && j < m)
+                    put_score((int64_t)a + j, idx[a + j], v, s2, q, bestq);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t v = lanes_sum<G>(d[u]);
+                    const int32_t j = t + u * P + p;
+                    if (gl == 0 && j < m)
+                        put_score((int64_t)a + j, idx[a + j], v, s2, q, bestq);
+                }
+            }
+        }
+    }
+}
+
+// out[r] = sum of the byte rows of members [ptr[r], ptr[r+1]) as int32, for r
+// below *limit; one wavefront per row, 4 counts per lane and pass (NC = passes
+// of 256 counts).  Bound by the 4 bytes written per count.
+template <int NC>
+__global__ __launch_bounds__(kThreads) void k_rowsum_bytes(const int32_t *__restrict__ ptr,
+                                                           const int32_t *__restrict__ idx,
+                                                           const uint32_t *__restrict__ x8, int k4, int kp4,
+                                                           int64_t n_rows, const int64_t *__restrict__ limit,
+                                                           int4 *__restrict__ out)
+{
+    constexpr int U = 4;
+    const int64_t r = linear_block() * (kThreads / kWave) + threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    if (r >= n_rows || r >= *limit)
+        return;
+    const int32_t a = ptr[r], b = ptr[r + 1];
+    int4 acc[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+        acc[i] = make_int4(0, 0, 0, 0);
+    for (int32_t j = a; j < b; j += U) {
+        uint32_t w[U][NC];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t base = (j + u < b) ? (int64_t)idx[j + u] * kp4 : 0;
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                const int c = lane + i * kWave;
+                w[u][i] = (j + u < b && c < kp4) ? x8[base + c] : 0u;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                acc[i].x += w[u][i] & 255u;
+                acc[i].y += (w[u][i] >> 8) & 255u;
+                acc[i].z += (w[u][i] >> 16) & 255u;
+                acc[i].w += w[u][i] >> 24;
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const int c = lane + i * kWave;
+        if (c < k4)
+            out[r * k4 + c] = acc[i];
+    }
+}
+
+template <int G>
+void launch_byte_scores(hipStream_t st, const int32_t *ptr, const int32_t *idx, const unsigned char *x8, int kp,
+                        int64_t n_edges, int64_t nnz, double *q, unsigned long long *bestq)
+{
+    const int per = kThreads / kWave;
+    k_byte_scores<G><<<fold_grid((n_edges + per - 1) / per), kThreads, 0, st>>>(ptr, idx, x8, kp, n_edges, q, bestq);
+    if (nnz > kByteSmall)
+        k_byte_scores_long<G><<<fold_grid((n_edges + kByteWindow - 1) / kByteWindow), kThreads, 0, st>>>(
+            ptr, idx, x8, kp, n_edges, q, bestq);
+}
+
 // best[v] = least rank among v's hyperedges whose score equals bestq[v]
 __global__ __launch_bounds__(kThreads) void k_best_feat(const int32_t *__restrict__ idx,
                                                         const int32_t *__restrict__ inc_edge,
@@ -908,7 +1287,8 @@ hnv_status layout(int64_t nV, int64_t nE, int64_t nnz, int k, CoarsenLayout &L)
     L.bstart = take(8 * (size_t)(std::max<int64_t>(nV >> kBucketShiftMax, 256) + 2));
     L.fsum = L.fsq = L.q = L.bestq = L.gcount = L.gptr = L.gcur = L.gnodes = 0;
     if (k > 0) {
-        L.fsum = take(4 * (size_t)nE * k);
+        // the member sums of the int32 path, or the byte copy of X of the byte path
+        L.fsum = take(std::max(4 * (size_t)nE * k, k <= kByteCols ? (size_t)nV * byte_stride(k) : 0));
         L.fsq = take(8 * nE);
         L.q = take(8 * nnz);
         L.bestq = take(8 * nV);
@@ -1001,9 +1381,10 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
         }
     }
     if (feat && nV > 0) {
-        const int64_t n4 = (int64_t)nV * k / 4;
-        k_fcheck<<<(unsigned)std::min<int64_t>(grid_for(n4), 2048), kThreads, 0, s>>>(
-            reinterpret_cast<const int4 *>(x), n4, flag, total);
+        const int kp4 = (k <= kByteCols ? byte_stride(k) : k) / 4;
+        k_fcheck<<<(unsigned)std::min<int64_t>(grid_for((int64_t)nV * kp4), 2048), kThreads, 0, s>>>(
+            reinterpret_cast<const int4 *>(x), n_nodes, k / 4, kp4, flag, flag + 1, total,
+            k <= kByteCols ? reinterpret_cast<uint32_t *>(at(L.fsum)) : nullptr);
     }
     if ((st = dev_check("coarsening input check")) != HNV_OK)
         return st;
@@ -1012,7 +1393,7 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
     // offsets or member ids, or writes an output, first reads the check
     // word and does nothing when it is set).
     struct {
-        int bad, pad;
+        int bad, largest;   // check bits; the largest count
         unsigned long long total;
     } chk{};
     auto report = [&]() -> hnv_status {
@@ -1039,6 +1420,8 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
         if ((st = sync_read(&chk, flag, sizeof(chk))) != HNV_OK || (st = report()) != HNV_OK)
             return st;
     }
+    // counts that fit a byte, in rows of one 16-byte piece per lane: the byte path
+    const bool bytes = feat && k <= kByteCols && chk.largest <= 255;
 
     int32_t *order = at(L.order), *rank = at(L.rank), *best = at(L.best), *choice = at(L.choice);
     int32_t *first = at(L.first), *count = at(L.count), *gflag = at(L.gflag), *gid = at(L.gid);
@@ -1098,7 +1481,19 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
             const dim3 wave_grid = fold_grid((n_edges + kThreads / kWave - 1) / (kThreads / kWave));
             k_fill<<<grid_for(2 * (int64_t)nV), kThreads, 0, s>>>(reinterpret_cast<int32_t *>(bestq),
                                                                    2 * (int64_t)nV, 0);
-            switch (pieces_for(k)) {
+            if (bytes) {
+                const unsigned char *x8 = reinterpret_cast<const unsigned char *>(fsum);
+                const int kp = byte_stride(k);
+#define HNV_BYTES(GG) launch_byte_scores<GG>(s, edge_ptr, edge_idx, x8, kp, n_edges, nnz, q, bestq)
+                if (kp <= 16) HNV_BYTES(1);
+                else if (kp <= 32) HNV_BYTES(2);
+                else if (kp <= 64) HNV_BYTES(4);
+                else if (kp <= 128) HNV_BYTES(8);
+                else if (kp <= 256) HNV_BYTES(16);
+                else if (kp <= 512) HNV_BYTES(32);
+                else HNV_BYTES(64);
+#undef HNV_BYTES
+            } else switch (pieces_for(k)) {
             case 1: launch_edge_features<1>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
             case 2: launch_edge_features<2>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
             case 4: launch_edge_features<4>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
@@ -1163,7 +1558,17 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
             return fail(HNV_EDEVICE, "scan of group sizes");
         k_group_fill<<<grid_for(nV), kThreads, 0, s>>>(node_rep, gptr, n_nodes, gcur, gnodes);
         const dim3 wave_grid = fold_grid((n_nodes + kThreads / kWave - 1) / (kThreads / kWave));
-        switch (pieces_for(k)) {
+        if (bytes) {
+            const uint32_t *x8 = reinterpret_cast<const uint32_t *>(at(L.fsum));
+            const int kp4 = byte_stride(k) / 4;
+            int4 *out = reinterpret_cast<int4 *>(c_x);
+#define HNV_BYTES(NC) \
+    k_rowsum_bytes<NC><<<wave_grid, kThreads, 0, s>>>(gptr, gnodes, x8, k / 4, kp4, n_nodes, sizes, out)
+            if (kp4 <= 64) HNV_BYTES(1);
+            else if (kp4 <= 128) HNV_BYTES(2);
+            else HNV_BYTES(4);
+#undef HNV_BYTES
+        } else switch (pieces_for(k)) {
         case 1: launch_group_sums<1>(wave_grid, s, gptr, gnodes, x, k, n_nodes, sizes, c_x); break;
         case 2: launch_group_sums<2>(wave_grid, s, gptr, gnodes, x, k, n_nodes, sizes, c_x); break;
         case 4: launch_group_sums<4>(wave_grid, s, gptr, gnodes, x, k, n_nodes, sizes, c_x); break;

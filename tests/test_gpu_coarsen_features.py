@@ -134,3 +134,24 @@ def test_features_without_hyperedges(H):
                        torch.zeros(0, dtype=torch.int32, device="cuda"))
     nrep, erep, c, xc = H.coarsen_level_features_device(lv, torch.zeros((0, 8), dtype=torch.int32, device="cuda"))
     assert (c.n_nodes, c.n_edges, c.nnz) == (0, 0, 0) and xc.shape[0] == 0
+
+
+@pytest.mark.parametrize("most", [255, 256])
+@pytest.mark.parametrize("k", [4, 16, 20, 32, 64, 68, 128, 260, 512, 1000, 1024, 1028])
+def test_byte_and_word_counts(oracle_mod, H, k, most):
+    """Counts up to 255 in rows of at most 1,024 take the byte path, larger
+    counts or wider rows the int32 path; hyperedges around the 64 members of a
+    wavefront, the 256 rows of a packed sum, and one of many more members."""
+    rng = np.random.default_rng(k + most)
+    n_nodes = 1500 if k < 500 else 700
+    sizes = [1, 2, 3, 8, 9, 32, 33, 63, 64, 65, 127, 255, 256, 257, n_nodes - 3] + list(rng.integers(1, 20, size=60))
+    edges = [np.sort(rng.choice(n_nodes - 1, size=s, replace=False)) for s in sizes]
+    ptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    x = np.where(rng.random((n_nodes, k)) < 0.3, rng.integers(0, most + 1, size=(n_nodes, k)), 0).astype(np.int32)
+    x[5, 0] = most
+    x[7] = most
+    x[9] = x[11]
+    from synth.hypergraph import Hypergraph
+    hg = Hypergraph(n_nodes, len(sizes), ptr, np.concatenate(edges).astype(np.int32), None)
+    print("counts", k, most, flush=True)
+    _compare(oracle_mod, H, hg, x, 2, f"k {k} counts up to {most}")
