@@ -2,21 +2,20 @@
 // featureless form has the same reading as the host coarsening in
 // hnv_host.cpp and the same maps bit for bit:
 //   1. every hyperedge gets a rank in the order (weight descending, size
-//      ascending, id ascending): a stable radix sort of a 64-bit key
-//      (inverted weight bits, size) over the ids;
+//      ascending, id ascending): a stable counting sort of the sizes, then, with
+//      weights, a stable radix sort of that order by the inverted weight bits;
 //   2. a node's choice c(v) is its incident hyperedge of least rank: an
 //      atomic minimum, which does not depend on the order of the updates;
 //   3. a group's coarse id follows its smallest node: a node starts a group
 //      if it has no hyperedge or is the smallest node that chose c(v); an
 //      exclusive scan over those flags numbers the groups in node order;
-//   4. a hyperedge is removed iff every member chose it (a count per
-//      hyperedge); a scan numbers the kept ones in order;
-//   5. the coarse member sets: every member mapped through rep(), a
-//      segmented sort per hyperedge, the first of each run of equal values
-//      flagged, one scan over the flags for positions and offsets.
-// Incidence-parallel steps find their hyperedge through inc_edge (a max-scan
-// of each hyperedge's id placed at its first incidence), so no thread walks a
-// whole hyperedge.
+//   4. the coarse member lists: every member mapped through rep(), sorted and
+//      made distinct by the thread, wavefront or workgroup that read it; a
+//      hyperedge is removed iff its list is one node whose group chose it;
+//   5. one scan over the hyperedges' counts of distinct members and of kept
+//      hyperedges gives the offsets and numbers, and the lists are copied there.
+// The passes over incidences walk windows of hyperedges with all lanes
+// (walk_window), so none needs an incidence -> hyperedge map in memory.
 // Integer work only (the key compares FP32 weights through their bit
 // patterns, which order like the values for positive finite floats).
 //
@@ -29,6 +28,7 @@
 // quotient, so the choice does not depend on summation order.
 #include <hip/hip_runtime.h>
 
+#include "hnv_binsort.h"
 #include "hnv_prim.h"
 
 #include <climits>
@@ -41,69 +41,135 @@
 namespace hnv {
 namespace {
 
-// Sort key of hyperedge e: the complemented weight bits above the size, which
-// takes size_bits bits (a size is at most n_nodes), so that an ascending
-// stable sort gives weight descending, size ascending, id ascending.
-__global__ __launch_bounds__(kThreads) void k_keys(const int32_t *__restrict__ ptr, const float *__restrict__ w,
-                                                   int64_t n_edges, int size_bits, uint64_t *__restrict__ keys,
-                                                   int32_t *__restrict__ ids)
+// The order of the hyperedges: by size first, then (with weights) a stable
+// radix sort of that order by the complemented weight bits: weight descending,
+// size ascending, id ascending.  The size order is a stable counting sort
+// (sizes of kSizeBins - 1 members and more share the last bin, which k_big_rank
+// puts in order), whose digit offsets also tell where each size begins: the
+// passes over longer member lists take them from there.  A level that can hold
+// more than kBigMax hyperedges of the last bin (by its incidences) sorts the
+// sizes by radix instead.  (As one radix sort of 64-bit keys of weight and
+// size: 119 us for the 1.5M sizes, where this takes 60.)
+constexpr int kSizeBins = kBinsMax;
+constexpr int64_t kBigMax = 1 << 15;
+
+inline int64_t max_last_bin(int64_t n_nodes, int64_t nnz)
+{
+    return n_nodes < kSizeBins - 1 ? 0 : nnz / (kSizeBins - 1);
+}
+
+// The last bin's hyperedges, in id order at the end of `order` (offs: the
+// scanned digit counts; the last bin's start is its first tile's): each one's
+// place among them by (size, id), counted against all of them, into tmp
+// (place -> hyperedge) and, when there are no weights, rank.  At most kBigMax
+// hyperedges, a few hundred as a rule.
+__global__ __launch_bounds__(kThreads) void k_big_rank(const int32_t *__restrict__ ptr,
+                                                       const int32_t *__restrict__ order,
+                                                       const int32_t *__restrict__ offs, int64_t n_tiles,
+                                                       int64_t n_edges, int32_t *__restrict__ tmp,
+                                                       int32_t *__restrict__ rank, const int *__restrict__ bad)
+{
+    if (*bad)   // the last bin may hold more than the grid's bound then
+        return;
+    const int64_t start = offs[(int64_t)(kSizeBins - 1) * n_tiles];
+    const int64_t n = n_edges - start, i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if ((int64_t)blockIdx.x * kThreads >= n)
+        return;
+    __shared__ __align__(16) int32_t sizes[kThreads];
+    const int32_t e = i < n ? order[start + i] : 0;
+    const int32_t size = i < n ? ptr[e + 1] - ptr[e] : 0;
+    int32_t place = 0;
+    for (int64_t t = 0; t < n; t += kThreads) {
+        __syncthreads();
+        int32_t s = INT_MAX;   // past the end: before nothing
+        if (t + threadIdx.x < n) {
+            const int32_t f = order[start + t + threadIdx.x];
+            s = ptr[f + 1] - ptr[f];
+        }
+        sizes[threadIdx.x] = s;
+        __syncthreads();
+        const int32_t equal_until = (int32_t)min<int64_t>(max<int64_t>(i - t, 0), kThreads);
+#pragma unroll 8
+        for (int c = 0; c < kThreads; c += 4) {
+            const int4 x = *reinterpret_cast<const int4 *>(sizes + c);
+            place += x.x < size + (c < equal_until);
+            place += x.y < size + (c + 1 < equal_until);
+            place += x.z < size + (c + 2 < equal_until);
+            place += x.w < size + (c + 3 < equal_until);
+        }
+    }
+    if (i < n) {
+        tmp[place] = e;
+        if (rank)
+            rank[e] = (int32_t)(start + place);
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_big_order(const int32_t *__restrict__ tmp,
+                                                        const int32_t *__restrict__ offs, int64_t n_tiles,
+                                                        int64_t n_edges, int32_t *__restrict__ order,
+                                                        const int *__restrict__ bad)
+{
+    if (*bad)
+        return;
+    const int64_t start = offs[(int64_t)(kSizeBins - 1) * n_tiles];
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i < n_edges - start)
+        order[start + i] = tmp[i];
+}
+
+// key of the i-th hyperedge in size order: its complemented weight bits (the
+// sign bit of a valid weight is clear, so the lower 31 decide)
+__global__ __launch_bounds__(kThreads) void k_weight_keys(const int32_t *__restrict__ order,
+                                                          const float *__restrict__ w, int64_t n_edges,
+                                                          uint32_t *__restrict__ keys)
+{
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i < n_edges)
+        keys[i] = ~__float_as_uint(w[order[i]]);
+}
+
+// each hyperedge's size (at most n_nodes) and id, for the radix sort of sizes
+__global__ __launch_bounds__(kThreads) void k_size_keys(const int32_t *__restrict__ ptr, int64_t n_edges,
+                                                        uint32_t *__restrict__ keys, int32_t *__restrict__ ids)
 {
     const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (e >= n_edges)
         return;
-    const uint32_t wb = __float_as_uint(w ? w[e] : 1.0f);
-    const uint32_t size = (uint32_t)(ptr[e + 1] - ptr[e]);
-    keys[e] = ((uint64_t)(~wb) << size_bits) | size;
+    keys[e] = (uint32_t)(ptr[e + 1] - ptr[e]);
     ids[e] = (int32_t)e;
 }
 
-// rank[order[i]] = i, and the per-hyperedge and per-node accumulators of
-// the choice step set to their start values (first INT_MAX, count 0, best
-// INT_MAX)
+// rank[order[i]] = i
 __global__ __launch_bounds__(kThreads) void k_rank(const int32_t *__restrict__ order, int64_t n_edges,
-                                                   int64_t n_nodes, int32_t *__restrict__ rank,
-                                                   int32_t *__restrict__ first, int32_t *__restrict__ count,
-                                                   int32_t *__restrict__ best)
+                                                   int32_t *__restrict__ rank)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n_edges) {
+    if (i < n_edges)
         rank[order[i]] = (int32_t)i;
-        first[i] = INT_MAX;
-        count[i] = 0;
-    }
-    if (i < n_nodes)
-        best[i] = INT_MAX;
 }
 
-// no long member lists yet: the count and both bound arrays cleared
-__global__ __launch_bounds__(kThreads) void k_clear_big(int32_t *__restrict__ n_big, int32_t *__restrict__ begin,
-                                                        int32_t *__restrict__ end, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i == 0)
-        *n_big = 0;
-    if (i < n)
-        begin[i] = end[i] = 0;
-}
-
-// best[v] = least rank over the hyperedges containing v, one incidence per
-// thread
-__global__ __launch_bounds__(kThreads) void k_best(const int32_t *__restrict__ idx,
-                                                   const int32_t *__restrict__ inc_edge,
-                                                   const int32_t *__restrict__ rank, int64_t nnz,
+// best[v] = least rank over the hyperedges containing v
+__global__ __launch_bounds__(kThreads) void k_best(const int32_t *__restrict__ ptr, const int32_t *__restrict__ idx,
+                                                   const int32_t *__restrict__ rank, int per, int64_t n_edges, int64_t nnz,
                                                    int32_t *__restrict__ best, const int *__restrict__ bad)
 {
-    if (*bad)   // the step's input failed its checks
+    __shared__ WalkLds lds;
+    const int64_t e0 = window_start(per);
+    if (*bad || e0 >= n_edges)   // the step's input failed its checks
         return;
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (j >= nnz)
-        return;
+    const int64_t e = e0 + threadIdx.x % kWave;
+    const int32_t r = threadIdx.x % kWave < per && e < n_edges ? rank[e] : 0;
     // The minimum only decreases, so any value read earlier (even a stale
     // cached one) bounds the final one from above: a rank not below it
     // cannot win and needs no atomic.
-    const int32_t v = idx[j], r = rank[inc_edge[j]];
-    if (r < best[v])
-        atomicMin(best + v, r);
+    walk_window<kWalk>(
+        window_of(ptr, e0, per, n_edges, nnz), lds, [&](uint32_t j, int, bool ok) { return ok ? idx[j] : -1; },
+        [&](uint32_t, int l, bool ok, bool, int32_t v) {
+            const int32_t lr = __shfl(r, l, kWave);
+            if (ok && lr < best[v])
+                atomicMin(best + v, lr);
+        });
 }
 
 // The same minima without global atomics, for large levels: the incidences'
@@ -120,13 +186,22 @@ int bucket_shift(int64_t n_nodes) { return std::min(bits_for(n_nodes) - 8, kBuck
 int64_t bucket_count(int64_t n_nodes) { return ((n_nodes - 1) >> bucket_shift(n_nodes)) + 1; }
 
 // the hyperedge rank of every incidence
-__global__ __launch_bounds__(kThreads) void k_inc_rank(const int32_t *__restrict__ inc_edge,
-                                                       const int32_t *__restrict__ rank, int64_t nnz,
-                                                       int32_t *__restrict__ out)
+__global__ __launch_bounds__(kThreads) void k_inc_rank(const int32_t *__restrict__ ptr,
+                                                       const int32_t *__restrict__ rank, int per, int64_t n_edges,
+                                                       int64_t nnz, int32_t *__restrict__ out, const int *__restrict__ bad)
 {
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (j < nnz)
-        out[j] = rank[inc_edge[j]];
+    __shared__ WalkLds lds;
+    const int64_t e0 = window_start(per);
+    if (*bad || e0 >= n_edges)   // the step's input failed its checks
+        return;
+    const int64_t e = e0 + threadIdx.x % kWave;
+    const int32_t r = threadIdx.x % kWave < per && e < n_edges ? rank[e] : 0;
+    walk_window<kWalk>(
+        window_of(ptr, e0, per, n_edges, nnz), lds, [&](uint32_t, int l, bool) { return __shfl(r, l, kWave); },
+        [&](uint32_t j, int, bool ok, bool, int32_t lr) {
+            if (ok)
+                out[j] = lr;
+        });
 }
 
 // start[b] = the first position of bucket b in node ids sorted on their bits
@@ -155,15 +230,14 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_min(const uint32_t *_
                                                                int64_t n_nodes, int32_t *__restrict__ best,
                                                                const int *__restrict__ bad)
 {
-    if (*bad)   // the step's input failed its checks
-        return;
     __shared__ int32_t m[1 << kBucketShiftMax];
     const int span = 1 << shift;
     const int64_t base = (int64_t)blockIdx.x << shift;
     for (int t = threadIdx.x; t < span; t += kBucketThreads)
         m[t] = INT_MAX;
     __syncthreads();
-    const int64_t a = start[blockIdx.x], b = start[blockIdx.x + 1];
+    // (no incidences of a step whose input failed its checks)
+    const int64_t a = start[blockIdx.x], b = *bad ? a : start[blockIdx.x + 1];
     for (int64_t i = a + threadIdx.x; i < b; i += kBucketThreads)
         atomicMin(&m[(int64_t)keys[i] - base], vals[i]);
     __syncthreads();
@@ -171,11 +245,10 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_min(const uint32_t *_
         best[base + t] = m[t];
 }
 
-// choice, then per hyperedge: smallest node that chose it, and how many did
+// choice, and per hyperedge the smallest node that chose it
 __global__ __launch_bounds__(kThreads) void k_choice(const int32_t *__restrict__ best,
                                                      const int32_t *__restrict__ order, int64_t n_nodes,
-                                                     int32_t *__restrict__ choice, int32_t *__restrict__ first,
-                                                     int32_t *__restrict__ count)
+                                                     int32_t *__restrict__ choice, int32_t *__restrict__ first)
 {
     const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (v >= n_nodes)
@@ -183,10 +256,8 @@ __global__ __launch_bounds__(kThreads) void k_choice(const int32_t *__restrict__
     const int32_t b = best[v];
     const int32_t c = (b == INT_MAX) ? -1 : order[b];
     choice[v] = c;
-    if (c >= 0) {
+    if (c >= 0 && (int32_t)v < first[c])   // an earlier read bounds the minimum from above
         atomicMin(first + c, (int32_t)v);
-        atomicAdd(count + c, 1);
-    }
 }
 
 __global__ __launch_bounds__(kThreads) void k_group_flags(const int32_t *__restrict__ choice,
@@ -203,7 +274,8 @@ __global__ __launch_bounds__(kThreads) void k_group_flags(const int32_t *__restr
 __global__ __launch_bounds__(kThreads) void k_node_rep(const int32_t *__restrict__ choice,
                                                        const int32_t *__restrict__ first,
                                                        const int32_t *__restrict__ gid, int64_t n_nodes,
-                                                       int32_t *__restrict__ node_rep, const int *__restrict__ bad)
+                                                       int32_t *__restrict__ node_rep, int64_t *__restrict__ sizes,
+                                                       const int *__restrict__ bad)
 {
     if (*bad)   // the step's input failed its checks
         return;
@@ -212,58 +284,60 @@ __global__ __launch_bounds__(kThreads) void k_node_rep(const int32_t *__restrict
         return;
     const int32_t c = choice[v];
     node_rep[v] = (c < 0) ? gid[v] : gid[first[c]];
-}
-
-__global__ __launch_bounds__(kThreads) void k_kept_flags(const int32_t *__restrict__ ptr,
-                                                         const int32_t *__restrict__ count, int64_t n_edges,
-                                                         int32_t *__restrict__ kept)
-{
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e < n_edges)
-        kept[e] = (count[e] != ptr[e + 1] - ptr[e]) ? 1 : 0;
-}
-
-__global__ __launch_bounds__(kThreads) void k_map(const int32_t *__restrict__ idx,
-                                                  const int32_t *__restrict__ node_rep, int64_t nnz,
-                                                  int32_t *__restrict__ mapped, const int *__restrict__ bad)
-{
-    if (*bad)   // the step's input failed its checks
-        return;
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (j < nnz)
-        mapped[j] = node_rep[idx[j]];
+    if (v == n_nodes - 1)   // the coarse nodes: the groups before v and, when v starts one, v's
+        sizes[0] = gid[v] + (c < 0 || first[c] == (int32_t)v ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------
-// Coarse member lists sorted per hyperedge.  A library segmented sort spends
-// most of its time on per-segment overhead when, as here, most segments hold
-// two to four keys.  So: lists of at most kSortThread members are sorted by
-// one thread in registers (a network of 8, or of 16 above 8 members); lists
-// of at most kSortWave members by one wavefront (a bitonic network over 64
-// lanes x up to 16 registers); the few longer ones go to the library's
-// segmented sort.  Each list's result is the same whatever order the lists
-// are taken in.
+// Coarse member lists.  A hyperedge's members are mapped through rep(), sorted
+// and their distinct values written to the start of its segment, all by the
+// thread, wavefront or workgroup that read them: lists of at most kSortThread
+// members by one thread in registers (a network of 8, or of 16 above 8
+// members); of at most kSortMid by one wavefront (a bitonic network over 64
+// lanes x up to 4 registers); of at most kSortLong by a workgroup's registers
+// and of at most kSortBlock by a workgroup in LDS; the few longer ones (none in most hypergraphs) by the library's segmented sort
+// over a list of them.  Each list's result is the same whatever order the
+// lists are taken in.  Bound by the random 4-byte reads of rep(); as separate
+// passes (map, sort, distinct flags, kept flags) a step of the 2M-node
+// hypergraph took 255 us here, and a scan and an emit of 13M flags after it,
+// where this takes 155 us and a scan of 1.5M counts.
+//
+// A hyperedge is removed iff every member chose it.  Then all members lie in
+// one group, so its list has one value; and members of one group made the same
+// choice, so it is enough that the first member's choice is this hyperedge:
+// its best rank is the hyperedge's own.
 // ---------------------------------------------------------------------------
 
 constexpr int kSortThread = 16;
-constexpr int kSortWave = 1024;
+constexpr int kSortMid = 256;
+constexpr int kSortLong = 2048;
+constexpr int kSortBlock = 32768;
+constexpr int kSortBlockThreads = 1024;
 
-// Appends the lanes with `pred` to a list through one atomic per wavefront;
-// returns each such lane's slot (-1 for the others).  Every lane of the
-// wavefront must call it.
-__device__ __forceinline__ int32_t wave_append(int32_t *counter, bool pred)
+// per hyperedge: distinct coarse members (0 when removed) and whether it is kept
+struct EdgeCount {
+    int32_t members, kept;
+};
+struct EdgeCountPlus {
+    __host__ __device__ EdgeCount operator()(const EdgeCount &x, const EdgeCount &y) const
+    {
+        return EdgeCount{x.members + y.members, x.kept + y.kept};
+    }
+};
+
+__device__ __forceinline__ EdgeCount edge_count(int32_t distinct, bool first_chose_it)
 {
-    const uint64_t m = __ballot(pred);
-    if (m == 0)
-        return -1;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int leader = __ffsll((long long)m) - 1;
-    int32_t base = 0;
-    if (lane == leader)
-        base = atomicAdd(counter, (int32_t)__popcll(m));
-    base = __shfl(base, leader, kWave);
-    return pred ? base + (int32_t)__popcll(m & ((1ull << lane) - 1ull)) : -1;
+    return distinct == 1 && first_chose_it ? EdgeCount{0, 0} : EdgeCount{distinct, 1};
 }
+
+// The hyperedges of at least `size` members (at most kSizeBins - 1) are the
+// entries [first_of(..), n_edges) of the size order.
+struct SizeOrder {
+    const int32_t *by_size;   // [n_edges]
+    const int32_t *offs;      // scanned size counts, size b of tile t at b * n_tiles + t
+    int64_t n_tiles, n_edges;
+    __device__ int64_t first_of(int size) const { return offs[size * n_tiles]; }
+};
 
 // Bitonic sorting network over the N registers of one thread (N a power of
 // two; every index is a compile-time constant).
@@ -288,229 +362,595 @@ __device__ __forceinline__ void thread_bitonic(int32_t (&v)[N])
     }
 }
 
+// Sorts the N mapped members of a thread's list (n of them, INT_MAX past the
+// end, which is above every coarse node) and writes the distinct ones to out.
+template <int N, typename Sort>
+__device__ __forceinline__ int32_t thread_list(const int32_t *__restrict__ idx, const int32_t *__restrict__ node_rep,
+                                               int32_t s, int32_t n, int32_t *__restrict__ out, Sort sort)
+{
+    int32_t v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        v[i] = (i < n) ? idx[s + i] : -1;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        v[i] = (i < n) ? node_rep[v[i]] : INT_MAX;
+    sort(v);
+    int32_t c = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (i < n && (i == 0 || v[i] != v[i - 1]))
+            out[s + c++] = v[i];
+    return c;
+}
+
 // One thread per hyperedge: a list of at most 8 members is sorted here with
 // Batcher's odd-even merge network of 19 comparators, one of 9 to
-// kSortThread members with a bitonic network of 16 (INT_MAX padding); one of
-// more than kSortWave members is appended to the library sort's segment
-// list (a few per level, so one atomic per wavefront that has any is
-// cheap).  The lists in between are left to k_sort_wave.
-__global__ __launch_bounds__(kThreads) void k_sort_short(const int32_t *__restrict__ ptr,
-                                                         const int32_t *__restrict__ mapped, int64_t n_edges,
-                                                         int32_t *__restrict__ sorted, int32_t *__restrict__ big_begin,
-                                                         int32_t *__restrict__ big_end, int32_t *__restrict__ n_big,
+// kSortThread members with a bitonic network of 16.  Longer lists are left to
+// the kernels below.
+__global__ __launch_bounds__(kThreads) void k_list_short(const int32_t *__restrict__ ptr,
+                                                         const int32_t *__restrict__ idx,
+                                                         const int32_t *__restrict__ node_rep,
+                                                         const int32_t *__restrict__ best,
+                                                         const int32_t *__restrict__ rank, int64_t n_edges,
+                                                         int32_t *__restrict__ out, EdgeCount *__restrict__ count,
                                                          const int *__restrict__ bad)
 {
-    if (*bad)   // the step's input failed its checks
-        return;
     const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    int32_t s = 0, n = 0;
-    if (e < n_edges) {
-        s = ptr[e];
-        n = ptr[e + 1] - s;
+    if (*bad || e >= n_edges)   // the step's input failed its checks
+        return;
+    const int32_t s = ptr[e], n = ptr[e + 1] - s;
+    if (n <= kSortThread) {
+        const bool chose = best[idx[s]] == rank[e];
+        int32_t c;
+        if (n <= 8)
+            c = thread_list<8>(idx, node_rep, s, n, out, [](int32_t(&v)[8]) {
+                constexpr int net[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6}, {5, 7}, {1, 2}, {5, 6},
+                                            {0, 4}, {3, 7}, {1, 5}, {2, 6}, {1, 4}, {3, 6}, {2, 4}, {3, 5}, {3, 4}};
+#pragma unroll
+                for (int i = 0; i < 19; ++i) {
+                    const int32_t x = v[net[i][0]], y = v[net[i][1]];
+                    v[net[i][0]] = min(x, y);
+                    v[net[i][1]] = max(x, y);
+                }
+            });
+        else
+            c = thread_list<16>(idx, node_rep, s, n, out, [](int32_t(&v)[16]) { thread_bitonic<16>(v); });
+        count[e] = edge_count(c, chose);
     }
-    if (e < n_edges && n > 8 && n <= kSortThread) {
-        int32_t v[16];
+}
+
+// Compare step of lane i's key x with lane i ^ X's: the smaller one where the
+// lane's bit of the distance is clear, the larger one elsewhere.  All on the
+// vector unit: with every exchange through the LDS crossbar the sorts of 2,048
+// keys took 132 us at the 2M-node level instead of 72.  A row is 16 lanes.
+template <int X>
+__device__ __forceinline__ int32_t row_xor(int32_t x)   // lane ^ X within a row
+{
+    if constexpr (X == 1)
+        return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, false);    // quad_perm [1, 0, 3, 2]
+    else if constexpr (X == 2)
+        return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xf, 0xf, false);    // quad_perm [2, 3, 0, 1]
+    else if constexpr (X == 3)
+        return __builtin_amdgcn_mov_dpp(x, 0x1B, 0xf, 0xf, false);    // quad_perm [3, 2, 1, 0]
+    else if constexpr (X == 4) {
+        const int32_t up = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xf, 0x5, false);   // row_shl 4 into quads 0, 2
+        return __builtin_amdgcn_update_dpp(up, x, 0x114, 0xf, 0xa, false);              // row_shr 4 into quads 1, 3
+    } else if constexpr (X == 7)
+        return __builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, false);   // row_half_mirror
+    else if constexpr (X == 8)
+        return __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, false);   // row_ror 8
+    else
+        return __builtin_amdgcn_mov_dpp(x, 0x140, 0xf, 0xf, false);   // row_mirror (15)
+}
+
+// Both keys of the pair of lanes i and i ^ 16 (and i ^ 32), in either order.
+__device__ __forceinline__ void pair16(int32_t x, int32_t &a, int32_t &b)
+{
+    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    a = (int32_t)p[0];
+    b = (int32_t)p[1];
+}
+__device__ __forceinline__ void pair32(int32_t x, int32_t &a, int32_t &b)
+{
+    const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    a = (int32_t)p[0];
+    b = (int32_t)p[1];
+}
+
+// lane ^ 31's and lane ^ 63's key
+__device__ __forceinline__ int32_t mirror32(int32_t x, int lane)
+{
+    int32_t a, b;
+    pair16(row_xor<15>(x), a, b);
+    return (lane & 16) ? a : b;
+}
+__device__ __forceinline__ int32_t mirror64(int32_t x, int lane)
+{
+    int32_t a, b;
+    pair32(mirror32(x, lane), a, b);
+    return (lane & 32) ? a : b;
+}
+
+template <int K, int X>
+__device__ __forceinline__ void lane_step(int32_t (&v)[K], int lane)
+{
+    constexpr int bit = X == 1 ? 1 : X <= 3 ? 2 : X <= 7 ? 4 : X <= 15 ? 8 : X <= 31 ? 16 : 32;
+    const bool low = (lane & bit) == 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            v[i] = (i < n) ? mapped[s + i] : INT_MAX;
-        thread_bitonic<16>(v);
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (i < n)
-                sorted[s + i] = v[i];
+    for (int r = 0; r < K; ++r) {
+        int32_t a = v[r], b;
+        if constexpr (X < 16)
+            b = row_xor<X>(a);
+        else if constexpr (X == 16)
+            pair16(v[r], a, b);
+        else if constexpr (X == 31)
+            b = mirror32(a, lane);
+        else if constexpr (X == 32)
+            pair32(v[r], a, b);
+        else
+            b = mirror64(a, lane);
+        const int32_t lo = min(a, b), hi = max(a, b);
+        v[r] = low ? lo : hi;
     }
-    if (e < n_edges && n <= 8) {
-        int32_t v[8];
+}
+
+// The steps that follow the first one of a block of k = 64 M keys (M > 1):
+// distances of M / 2 registers down to one.
+template <int K, int M>
+__device__ __forceinline__ void register_steps(int32_t (&v)[K])
+{
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            v[i] = (i < n) ? mapped[s + i] : INT_MAX;
-        constexpr int net[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6}, {5, 7}, {1, 2}, {5, 6},
-                                    {0, 4}, {3, 7}, {1, 5}, {2, 6}, {1, 4}, {3, 6}, {2, 4}, {3, 5}, {3, 4}};
+    for (int d = M / 4; d > 0; d /= 2) {
 #pragma unroll
-        for (int c = 0; c < 19; ++c) {
-            const int32_t a = v[net[c][0]], b = v[net[c][1]];
-            v[net[c][0]] = min(a, b);
-            v[net[c][1]] = max(a, b);
+        for (int r = 0; r < K; ++r) {
+            if (r & d)
+                continue;
+            const int32_t a = v[r], b = v[r | d];
+            v[r] = min(a, b);
+            v[r | d] = max(a, b);
         }
+    }
+}
+
+// A block of 64 M keys whose halves ascend: key i against key 64 M - 1 - i
+// (the mirrored register and lane), then the register distances.
+template <int K, int M>
+__device__ __forceinline__ void merge_registers(int32_t (&v)[K], int lane)
+{
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (i < n)
-                sorted[s + i] = v[i];
+    for (int r = 0; r < K; ++r) {
+        constexpr int m = M - 1;
+        if (r > (r ^ m))
+            continue;
+        const int32_t a = v[r], b = v[r ^ m];
+        v[r] = min(a, mirror64(b, lane));
+        v[r ^ m] = max(b, mirror64(a, lane));
     }
-    const bool is_big = e < n_edges && n > kSortWave;
-    const int32_t b = wave_append(n_big, is_big);
-    if (is_big) {
-        big_begin[b] = s;
-        big_end[b] = s + n;
-    }
+    register_steps<K, M>(v);
+}
+
+template <int K>
+__device__ __forceinline__ void lane_steps(int32_t (&v)[K], int lane)
+{
+    lane_step<K, 32>(v, lane);
+    lane_step<K, 16>(v, lane);
+    lane_step<K, 8>(v, lane);
+    lane_step<K, 4>(v, lane);
+    lane_step<K, 2>(v, lane);
+    lane_step<K, 1>(v, lane);
 }
 
 // Bitonic sorting network over 64 K keys held as v[r] in lane `lane`, key
-// index r * 64 + lane: partners at distance j < 64 are in other lanes of the
-// same register (exchanged by shuffles), at j >= 64 in other registers of
-// the same lane.  All loop bounds are compile-time, so every register index
-// is a constant.
+// index r * 64 + lane, in the form whose every comparison is ascending: a block
+// of two ascending halves is compared with its mirror image, then at halving
+// distances.  The blocks of more than 64 keys are a loop at run time, to keep
+// the code small; every register index is a constant.
 template <int K>
 __device__ __forceinline__ void wave_bitonic(int32_t (&v)[K], int lane)
 {
-    constexpr int LOGN = (K == 1) ? 6 : (K == 2) ? 7 : (K == 4) ? 8 : (K == 8) ? 9 : 10;
-#pragma unroll
-    for (int lk = 1; lk <= LOGN; ++lk) {
-        const int k = 1 << lk;
-#pragma unroll
-        for (int lj = lk - 1; lj >= 0; --lj) {
-            const int j = 1 << lj;
-            if (j >= kWave) {
-                const int rj = j / kWave;
-#pragma unroll
-                for (int r = 0; r < K; ++r) {
-                    if (r & rj)
-                        continue;
-                    const bool asc = ((r * kWave) & k) == 0;   // k > 64: the direction is the register's
-                    const int32_t a = v[r], b = v[r | rj];
-                    v[r] = asc ? min(a, b) : max(a, b);
-                    v[r | rj] = asc ? max(a, b) : min(a, b);
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < K; ++r) {
-                    const bool asc = ((r * kWave + lane) & k) == 0;
-                    const int32_t y = __shfl_xor(v[r], j, kWave);
-                    const bool keep_min = ((lane & j) == 0) == asc;
-                    v[r] = keep_min ? min(v[r], y) : max(v[r], y);
-                }
-            }
-        }
+    lane_step<K, 1>(v, lane);
+    lane_step<K, 3>(v, lane);
+    lane_step<K, 1>(v, lane);
+    lane_step<K, 7>(v, lane);
+    lane_step<K, 2>(v, lane);
+    lane_step<K, 1>(v, lane);
+    lane_step<K, 15>(v, lane);
+    lane_step<K, 4>(v, lane);
+    lane_step<K, 2>(v, lane);
+    lane_step<K, 1>(v, lane);
+    lane_step<K, 31>(v, lane);
+    lane_step<K, 8>(v, lane);
+    lane_step<K, 4>(v, lane);
+    lane_step<K, 2>(v, lane);
+    lane_step<K, 1>(v, lane);
+    lane_step<K, 63>(v, lane);
+    lane_step<K, 16>(v, lane);
+    lane_step<K, 8>(v, lane);
+    lane_step<K, 4>(v, lane);
+    lane_step<K, 2>(v, lane);
+    lane_step<K, 1>(v, lane);
+    for (int m = 2; m <= K; m <<= 1) {
+        if constexpr (K >= 2)
+            if (m == 2)
+                merge_registers<K, 2>(v, lane);
+        if constexpr (K >= 4)
+            if (m == 4)
+                merge_registers<K, 4>(v, lane);
+        if constexpr (K >= 8)
+            if (m == 8)
+                merge_registers<K, 8>(v, lane);
+        lane_steps<K>(v, lane);
     }
 }
 
-template <int K>
-__device__ __forceinline__ void wave_sort(const int32_t *__restrict__ in, int32_t *__restrict__ out, int n, int lane)
+// A wavefront's list: the coarse nodes of the members `ids` (n of them, 64 per
+// register), sorted, the distinct values written to out; returns how many.
+template <int K, int KM>
+__device__ __forceinline__ int32_t wave_list(const int32_t (&ids)[KM], const int32_t *__restrict__ node_rep, int32_t n,
+                                             int32_t *__restrict__ out, int lane)
 {
     int32_t v[K];
 #pragma unroll
-    for (int r = 0; r < K; ++r) {
-        const int i = r * kWave + lane;
-        v[r] = (i < n) ? in[i] : INT_MAX;
-    }
+    for (int r = 0; r < K; ++r)
+        v[r] = (r * kWave + lane < n) ? node_rep[ids[r]] : INT_MAX;
     wave_bitonic<K>(v, lane);
+    int32_t c = 0;
 #pragma unroll
     for (int r = 0; r < K; ++r) {
-        const int i = r * kWave + lane;
-        if (i < n)
-            out[i] = v[r];
+        // the value before: the lane below's, or the last lane's of the register before
+        int32_t before = __shfl_up(v[r], 1, kWave);
+        if (r > 0) {
+            const int32_t last = __shfl(v[r > 0 ? r - 1 : 0], kWave - 1, kWave);
+            before = lane == 0 ? last : before;
+        }
+        const bool put = r * kWave + lane < n && ((r == 0 && lane == 0) || v[r] != before);
+        const uint64_t m = __ballot(put);
+        if (put)
+            out[c + (int32_t)__popcll(m & ((1ull << lane) - 1ull))] = v[r];
+        c += (int32_t)__popcll(m);
     }
+    return c;
 }
 
-// The lists of more than kSortThread and at most kSortWave members: each
-// wavefront takes a window of 64 consecutive hyperedges (one per lane),
-// finds those lists by a ballot, and sorts them one after the other with
-// all 64 lanes.  No list of work, no atomics.
-__global__ __launch_bounds__(kThreads) void k_sort_wave(const int32_t *__restrict__ ptr,
-                                                        const int32_t *__restrict__ mapped, int64_t n_edges,
-                                                        int32_t *__restrict__ sorted, const int *__restrict__ bad)
+// The lists of more than kSortThread and at most kSortMid members, a wavefront
+// each, longest first: kListBlocks workgroups at most, whose wavefronts go
+// through the size order in turn and fetch the next list while they sort one
+// (windows of 16 hyperedges per wavefront, found with a ballot, left most of
+// the time to wavefronts without a list: 57 us at the 2M-node level, where
+// this takes 49).
+constexpr int kListBlocks = 2048;
+
+__global__ __launch_bounds__(kThreads) void k_list_wave(const int32_t *__restrict__ ptr,
+                                                        const int32_t *__restrict__ idx,
+                                                        const int32_t *__restrict__ node_rep,
+                                                        const int32_t *__restrict__ best,
+                                                        const int32_t *__restrict__ rank, SizeOrder S,
+                                                        int32_t *__restrict__ out, EdgeCount *__restrict__ count,
+                                                        const int *__restrict__ bad)
 {
     if (*bad)   // the step's input failed its checks
         return;
+    constexpr int KM = kSortMid / kWave;
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t window = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / kWave;
-    const int64_t e = window * kWave + lane;
-    int32_t s = 0, n = 0;
-    if (e < n_edges) {
-        s = ptr[e];
-        n = ptr[e + 1] - s;
+    const int64_t first = S.first_of(kSortThread + 1), end = S.first_of(kSortMid + 1);
+    const int64_t step = (int64_t)gridDim.x * (kThreads / kWave);
+    int64_t i = end - 1 - ((int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave);
+    if (i < first)
+        return;   // uniform over the wavefront
+    auto edge_at = [&](int64_t at) { return __builtin_amdgcn_readfirstlane(at >= first ? S.by_size[at] : 0); };
+    int32_t ids[KM];
+    auto load_ids = [&](int32_t s, int32_t n) {
+#pragma unroll
+        for (int r = 0; r < KM; ++r) {
+            const int32_t p = r * kWave + lane;
+            ids[r] = (p < n) ? idx[s + p] : 0;
+        }
+    };
+    int32_t e = edge_at(i), next = edge_at(i - step);
+    int32_t s = __builtin_amdgcn_readfirstlane(ptr[e]), n = __builtin_amdgcn_readfirstlane(ptr[e + 1]) - s;
+    load_ids(s, n);
+    for (; i >= first; i -= step) {
+        // the first member's choice, and the next list's place
+        const int32_t b0 = best[__builtin_amdgcn_readfirstlane(ids[0])], re = rank[e];
+        const int32_t s2 = ptr[next], n2 = ptr[next + 1] - s2;
+        const int32_t after = edge_at(i - 2 * step);
+        const int32_t c = n <= 64    ? wave_list<1>(ids, node_rep, n, out + s, lane)
+                          : n <= 128 ? wave_list<2>(ids, node_rep, n, out + s, lane)
+                                     : wave_list<4>(ids, node_rep, n, out + s, lane);
+        if (i - step >= first)
+            load_ids(s2, n2);
+        if (lane == 0)
+            count[e] = edge_count(c, b0 == re);
+        e = next;
+        next = after;
+        s = s2;
+        n = n2;
     }
-    uint64_t todo = __ballot(n > kSortThread && n <= kSortWave);
-    while (todo) {
-        const int src = __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        const int32_t ss = __shfl(s, src, kWave), nn = __shfl(n, src, kWave);
-        if (nn <= 64)
-            wave_sort<1>(mapped + ss, sorted + ss, nn, lane);
-        else if (nn <= 128)
-            wave_sort<2>(mapped + ss, sorted + ss, nn, lane);
-        else if (nn <= 256)
-            wave_sort<4>(mapped + ss, sorted + ss, nn, lane);
-        else if (nn <= 512)
-            wave_sort<8>(mapped + ss, sorted + ss, nn, lane);
-        else
-            wave_sort<16>(mapped + ss, sorted + ss, nn, lane);
+}
+
+// The lists of more than kSortMid and at most kSortLong members, a workgroup
+// each: every wavefront sorts 512 keys in registers (key index 512 wave + 64 r
+// + lane), then blocks of 1,024 and 2,048 keys are merged in the same network,
+// whose steps between wavefronts go through LDS.  (Windows of 64 hyperedges
+// per workgroup took 72 us at the 2M-node level, where the size order takes
+// 53; a wavefront with up to 32 registers of keys per list 60 and more.)
+constexpr int kLongRegs = 8;
+
+__global__ __launch_bounds__(kThreads) void k_list_long(const int32_t *__restrict__ ptr,
+                                                        const int32_t *__restrict__ idx,
+                                                        const int32_t *__restrict__ node_rep,
+                                                        const int32_t *__restrict__ best,
+                                                        const int32_t *__restrict__ rank, SizeOrder S,
+                                                        int32_t *__restrict__ out, EdgeCount *__restrict__ count,
+                                                        const int *__restrict__ bad)
+{
+    if (*bad)   // the step's input failed its checks
+        return;
+    static_assert(kThreads * kLongRegs == kSortLong, "a key per register of the workgroup");
+    __shared__ int32_t keys[kSortLong];
+    __shared__ int32_t part[kThreads / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int32_t base = wave * kLongRegs * kWave;
+    const int64_t first = S.first_of(kSortMid + 1);
+    for (int64_t i = S.n_edges - 1 - blockIdx.x; i >= first; i -= gridDim.x) {   // longest first
+        const int32_t e = S.by_size[i], s = ptr[e], n = ptr[e + 1] - s;
+        if (n > kSortLong)   // uniform over the workgroup
+            continue;
+        const int32_t b0 = best[idx[s]], re = rank[e];
+        int32_t v[kLongRegs];
+#pragma unroll
+        for (int r = 0; r < kLongRegs; ++r) {
+            const int32_t i = base + r * kWave + lane;
+            v[r] = (i < n) ? idx[s + i] : -1;
+        }
+#pragma unroll
+        for (int r = 0; r < kLongRegs; ++r)
+            v[r] = (base + r * kWave + lane < n) ? node_rep[v[r]] : INT_MAX;
+        if (base < n)   // (the later wavefronts of a short list hold only padding)
+            wave_bitonic<kLongRegs>(v, lane);
+        // compares every key with the one at index ^ x, the wavefronts with
+        // `bit` clear keeping the smaller ones
+        auto exchange = [&](int32_t x, int bit) {
+            __syncthreads();   // the last exchange has been read
+#pragma unroll
+            for (int r = 0; r < kLongRegs; ++r)
+                keys[base + r * kWave + lane] = v[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kLongRegs; ++r) {
+                const int32_t y = keys[(base + r * kWave + lane) ^ x];
+                v[r] = (wave & bit) == 0 ? min(v[r], y) : max(v[r], y);
+            }
+        };
+        if (n > 512) {   // uniform over the workgroup
+            exchange(1023, 1);
+            register_steps<kLongRegs, 2 * kLongRegs>(v);
+            lane_steps<kLongRegs>(v, lane);
+        }
+        if (n > 1024) {
+            exchange(2047, 2);
+            exchange(512, 1);
+            register_steps<kLongRegs, 2 * kLongRegs>(v);
+            lane_steps<kLongRegs>(v, lane);
+        }
+        // distinct values: a value is written if the one before it differs
+        __syncthreads();
+        if (lane == kWave - 1)
+            keys[wave] = v[kLongRegs - 1];
+        __syncthreads();
+        int32_t last = wave > 0 ? keys[wave - 1] : -1, c = 0;
+        uint64_t put[kLongRegs];
+#pragma unroll
+        for (int r = 0; r < kLongRegs; ++r) {
+            int32_t before = __shfl_up(v[r], 1, kWave);
+            before = lane == 0 ? last : before;
+            last = __shfl(v[r], kWave - 1, kWave);
+            put[r] = __ballot(base + r * kWave + lane < n && v[r] != before);
+            c += (int32_t)__popcll(put[r]);
+        }
+        if (lane == 0)
+            part[wave] = c;
+        __syncthreads();
+        int32_t at = s, total = 0;
+        for (int w = 0; w < kThreads / kWave; ++w) {
+            at += w < wave ? part[w] : 0;
+            total += part[w];
+        }
+#pragma unroll
+        for (int r = 0; r < kLongRegs; ++r) {
+            if ((put[r] >> lane) & 1)
+                out[at + (int32_t)__popcll(put[r] & ((1ull << lane) - 1ull))] = v[r];
+            at += (int32_t)__popcll(put[r]);
+        }
+        if (threadIdx.x == 0)
+            count[e] = edge_count(total, b0 == re);
     }
 }
 
-// dflag[j] = 1 where sorted[j] starts a new distinct value inside a kept
-// hyperedge's sorted mapped members
-__global__ __launch_bounds__(kThreads) void k_distinct(const int32_t *__restrict__ ptr,
-                                                       const int32_t *__restrict__ sorted,
-                                                       const int32_t *__restrict__ inc_edge,
-                                                       const int32_t *__restrict__ kept, int64_t nnz,
-                                                       int32_t *__restrict__ dflag, const int *__restrict__ bad)
+// Writes the distinct values of the ascending v[0, n) to out (which may be v
+// itself: a round reads its values before it writes, and writes nothing past
+// them) and returns how many, to every thread of the workgroup.
+__device__ int32_t block_distinct(const int32_t *v, int32_t n, int32_t *out, int32_t (&part)[kSortBlockThreads / kWave])
 {
-    if (*bad)   // the step's input failed its checks
-        return;
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (j >= nnz)
-        return;
-    const int32_t e = inc_edge[j];
-    dflag[j] = (kept[e] && (j == ptr[e] || sorted[j] != sorted[j - 1])) ? 1 : 0;
-}
-
-// coarse members: the flagged values at their scanned positions
-__global__ __launch_bounds__(kThreads) void k_emit_members(const int32_t *__restrict__ sorted,
-                                                           const int32_t *__restrict__ dflag,
-                                                           const int32_t *__restrict__ dpos, int64_t nnz,
-                                                           int32_t *__restrict__ c_idx, const int *__restrict__ bad)
-{
-    if (*bad)   // the step's input failed its checks
-        return;
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (j < nnz && dflag[j])
-        c_idx[dpos[j]] = sorted[j];
-}
-
-// per hyperedge: edge_rep, coarse offset (the scanned position of its first
-// incidence, which is always flagged when kept) and weight
-__global__ __launch_bounds__(kThreads) void k_emit_edges(const int32_t *__restrict__ ptr,
-                                                         const int32_t *__restrict__ kept,
-                                                         const int32_t *__restrict__ krank,
-                                                         const int32_t *__restrict__ dpos,
-                                                         const float *__restrict__ w, int64_t n_edges,
-                                                         int32_t *__restrict__ edge_rep, int32_t *__restrict__ c_ptr,
-                                                         float *__restrict__ c_w, const int *__restrict__ bad)
-{
-    if (*bad)   // the step's input failed its checks
-        return;
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= n_edges)
-        return;
-    if (!kept[e]) {
-        edge_rep[e] = -1;
-        return;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    int32_t c = 0, last = -1;   // the values written, and the value before the round's first
+    for (uint32_t t = 0; t < (uint32_t)n; t += kSortBlockThreads) {
+        const uint32_t i = t + threadIdx.x;
+        const int32_t x = i < (uint32_t)n ? v[i] : -1;
+        const int32_t before = i >= (uint32_t)n ? -1 : threadIdx.x == 0 ? last : v[i - 1];
+        last = v[min(t + kSortBlockThreads, (uint32_t)n) - 1];
+        const bool put = i < (uint32_t)n && x != before;
+        const uint64_t m = __ballot(put);
+        if (lane == 0)
+            part[wave] = (int32_t)__popcll(m);
+        __syncthreads();   // (also: the round's values have been read)
+        int32_t at = c + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+        for (int w = 0; w < kSortBlockThreads / kWave; ++w) {
+            if (w < wave)
+                at += part[w];
+            c += part[w];
+        }
+        if (put)
+            out[at] = x;
+        __syncthreads();   // the counts have been read, the values written
     }
-    const int32_t r = krank[e];
-    edge_rep[e] = r;
-    c_ptr[r] = dpos[ptr[e]];
-    if (c_w)
-        c_w[r] = w ? w[e] : 1.0f;
+    return c;
 }
 
-// sizes[0..2] = coarse nodes, kept hyperedges, coarse incidences; closes c_ptr
-__global__ void k_sizes(const int32_t *__restrict__ gflag, const int32_t *__restrict__ gid, int64_t n_nodes,
-                        const int32_t *__restrict__ kept, const int32_t *__restrict__ krank, int64_t n_edges,
-                        const int32_t *__restrict__ dflag, const int32_t *__restrict__ dpos, int64_t nnz,
-                        int32_t *__restrict__ c_ptr, int64_t *__restrict__ sizes, const int *__restrict__ bad)
+// The lists of more than kSortLong members, a workgroup each: up to kSortBlock members bitonic in LDS; longer ones are
+// only mapped, and appended to the library sort's segments.
+__global__ __launch_bounds__(kSortBlockThreads) void k_list_block(
+    const int32_t *__restrict__ ptr, const int32_t *__restrict__ idx, const int32_t *__restrict__ node_rep,
+    const int32_t *__restrict__ best, const int32_t *__restrict__ rank, SizeOrder S, int32_t *__restrict__ out,
+    int32_t *__restrict__ mapped,
+    EdgeCount *__restrict__ count, int32_t *__restrict__ huge_begin, int32_t *__restrict__ huge_end,
+    int32_t *__restrict__ huge, int32_t *__restrict__ n_huge, const int *__restrict__ bad)
 {
     if (*bad)   // the step's input failed its checks
         return;
-    if (threadIdx.x != 0 || blockIdx.x != 0)
+    __shared__ int32_t v[kSortBlock];
+    __shared__ int32_t part[kSortBlockThreads / kWave];
+    const int64_t first = S.first_of(kSizeBins - 1);
+    for (int64_t l = S.n_edges - 1 - blockIdx.x; l >= first; l -= gridDim.x) {
+        const int32_t e = S.by_size[l], s = ptr[e], n = ptr[e + 1] - s;
+        if (n <= kSortLong)
+            break;   // the sizes descend
+        if (n > kSortBlock) {
+            for (uint32_t i = threadIdx.x; i < (uint32_t)n; i += kSortBlockThreads)
+                mapped[s + i] = node_rep[idx[s + i]];
+            if (threadIdx.x == 0) {
+                const int32_t h = atomicAdd(n_huge, 1);
+                huge_begin[h] = s;
+                huge_end[h] = s + n;
+                huge[h] = e;
+            }
+            continue;
+        }
+        int32_t cap = 2 * kSortLong;
+        while (cap < n)
+            cap *= 2;
+        for (int32_t i = threadIdx.x; i < cap; i += kSortBlockThreads)
+            v[i] = i < n ? node_rep[idx[s + i]] : INT_MAX;
+        __syncthreads();
+        for (int32_t k = 2; k <= cap; k <<= 1) {
+            for (int32_t j = k >> 1; j > 0; j >>= 1) {
+                for (int32_t p = threadIdx.x; p < cap / 2; p += kSortBlockThreads) {
+                    const int32_t i = 2 * p - (p & (j - 1)), q = i + j;   // pair p at distance j
+                    const int32_t x = v[i], y = v[q];
+                    const bool up = (i & k) == 0;
+                    v[i] = up ? min(x, y) : max(x, y);
+                    v[q] = up ? max(x, y) : min(x, y);
+                }
+                __syncthreads();
+            }
+        }
+        const int32_t c = block_distinct(v, n, out + s, part);
+        if (threadIdx.x == 0)
+            count[e] = edge_count(c, best[idx[s]] == rank[e]);
+        __syncthreads();   // the list's LDS has been read
+    }
+}
+
+// The lists the library sorted (in out): their distinct values, in place.
+__global__ __launch_bounds__(kSortBlockThreads) void k_list_huge(const int32_t *__restrict__ ptr,
+                                                                 const int32_t *__restrict__ idx,
+                                                                 const int32_t *__restrict__ best,
+                                                                 const int32_t *__restrict__ rank,
+                                                                 const int32_t *__restrict__ huge,
+                                                                 const int32_t *__restrict__ n_huge, int32_t *out,
+                                                                 EdgeCount *__restrict__ count,
+                                                                 const int *__restrict__ bad)
+{
+    if (*bad)   // the step's input failed its checks
         return;
-    const int64_t nv = n_nodes ? (int64_t)gid[n_nodes - 1] + gflag[n_nodes - 1] : 0;
-    const int64_t ne = n_edges ? (int64_t)krank[n_edges - 1] + kept[n_edges - 1] : 0;
-    const int64_t nz = nnz ? (int64_t)dpos[nnz - 1] + dflag[nnz - 1] : 0;
-    sizes[0] = nv;
-    sizes[1] = ne;
-    sizes[2] = nz;
-    c_ptr[ne] = (int32_t)nz;
+    __shared__ int32_t part[kSortBlockThreads / kWave];
+    const int32_t lists = *n_huge;
+    for (int32_t l = blockIdx.x; l < lists; l += gridDim.x) {
+        const int32_t e = huge[l], s = ptr[e], n = ptr[e + 1] - s;
+        const int32_t c = block_distinct(out + s, n, out + s, part);
+        if (threadIdx.x == 0)
+            count[e] = edge_count(c, best[idx[s]] == rank[e]);
+    }
+}
+
+// per hyperedge: edge_rep, and for a kept one its coarse offset, weight and
+// members (copied from the start of its segment; lists of more than kSortLong
+// are left to k_emit_long); the last hyperedge closes the offsets and writes
+// sizes[1] and sizes[2]
+__global__ __launch_bounds__(kThreads) void k_emit(const int32_t *__restrict__ ptr,
+                                                   const EdgeCount *__restrict__ count,
+                                                   const EdgeCount *__restrict__ at, const int32_t *__restrict__ lists,
+                                                   const float *__restrict__ w, int per, int64_t n_edges, int64_t nnz,
+                                                   int32_t *__restrict__ edge_rep, int32_t *__restrict__ c_ptr,
+                                                   int32_t *__restrict__ c_idx, float *__restrict__ c_w,
+                                                   int64_t *__restrict__ sizes, const int *__restrict__ bad)
+{
+    __shared__ WalkLds lds;
+    const int64_t e0 = window_start(per);
+    if (*bad || e0 >= n_edges)   // the step's input failed its checks
+        return;
+    const int64_t e = e0 + threadIdx.x % kWave;
+    const Window W = window_of(ptr, e0, per, n_edges, nnz);
+    int32_t until = 0, shift = 0;   // the segment's incidences below `until` go to their position + shift
+    if (threadIdx.x % kWave < per && e < n_edges) {
+        const EdgeCount c = count[e], p = at[e];
+        until = W.first + (ptr[e + 1] - W.first > kSortLong ? 0 : c.members);
+        shift = p.members - W.first;
+        edge_rep[e] = c.kept ? p.kept : -1;
+        if (c.kept) {
+            c_ptr[p.kept] = p.members;
+            if (c_w)
+                c_w[p.kept] = w ? w[e] : 1.0f;
+        }
+        if (e == n_edges - 1) {
+            sizes[1] = p.kept + c.kept;
+            sizes[2] = p.members + c.members;
+            c_ptr[p.kept + c.kept] = p.members + c.members;
+        }
+    }
+    walk_window<kWalk>(
+        W, lds, [&](uint32_t j, int, bool ok) { return ok ? lists[j] : 0; },
+        [&](uint32_t j, int l, bool ok, bool, int32_t x) {
+            const int32_t u = __shfl(until, l, kWave), d = __shfl(shift, l, kWave);
+            if (ok && j < (uint32_t)u)
+                c_idx[(int32_t)j + d] = x;
+        });
+}
+
+// the members of the lists of more than kSortLong, kEmitSplit workgroups each
+constexpr int kEmitSplit = 16;
+__global__ __launch_bounds__(kThreads) void k_emit_long(const int32_t *__restrict__ ptr,
+                                                        const EdgeCount *__restrict__ count,
+                                                        const EdgeCount *__restrict__ at,
+                                                        const int32_t *__restrict__ lists, SizeOrder S,
+                                                        int32_t *__restrict__ c_idx, const int *__restrict__ bad)
+{
+    if (*bad)   // the step's input failed its checks
+        return;
+    const int64_t first = S.first_of(kSizeBins - 1);
+    for (int64_t l = S.n_edges - 1 - blockIdx.x; l >= first; l -= gridDim.x) {
+        const int32_t e = S.by_size[l], s = ptr[e], to = at[e].members;
+        if (ptr[e + 1] - s <= kSortLong)
+            break;   // the sizes descend
+        const uint32_t n = count[e].members;
+        for (uint32_t i = blockIdx.y * kThreads + threadIdx.x; i < n; i += kEmitSplit * kThreads)
+            c_idx[to + i] = lists[s + i];
+    }
+}
+
+// The sizes a level without hyperedges, or without nodes, leaves open.
+__global__ void k_sizes_empty(int64_t n_nodes, int64_t n_edges, int32_t *__restrict__ c_ptr,
+                              int64_t *__restrict__ sizes, const int *__restrict__ bad)
+{
+    if (threadIdx.x != 0 || blockIdx.x != 0 || *bad)
+        return;
+    if (n_nodes == 0)
+        sizes[0] = 0;
+    if (n_edges == 0) {
+        sizes[1] = sizes[2] = 0;
+        c_ptr[0] = 0;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1183,22 +1623,38 @@ void launch_byte_scores(hipStream_t st, const int32_t *ptr, const int32_t *idx, 
 }
 
 // best[v] = least rank among v's hyperedges whose score equals bestq[v]
-__global__ __launch_bounds__(kThreads) void k_best_feat(const int32_t *__restrict__ idx,
-                                                        const int32_t *__restrict__ inc_edge,
+__global__ __launch_bounds__(kThreads) void k_best_feat(const int32_t *__restrict__ ptr,
+                                                        const int32_t *__restrict__ idx,
                                                         const int32_t *__restrict__ rank,
                                                         const double *__restrict__ q,
-                                                        const unsigned long long *__restrict__ bestq, int64_t nnz,
-                                                        int32_t *__restrict__ best)
+                                                        const unsigned long long *__restrict__ bestq, int per,
+                                                        int64_t n_edges, int64_t nnz, int32_t *__restrict__ best)
 {
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (j >= nnz)
+    __shared__ WalkLds lds;
+    const int64_t e0 = window_start(per);
+    if (e0 >= n_edges)
         return;
-    const int32_t v = idx[j];
-    if (ordered_bits(q[j]) == bestq[v]) {
-        const int32_t r = rank[inc_edge[j]];
-        if (r < best[v])   // an earlier read bounds the minimum from above
-            atomicMin(best + v, r);
-    }
+    const int64_t e = e0 + threadIdx.x % kWave;
+    const int32_t r = threadIdx.x % kWave < per && e < n_edges ? rank[e] : 0;
+    struct Score {
+        int32_t v;
+        unsigned long long q, most;
+    };
+    walk_window<kWalk>(
+        window_of(ptr, e0, per, n_edges, nnz), lds,
+        [&](uint32_t j, int, bool ok) {
+            Score x{ok ? idx[j] : 0, 0, 1};
+            if (ok) {
+                x.q = ordered_bits(q[j]);
+                x.most = bestq[x.v];
+            }
+            return x;
+        },
+        [&](uint32_t, int l, bool, bool, const Score &x) {
+            const int32_t lr = __shfl(r, l, kWave);
+            if (x.q == x.most && lr < best[x.v])   // an earlier read bounds the minimum from above
+                atomicMin(best + x.v, lr);
+        });
 }
 
 // coarse-node member lists: count, then place (the order inside a group is
@@ -1222,31 +1678,14 @@ __global__ __launch_bounds__(kThreads) void k_group_fill(const int32_t *__restri
     gnodes[gptr[g] + atomicAdd(gcur + g, 1)] = (int32_t)v;
 }
 
-// Member lists longer than kSortWave that one level can hold.
-int64_t max_big_lists(int64_t nnz) { return nnz / (kSortWave + 1) + 1; }
-
-// Temporary storage of the two sorts for the given key widths in bits (the
-// segmented sort over at most max_big_lists segments).
-hnv_status sort_storage(int64_t nE, int64_t nnz, int key_bits, int member_bits, size_t &t_keys, size_t &t_members)
-{
-    t_keys = t_members = 0;
-    hipError_t e = prim_sort_pairs(nullptr, t_keys, (uint64_t *)nullptr, (uint64_t *)nullptr,
-                                                      (int32_t *)nullptr, (int32_t *)nullptr,
-                                                      (int)std::max<int64_t>(nE, 1), 0, key_bits);
-    if (e == hipSuccess)
-        e = prim_segmented_sort_keys(nullptr, t_members, (uint32_t *)nullptr, (uint32_t *)nullptr,
-                                                       (int)std::max<int64_t>(nnz, 1), max_big_lists(nnz),
-                                                       (int32_t *)nullptr, (int32_t *)nullptr, 0, member_bits);
-    if (e != hipSuccess)
-        return fail(HNV_EDEVICE, std::string("sort storage query (needs a visible GPU): ") + hipGetErrorString(e));
-    return HNV_OK;
-}
+// Lists of more than `size` members that one level can hold.
+int64_t max_lists(int64_t n_nodes, int64_t nnz, int size) { return n_nodes > size ? nnz / (size + 1) : 0; }
 
 struct CoarsenLayout {
-    size_t keys_in, keys_out, ids_in, order, rank, best, choice, first, count, gflag, gid, kept, krank, mapped,
-        sorted, inc_edge, dflag, dpos, sizes, flag, big_begin, big_end, sort_counts, bstart;
+    size_t keys_in, keys_out, ids_in, order, rank, bins, bin_offs, best, choice, first, gflag, gid, count, at, mapped,
+        lists, spare, bstart, sizes, flag, n_huge, huge, huge_ends;
     // feature path (k > 0)
-    size_t fsum, fsq, q, bestq, gcount, gptr, gcur, gnodes;
+    size_t inc_edge, fsum, fsq, q, bestq, gcount, gptr, gcur, gnodes;
     size_t temp, temp_bytes, total;
 };
 
@@ -1264,29 +1703,32 @@ hnv_status layout(int64_t nV, int64_t nE, int64_t nnz, int k, CoarsenLayout &L)
     L.ids_in = take(4 * nE);
     L.order = take(4 * nE);
     L.rank = take(4 * nE);
+    const int64_t bins = bin_cap(nE, kSizeBins);
+    L.bins = take(4 * bins);
+    L.bin_offs = take(4 * bins);
     L.best = take(4 * nV);
     L.choice = take(4 * nV);
     L.first = take(4 * nE);
-    L.count = take(4 * nE);
     L.gflag = take(4 * nV);
     L.gid = take(4 * nV);
-    L.kept = take(4 * nE);
-    L.krank = take(4 * nE);
+    L.count = take(sizeof(EdgeCount) * nE);
+    L.at = take(sizeof(EdgeCount) * nE);
     L.mapped = take(4 * nnz);
-    L.sorted = take(4 * nnz);
-    L.inc_edge = take(4 * nnz);
-    L.dflag = take(4 * nnz);
-    L.dpos = take(4 * nnz);
-    // the check word (int flags, pad, uint64 feature total) and the coarse
-    // sizes (3 x int64) side by side: one read-back takes both
-    L.flag = take(16 + 8 * 4);
-    L.sizes = L.flag + 16;
-    L.big_begin = take(4 * max_big_lists(nnz));
-    L.big_end = take(4 * max_big_lists(nnz));
-    L.sort_counts = take(8);
+    L.lists = take(4 * nnz);
+    L.spare = take(bucketed_best(nV, nnz) ? 4 * nnz : 0);
     L.bstart = take(8 * (size_t)(std::max<int64_t>(nV >> kBucketShiftMax, 256) + 2));
-    L.fsum = L.fsq = L.q = L.bestq = L.gcount = L.gptr = L.gcur = L.gnodes = 0;
+    // the check word (int flags, largest count, uint64 feature total), the
+    // coarse sizes (3 x int64; one read-back takes both) and the count of the
+    // lists for the library's sort, cleared together
+    L.flag = take(64);
+    L.sizes = L.flag + 16;
+    L.n_huge = L.flag + 40;
+    const int64_t max_huge = max_lists(nV, nnz, kSortBlock);
+    L.huge = take(4 * max_huge);
+    L.huge_ends = take(8 * max_huge);
+    L.inc_edge = L.fsum = L.fsq = L.q = L.bestq = L.gcount = L.gptr = L.gcur = L.gnodes = 0;
     if (k > 0) {
+        L.inc_edge = take(4 * nnz);
         // the member sums of the int32 path, or the byte copy of X of the byte path
         L.fsum = take(std::max(4 * (size_t)nE * k, k <= kByteCols ? (size_t)nV * byte_stride(k) : 0));
         L.fsq = take(8 * nE);
@@ -1297,21 +1739,28 @@ hnv_status layout(int64_t nV, int64_t nE, int64_t nnz, int k, CoarsenLayout &L)
         L.gcur = take(4 * nV);
         L.gnodes = take(4 * nV);
     }
-    size_t t1 = 0, t2 = 0, t3 = 0, t4 = 0;
-    if (hnv_status st = sort_storage(nE, nnz, 64, 32, t1, t4); st != HNV_OK)
-        return st;
-    hipError_t e = prim_exclusive_sum(nullptr, t2, (int32_t *)nullptr, (int32_t *)nullptr,
-                                                    (int)std::max<int64_t>(nV + 1, 1));
+    size_t t[7] = {};
+    const int64_t scan = std::max<int64_t>(std::max(nV + 1, bins), 1);
+    hipError_t e = prim_exclusive_sum(nullptr, t[0], (int32_t *)nullptr, (int32_t *)nullptr, scan);
     if (e == hipSuccess)
-        e = prim_exclusive_sum(nullptr, t3, (int32_t *)nullptr, (int32_t *)nullptr,
-                                             (int)std::max<int64_t>(std::max(nE, nnz), 1));
-    size_t t6 = 0;
+        e = prim_exclusive_scan(nullptr, t[1], (EdgeCount *)nullptr, (EdgeCount *)nullptr, EdgeCount{0, 0},
+                                std::max<int64_t>(nE, 1), EdgeCountPlus());
+    if (e == hipSuccess)
+        e = prim_sort_pairs(nullptr, t[2], (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr,
+                            (int32_t *)nullptr, std::max<int64_t>(nE, 1), 0, 31);
+    if (e == hipSuccess && max_last_bin(nV, nnz) > kBigMax)
+        e = prim_sort_pairs(nullptr, t[3], (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr,
+                            (int32_t *)nullptr, std::max<int64_t>(nE, 1), 0, bits_for(nV + 1));
+    if (e == hipSuccess && max_huge > 0)
+        e = prim_segmented_sort_keys(nullptr, t[4], (uint32_t *)nullptr, (uint32_t *)nullptr, nnz, max_huge,
+                                     (int32_t *)nullptr, (int32_t *)nullptr, 0, bits_for(nV));
     if (e == hipSuccess && bucketed_best(nV, nnz))
-        e = prim_sort_pairs(nullptr, t6, (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr,
+        e = prim_sort_pairs(nullptr, t[5], (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr,
                             (int32_t *)nullptr, nnz, bucket_shift(nV), bits_for(nV));
     if (e != hipSuccess)
-        return fail(HNV_EDEVICE, std::string("scan storage query (needs a visible GPU): ") + hipGetErrorString(e));
-    L.temp_bytes = std::max(std::max(std::max(t1, t2), std::max(t3, t4)), t6);
+        return fail(HNV_EDEVICE, std::string("sort / scan storage query (needs a visible GPU): ") +
+                                     hipGetErrorString(e));
+    L.temp_bytes = *std::max_element(t, t + 7);
     L.temp = take(L.temp_bytes);
     L.total = (off + 255) & ~size_t(255);
     return HNV_OK;
@@ -1359,6 +1808,8 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
     auto at = [&](size_t off) { return reinterpret_cast<int32_t *>(base + off); };
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int nV = (int)n_nodes, nE = (int)n_edges, nz = (int)nnz;
+    const int per = window_size(n_edges);
+    const unsigned wgrid = window_grid(n_edges);
     auto sync_read = [&](void *dst, const void *src, size_t n) -> hnv_status {
         hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess)
@@ -1369,17 +1820,12 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
     // 0. input check (every later kernel trusts offsets, member ids, counts)
     int *flag = reinterpret_cast<int *>(base + L.flag);
     unsigned long long *total = reinterpret_cast<unsigned long long *>(base + L.flag + 8);
-    k_fill<<<1, kThreads, 0, s>>>(flag, 4, 0);
-    int32_t *inc_edge = at(L.inc_edge), *dflag = at(L.dflag), *dpos = at(L.dpos);
-    if (nE > 0) {
-        k_check_edges<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, edge_w, n_edges, nnz, 1, flag);
-        if (nz > 0) {
-            k_fill<<<grid_for(nz), kThreads, 0, s>>>(inc_edge, nnz, 0);
-            k_inc_edge<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, n_edges, nnz, inc_edge);
-            k_check_members<<<grid_for(nz), kThreads, 0, s>>>(edge_ptr, edge_idx, inc_edge, n_nodes, n_edges, nnz, 1,
-                                                              flag);
-        }
-    }
+    k_fill<<<1, kThreads, 0, s>>>(flag, 12, 0);
+    int32_t *first = at(L.first);
+    uint32_t *size_key = reinterpret_cast<uint32_t *>(base + L.keys_in);
+    if (nE > 0)
+        k_check_level<<<wgrid, kThreads, 0, s>>>(edge_ptr, edge_idx, edge_w, n_nodes, per, n_edges, nnz, 1, nullptr,
+                                                        size_key, kSizeBins - 1, first, flag);
     if (feat && nV > 0) {
         const int kp4 = (k <= kByteCols ? byte_stride(k) : k) / 4;
         k_fcheck<<<(unsigned)std::min<int64_t>(grid_for((int64_t)nV * kp4), 2048), kThreads, 0, s>>>(
@@ -1424,44 +1870,72 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
     const bool bytes = feat && k <= kByteCols && chk.largest <= 255;
 
     int32_t *order = at(L.order), *rank = at(L.rank), *best = at(L.best), *choice = at(L.choice);
-    int32_t *first = at(L.first), *count = at(L.count), *gflag = at(L.gflag), *gid = at(L.gid);
-    int32_t *kept = at(L.kept), *krank = at(L.krank), *mapped = at(L.mapped), *sorted = at(L.sorted);
+    int32_t *gflag = at(L.gflag), *gid = at(L.gid);
+    int32_t *mapped = at(L.mapped), *lists = at(L.lists);
+    EdgeCount *count = reinterpret_cast<EdgeCount *>(base + L.count);
+    EdgeCount *place = reinterpret_cast<EdgeCount *>(base + L.at);
     int64_t *sizes = reinterpret_cast<int64_t *>(base + L.sizes);
     void *temp = base + L.temp;
     size_t tb = L.temp_bytes;
-    // Without weights every key's weight part is the same: sort the size bits
-    // only.  Coarse member ids are below n_nodes.
-    const int size_bits = bits_for(n_nodes + 1);
-    const int key_bits = edge_w ? 32 + size_bits : size_bits, member_bits = bits_for(n_nodes);
-    {
-        size_t need_keys = 0, need_members = 0;
-        if ((st = sort_storage(n_edges, nnz, key_bits, member_bits, need_keys, need_members)) != HNV_OK)
-            return st;
-        if (need_keys > L.temp_bytes || need_members > L.temp_bytes)
-            return fail(HNV_EDEVICE, "sort storage exceeds the queried size");
-    }
+    SizeOrder S{};
     if (nE > 0) {
-        // 1. ranks in the order (weight descending, size ascending, id ascending)
-        uint64_t *kin = reinterpret_cast<uint64_t *>(base + L.keys_in);
-        uint64_t *kout = reinterpret_cast<uint64_t *>(base + L.keys_out);
-        k_keys<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, edge_w, n_edges, size_bits, kin, at(L.ids_in));
-        if (prim_sort_pairs(temp, tb, kin, kout, at(L.ids_in), order, nE, 0, key_bits, s) != hipSuccess)
-            return fail(HNV_EDEVICE, "radix sort of hyperedge keys");
+        // 1. ranks in the order (weight descending, size ascending, id
+        // ascending): the size order, which is the whole order without weights
+        int32_t *bins = at(L.bins), *offs = at(L.bin_offs);
+        int32_t *by_size = edge_w ? at(L.ids_in) : order, *size_rank = edge_w ? nullptr : rank;
+        const int rounds = bin_rounds(n_edges);
+        const int64_t tiles = bin_tiles(n_edges), last_bin = max_last_bin(n_nodes, nnz);
+        S = SizeOrder{by_size, offs, tiles, n_edges};
+        k_bin_count<<<(unsigned)tiles, kThreads, 0, s>>>(size_key, n_edges, nullptr, 0, ~0u, kSizeBins, rounds, tiles,
+                                                         bins);
+        if (prim_exclusive_sum(temp, tb, bins, offs, tiles * kSizeBins, s) != hipSuccess)
+            return fail(HNV_EDEVICE, "scan of the size counts");
+        if (last_bin <= kBigMax) {
+            k_bin_scatter<<<(unsigned)tiles, kThreads, 0, s>>>(size_key, nullptr, n_edges, nullptr, 0, ~0u, kSizeBins,
+                                                               bits_for(kSizeBins), rounds, tiles, offs, nullptr,
+                                                               by_size, size_rank);
+            if (last_bin > 0) {
+                int32_t *tmp = at(L.keys_out);
+                k_big_rank<<<grid_for(last_bin), kThreads, 0, s>>>(edge_ptr, by_size, offs, tiles, n_edges, tmp,
+                                                                   size_rank, flag);
+                k_big_order<<<grid_for(last_bin), kThreads, 0, s>>>(tmp, offs, tiles, n_edges, by_size, flag);
+            }
+        } else {
+            uint32_t *kin = reinterpret_cast<uint32_t *>(base + L.keys_in);
+            uint32_t *kout = reinterpret_cast<uint32_t *>(base + L.keys_out);
+            int32_t *ids = reinterpret_cast<int32_t *>(kin + n_edges);
+            k_size_keys<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, n_edges, kin, ids);
+            tb = L.temp_bytes;
+            if (prim_sort_pairs(temp, tb, kin, kout, ids, by_size, nE, 0, bits_for(n_nodes + 1), s) != hipSuccess)
+                return fail(HNV_EDEVICE, "radix sort of hyperedge sizes");
+            if (!edge_w)
+                k_rank<<<grid_for(nE), kThreads, 0, s>>>(by_size, n_edges, rank);
+        }
+        if (edge_w) {
+            uint32_t *kin = reinterpret_cast<uint32_t *>(base + L.keys_in);
+            uint32_t *kout = reinterpret_cast<uint32_t *>(base + L.keys_out);
+            k_weight_keys<<<grid_for(nE), kThreads, 0, s>>>(by_size, edge_w, n_edges, kin);
+            tb = L.temp_bytes;
+            if (prim_sort_pairs(temp, tb, kin, kout, by_size, order, nE, 0, 31, s) != hipSuccess)
+                return fail(HNV_EDEVICE, "radix sort of hyperedge weights");
+            k_rank<<<grid_for(nE), kThreads, 0, s>>>(order, n_edges, rank);
+        }
     }
-    if (nE > 0 || nV > 0)
-        k_rank<<<grid_for(std::max(nE, nV)), kThreads, 0, s>>>(order, n_edges, n_nodes, rank, first, count, best);
     if (nV > 0) {
         // 2. choices: the least rank, or (features) the least rank among the
         // hyperedges of best cosine score
+        const bool buckets = nE > 0 && !feat && bucketed_best(n_nodes, nnz);
+        if (!buckets)
+            k_fill<<<grid_for(nV), kThreads, 0, s>>>(best, n_nodes, INT_MAX);
         if (nE > 0 && !feat) {
-            if (bucketed_best(n_nodes, nnz)) {
-                // (mapped, sorted and dflag are free until step 5)
-                int32_t *pr = mapped, *pr_sorted = dflag;
-                uint32_t *nodes_sorted = reinterpret_cast<uint32_t *>(sorted);
+            if (buckets) {
+                // (mapped and lists are free until step 5)
+                int32_t *pr = mapped, *pr_sorted = at(L.spare);
+                uint32_t *nodes_sorted = reinterpret_cast<uint32_t *>(lists);
                 const int shift = bucket_shift(n_nodes);
                 const int64_t nb = bucket_count(n_nodes);
                 int64_t *bstart = reinterpret_cast<int64_t *>(base + L.bstart);
-                k_inc_rank<<<grid_for(nz), kThreads, 0, s>>>(inc_edge, rank, nnz, pr);
+                k_inc_rank<<<wgrid, kThreads, 0, s>>>(edge_ptr, rank, per, n_edges, nnz, pr, flag);
                 tb = L.temp_bytes;
                 if (prim_sort_pairs(temp, tb, reinterpret_cast<const uint32_t *>(edge_idx), nodes_sorted, pr,
                                     pr_sorted, nz, shift, bits_for(n_nodes), s) != hipSuccess)
@@ -1470,7 +1944,7 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
                 k_bucket_min<<<(unsigned)nb, kBucketThreads, 0, s>>>(nodes_sorted, pr_sorted, bstart, shift, n_nodes,
                                                                      best, flag);
             } else {
-                k_best<<<grid_for(nz), kThreads, 0, s>>>(edge_idx, inc_edge, rank, nnz, best, flag);
+                k_best<<<wgrid, kThreads, 0, s>>>(edge_ptr, edge_idx, rank, per, n_edges, nnz, best, flag);
             }
         }
         if (nE > 0 && feat) {
@@ -1493,60 +1967,71 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
                 else if (kp <= 512) HNV_BYTES(32);
                 else HNV_BYTES(64);
 #undef HNV_BYTES
-            } else switch (pieces_for(k)) {
-            case 1: launch_edge_features<1>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
-            case 2: launch_edge_features<2>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
-            case 4: launch_edge_features<4>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
-            case 8: launch_edge_features<8>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
-            default: launch_edge_features<0>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq);
+            } else {
+                int32_t *inc_edge = at(L.inc_edge);
+                k_inc_edge<<<wgrid, kThreads, 0, s>>>(edge_ptr, per, n_edges, nnz, inc_edge);
+                switch (pieces_for(k)) {
+                case 1: launch_edge_features<1>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
+                case 2: launch_edge_features<2>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
+                case 4: launch_edge_features<4>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
+                case 8: launch_edge_features<8>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq); break;
+                default: launch_edge_features<0>(wave_grid, s, edge_ptr, edge_idx, inc_edge, x, k, n_edges, nnz, fsum, fsq, q, bestq);
+                }
             }
-            k_best_feat<<<grid_for(nz), kThreads, 0, s>>>(edge_idx, inc_edge, rank, q, bestq, nnz, best);
+            k_best_feat<<<wgrid, kThreads, 0, s>>>(edge_ptr, edge_idx, rank, q, bestq, per, n_edges, nnz, best);
         }
-        k_choice<<<grid_for(nV), kThreads, 0, s>>>(best, order, n_nodes, choice, first, count);
+        k_choice<<<grid_for(nV), kThreads, 0, s>>>(best, order, n_nodes, choice, first);
         // 3. group numbering by smallest node
         k_group_flags<<<grid_for(nV), kThreads, 0, s>>>(choice, first, n_nodes, gflag);
         tb = L.temp_bytes;
         if (prim_exclusive_sum(temp, tb, gflag, gid, nV, s) != hipSuccess)
             return fail(HNV_EDEVICE, "scan of group flags");
-        k_node_rep<<<grid_for(nV), kThreads, 0, s>>>(choice, first, gid, n_nodes, node_rep, flag);
+        k_node_rep<<<grid_for(nV), kThreads, 0, s>>>(choice, first, gid, n_nodes, node_rep, sizes, flag);
     }
     if (nE > 0) {
-        // 4. removed hyperedges
-        k_kept_flags<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, count, n_edges, kept);
-        tb = L.temp_bytes;
-        if (prim_exclusive_sum(temp, tb, kept, krank, nE, s) != hipSuccess)
-            return fail(HNV_EDEVICE, "scan of kept flags");
-        // 5. coarse member sets: every hyperedge's mapped members sorted (short
-        // lists by a thread, medium ones by a wavefront, long ones by the
-        // library's segmented sort over a list of them)
-        if (nz > 0) {
-            k_map<<<grid_for(nz), kThreads, 0, s>>>(edge_idx, node_rep, nnz, mapped, flag);
-            int32_t *big_begin = at(L.big_begin), *big_end = at(L.big_end), *n_big_dev = at(L.sort_counts);
-            const int64_t n_big = max_big_lists(nnz);
-            k_clear_big<<<grid_for(n_big), kThreads, 0, s>>>(n_big_dev, big_begin, big_end, n_big);
-            k_sort_short<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, mapped, n_edges, sorted, big_begin, big_end,
-                                                            n_big_dev, flag);
-            if (nnz > kSortThread)
-                k_sort_wave<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, mapped, n_edges, sorted, flag);
-            if (nnz > kSortWave) {
-                tb = L.temp_bytes;
-                // non-negative ids: sorted as unsigned so only the low bits count;
-                // unused segments are empty
-                if (prim_segmented_sort_keys(temp, tb, reinterpret_cast<const uint32_t *>(mapped),
-                                             reinterpret_cast<uint32_t *>(sorted), nz, n_big, big_begin, big_end, 0,
-                                             member_bits, s) != hipSuccess)
-                    return fail(HNV_EDEVICE, "segmented sort of long coarse member lists");
-            }
+        // 4. coarse member lists, and with them the removed hyperedges
+        const int64_t max_big = max_lists(n_nodes, nnz, kSortLong), max_huge = max_lists(n_nodes, nnz, kSortBlock);
+        int32_t *huge = at(L.huge), *huge_begin = at(L.huge_ends), *huge_end = huge_begin + max_huge;
+        int32_t *n_huge = at(L.n_huge);
+        auto blocks = [&](int longer_than, int per_block, int most) {   // for the lists of more than `longer_than`
+            return (unsigned)std::min<int64_t>(max_lists(n_nodes, nnz, longer_than) / per_block + 1, most);
+        };
+        k_list_short<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, edge_idx, node_rep, best, rank, n_edges, lists, count,
+                                                       flag);
+        if (max_lists(n_nodes, nnz, kSortThread) > 0)
+            k_list_wave<<<blocks(kSortThread, kThreads / kWave, kListBlocks), kThreads, 0, s>>>(
+                edge_ptr, edge_idx, node_rep, best, rank, S, lists, count, flag);
+        if (max_lists(n_nodes, nnz, kSortMid) > 0)
+            k_list_long<<<blocks(kSortMid, 1, kListBlocks), kThreads, 0, s>>>(edge_ptr, edge_idx, node_rep, best, rank, S,
+                                                                              lists, count, flag);
+        if (max_huge > 0)   // unused segments are empty
+            k_fill<<<grid_for(2 * max_huge), kThreads, 0, s>>>(huge_begin, 2 * max_huge, 0);
+        if (max_big > 0)
+            k_list_block<<<blocks(kSortLong, 1, 512), kSortBlockThreads, 0, s>>>(
+                edge_ptr, edge_idx, node_rep, best, rank, S, lists, mapped, count, huge_begin, huge_end, huge, n_huge,
+                flag);
+        if (max_huge > 0) {
+            tb = L.temp_bytes;
+            // non-negative ids below n_nodes: sorted as unsigned so only the low bits count
+            if (prim_segmented_sort_keys(temp, tb, reinterpret_cast<const uint32_t *>(mapped),
+                                         reinterpret_cast<uint32_t *>(lists), nz, max_huge, huge_begin, huge_end, 0,
+                                         bits_for(n_nodes), s) != hipSuccess)
+                return fail(HNV_EDEVICE, "segmented sort of very long coarse member lists");
+            k_list_huge<<<(unsigned)std::min<int64_t>(max_huge, 512), kSortBlockThreads, 0, s>>>(
+                edge_ptr, edge_idx, best, rank, huge, n_huge, lists, count, flag);
         }
-        k_distinct<<<grid_for(nz), kThreads, 0, s>>>(edge_ptr, sorted, inc_edge, kept, nnz, dflag, flag);
+        // 5. the kept hyperedges' numbers and offsets, and the coarse arrays
         tb = L.temp_bytes;
-        if (prim_exclusive_sum(temp, tb, dflag, dpos, nz, s) != hipSuccess)
-            return fail(HNV_EDEVICE, "scan of coarse members");
-        k_emit_members<<<grid_for(nz), kThreads, 0, s>>>(sorted, dflag, dpos, nnz, c_edge_idx, flag);
-        k_emit_edges<<<grid_for(nE), kThreads, 0, s>>>(edge_ptr, kept, krank, dpos, edge_w, n_edges, edge_rep,
-                                                       c_edge_ptr, c_edge_w, flag);
+        if (prim_exclusive_scan(temp, tb, count, place, EdgeCount{0, 0}, nE, EdgeCountPlus(), s) != hipSuccess)
+            return fail(HNV_EDEVICE, "scan of the coarse member counts");
+        k_emit<<<wgrid, kThreads, 0, s>>>(edge_ptr, count, place, lists, edge_w, per, n_edges, nnz, edge_rep,
+                                                 c_edge_ptr, c_edge_idx, c_edge_w, sizes, flag);
+        if (max_big > 0)
+            k_emit_long<<<dim3(blocks(kSortLong, 1, 256), kEmitSplit), kThreads, 0, s>>>(edge_ptr, count, place, lists, S,
+                                                                                         c_edge_idx, flag);
     }
-    k_sizes<<<1, 64, 0, s>>>(gflag, gid, n_nodes, kept, krank, n_edges, dflag, dpos, nnz, c_edge_ptr, sizes, flag);
+    if (nV == 0 || nE == 0)
+        k_sizes_empty<<<1, 64, 0, s>>>(n_nodes, n_edges, c_edge_ptr, sizes, flag);
     if (feat && nV > 0) {
         // 6. X': each coarse node's row is the sum of its fine nodes' rows
         int32_t *gcount = at(L.gcount), *gptr = at(L.gptr), *gcur = at(L.gcur), *gnodes = at(L.gnodes);

@@ -16,6 +16,7 @@
 // scratch embedding when it is large enough, else after the plan.
 #include <hip/hip_runtime.h>
 
+#include "hnv_binsort.h"
 #include "hnv_prim.h"
 
 #include <algorithm>
@@ -83,118 +84,6 @@ __global__ void k_check_no_edges(const int32_t *__restrict__ ptr, int64_t nnz, i
 {
     if (threadIdx.x == 0 && blockIdx.x == 0 && (ptr[0] != 0 || nnz != 0))
         atomicOr(flag, 1);
-}
-
-// One pass of a stable counting sort of (key, value) pairs by the digit
-// (key >> shift) & mask, which is below n_bins <= kBinsMax: per-tile counts
-// of every digit, an exclusive scan of the counts laid out digit-major
-// (digit b of tile t at b * n_tiles + t), and a scatter in which each tile
-// places its elements in input order.  The degree tiers of both sides need
-// one pass (2 (small_max + 3) keys), the wavefront tier's chunk keys one pass
-// while both sides' keys (2 chunk_keys) fit in kBinsMax, else one per 10 bits;
-// the result equals a stable radix sort's.  The number of pairs is n_max, or
-// *n_dev when that is given (the grid is sized for n_max).  The values may
-// be absent (null); a one-pass sort can also write each input element's
-// sorted position (pos_out).
-constexpr int kBinsMax = 1024;
-constexpr int kBinBits = 10;   // digit width of the multi-pass form
-constexpr int kBinRounds = 16;
-constexpr int kBinTile = kThreads * kBinRounds;
-constexpr int kBinWaves = kThreads / kWave;
-
-__device__ inline int64_t pairs_of(int64_t n_max, const int64_t *n_dev)
-{
-    return n_dev ? min(n_max, *n_dev) : n_max;
-}
-
-__global__ __launch_bounds__(kThreads) void k_bin_count(const uint32_t *__restrict__ key, int64_t n_max,
-                                                        const int64_t *__restrict__ n_dev, int shift, uint32_t mask,
-                                                        int n_bins, int64_t n_tiles, int32_t *__restrict__ counts)
-{
-    __shared__ int32_t h[kBinsMax];
-    for (int b = threadIdx.x; b < n_bins; b += kThreads)
-        h[b] = 0;
-    __syncthreads();
-    const int64_t n = pairs_of(n_max, n_dev);
-    const int64_t base = (int64_t)blockIdx.x * kBinTile;
-    for (int k = 0; k < kBinRounds; ++k) {
-        const int64_t i = base + (int64_t)k * kThreads + threadIdx.x;
-        if (i < n)
-            atomicAdd(&h[(key[i] >> shift) & mask], 1);
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < n_bins; b += kThreads)
-        counts[(int64_t)b * n_tiles + blockIdx.x] = h[b];
-}
-
-// The lanes of the wavefront that hold the same key (active lanes only):
-// one ballot per key bit.  Every lane of the wavefront must call it.
-__device__ inline uint64_t same_key_lanes(uint32_t key, int bits, bool active)
-{
-    uint64_t m = __ballot(active);
-    for (int b = 0; b < bits; ++b) {
-        const bool one = (key >> b) & 1u;
-        const uint64_t ones = __ballot(active && one);
-        m &= one ? ones : ~ones;
-    }
-    return m;
-}
-
-// Round k of a tile places elements base + k * kThreads + [0, kThreads):
-// an element goes to the next free position of its key, after the elements
-// of the same key in lower lanes of its wavefront and in lower wavefronts.
-__global__ __launch_bounds__(kThreads) void k_bin_scatter(const uint32_t *__restrict__ key,
-                                                          const int32_t *__restrict__ val, int64_t n_max,
-                                                          const int64_t *__restrict__ n_dev, int shift,
-                                                          uint32_t mask, int n_bins, int bits, int64_t n_tiles,
-                                                          const int32_t *__restrict__ offs,
-                                                          uint32_t *__restrict__ key_out,
-                                                          int32_t *__restrict__ val_out,
-                                                          int32_t *__restrict__ pos_out)
-{
-    __shared__ int32_t next[kBinsMax];
-    __shared__ int32_t wcount[kBinWaves][kBinsMax];
-    for (int b = threadIdx.x; b < n_bins; b += kThreads) {
-        next[b] = offs[(int64_t)b * n_tiles + blockIdx.x];
-        for (int w = 0; w < kBinWaves; ++w)
-            wcount[w][b] = 0;
-    }
-    __syncthreads();
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-    const int64_t n = pairs_of(n_max, n_dev);
-    const int64_t base = (int64_t)blockIdx.x * kBinTile;
-    for (int k = 0; k < kBinRounds && base + (int64_t)k * kThreads < n; ++k) {   // uniform over the block
-        const int64_t i = base + (int64_t)k * kThreads + threadIdx.x;
-        const bool act = i < n;
-        const uint32_t kv = act ? key[i] : 0u;
-        const uint32_t dg = (kv >> shift) & mask;
-        const uint64_t peers = same_key_lanes(dg, bits, act);
-        const int rank = __popcll(peers & below);
-        if (act && rank == 0)
-            wcount[wave][dg] = __popcll(peers);
-        __syncthreads();
-        if (act) {
-            int32_t pos = next[dg] + rank;
-            for (int w = 0; w < wave; ++w)
-                pos += wcount[w][dg];
-            key_out[pos] = kv;
-            if (val_out)
-                val_out[pos] = val[i];
-            if (pos_out)
-                pos_out[i] = pos;
-        }
-        __syncthreads();
-        for (int b = threadIdx.x; b < n_bins; b += kThreads) {
-            int32_t add = 0;
-            for (int w = 0; w < kBinWaves; ++w) {
-                add += wcount[w][b];
-                wcount[w][b] = 0;
-            }
-            next[b] += add;
-        }
-        __syncthreads();
-    }
 }
 
 // A level's build runs to its end even when its checks failed, so that the
@@ -294,10 +183,13 @@ __global__ __launch_bounds__(kThreads) void k_side1_idx(const int32_t *__restric
     const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (j >= nnz)
         return;
-    const int32_t u = csc_e[j] + n_nodes;
+    // (of a level that failed its checks the incidence map may have gaps:
+    // hyperedge 0, which the weights' fill then reads)
+    const bool failed = level_failed(bad);
+    const int32_t u = failed ? n_nodes : csc_e[j] + n_nodes;
     idx[j] = u;
     if (cidx)
-        cidx[j] = level_failed(bad) ? 0 : rowmap[u];
+        cidx[j] = failed ? 0 : rowmap[u];
 }
 
 // A row's wavefront-tier counts: its chunks, whether it is split, its
@@ -593,9 +485,6 @@ static_assert(kTierAlign % kWave == 0, "a wavefront of tier entries must lie in 
 int64_t side1_offset(int64_t n_edges) { return (n_edges + 1 + kTierAlign - 1) / kTierAlign * kTierAlign; }
 int64_t tier_entries(int64_t rows) { return rows + 2 + kTierAlign; }
 
-// entries of the key-count arrays of a bin sort of up to `rows` pairs
-int64_t bin_cap(int64_t rows, int n_bins) { return (int64_t)n_bins * (rows / kBinTile + 1); }
-
 hnv_status cub_sizes(int64_t nnz, int64_t rows, int64_t n_chunks, int64_t bins, size_t &bytes)
 {
     size_t t[6] = {0, 0, 0, 0, 0, 0};
@@ -743,14 +632,6 @@ hnv_status copy_d2d(void *dst, const void *src, size_t n, hipStream_t s)
     return e == hipSuccess ? HNV_OK : fail(HNV_EDEVICE, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
 }
 
-// S.inc_edge[j] = the hyperedge of incidence j
-hnv_status incidence_edges(const int32_t *ptr, int64_t nE, int64_t nnz, Scratch &S, hipStream_t s)
-{
-    k_fill<<<grid_for(nnz), kThreads, 0, s>>>(S.inc_edge, nnz, 0);
-    k_inc_edge<<<grid_for(nE), kThreads, 0, s>>>(ptr, nE, nnz, S.inc_edge);
-    return dev_check("incidence map");
-}
-
 // Checks of level l and (with a coarser level) of map l, launched without
 // waiting: flags[0] gets the level's bits, flags[1] the map's.  The map's
 // member-following check does nothing unless the level's offsets and member
@@ -760,13 +641,8 @@ hnv_status launch_checks(const hnv_level_dev &L, const hnv_level_dev *C, const h
 {
     const int64_t nV = L.n_nodes, nE = L.n_edges, nnz = L.nnz;
     if (nE > 0) {
-        k_check_edges<<<grid_for(nE), kThreads, 0, s>>>(L.edge_ptr, L.edge_w, nE, nnz, full ? 1 : 0, flags);
-        if (nnz > 0) {
-            if (hnv_status st = incidence_edges(L.edge_ptr, nE, nnz, S, s); st != HNV_OK)
-                return st;
-            k_check_members<<<grid_for(nnz), kThreads, 0, s>>>(L.edge_ptr, L.edge_idx, S.inc_edge, nV, nE, nnz,
-                                                              full ? 1 : 0, flags);
-        }
+        k_check_level<<<window_grid(nE), kThreads, 0, s>>>(L.edge_ptr, L.edge_idx, L.edge_w, nV, window_size(nE), nE, nnz,
+                                                           full ? 1 : 0, S.inc_edge, nullptr, 0, nullptr, flags);
     } else {
         k_check_no_edges<<<1, 64, 0, s>>>(L.edge_ptr, nnz, flags);
     }
@@ -817,7 +693,8 @@ hnv_status bin_sort(uint32_t *ka, int32_t *va, uint32_t *kb, int32_t *vb, int64_
     in_b = false;
     if (n_max == 0)
         return HNV_OK;
-    const int64_t tiles = (n_max + kBinTile - 1) / kBinTile;
+    const int rounds = bin_rounds(n_max);
+    const int64_t tiles = bin_tiles(n_max);
     const bool one = key_limit <= kBinsMax;
     const int passes = one ? 1 : (bits_for(key_limit) + kBinBits - 1) / kBinBits;
     const int n_bins = one ? (int)key_limit : kBinsMax;
@@ -828,12 +705,14 @@ hnv_status bin_sort(uint32_t *ka, int32_t *va, uint32_t *kb, int32_t *vb, int64_
     int32_t *vin = va, *vout = vb;
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = pass * kBinBits;
-        k_bin_count<<<(unsigned)tiles, kThreads, 0, s>>>(kin, n_max, n_dev, shift, mask, n_bins, tiles, S.bin_counts);
+        k_bin_count<<<(unsigned)tiles, kThreads, 0, s>>>(kin, n_max, n_dev, shift, mask, n_bins, rounds, tiles,
+                                                         S.bin_counts);
         size_t tb = S.temp_bytes;
         if (prim_exclusive_sum(S.temp, tb, S.bin_counts, S.bin_offs, tiles * n_bins, s) != hipSuccess)
             return fail(HNV_EDEVICE, "scan of a counting sort's digit counts");
         k_bin_scatter<<<(unsigned)tiles, kThreads, 0, s>>>(kin, vin, n_max, n_dev, shift, mask, n_bins,
-                                                           bits_for(n_bins), tiles, S.bin_offs, kout, vout, pos_out);
+                                                           bits_for(n_bins), rounds, tiles, S.bin_offs, kout,
+                                                           vin ? vout : nullptr, pos_out);
         std::swap(kin, kout);
         std::swap(vin, vout);
         in_b = !in_b;

@@ -241,3 +241,65 @@ def test_member_sort_boundaries(oracle_mod, H):
     ptr = np.concatenate([[0], np.cumsum([len(e) for e in edges])]).astype(np.int64)
     idx = np.array([v for e in edges for v in e], dtype=np.int32)
     _compare(oracle_mod, H, n_nodes, len(edges), ptr, idx, None, 2, "member sort boundaries")
+
+
+LIST_LENGTHS = [1, 2, 7, 8, 9, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1022, 1023, 1024, 1025,
+                2047, 2048, 2049, 4096, 4097, 32768, 32769]
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("n_nodes", [40000, 300000])
+def test_list_lengths(oracle_mod, H, n_nodes, weighted):
+    """Member lists on the edges of the sorts by a thread, a wavefront, a
+    workgroup's registers, a workgroup's LDS and the library, and sizes on both
+    sides of the last bin of the size order, several of each so that ids break
+    ties; two steps, against the oracle.  At 300,000 nodes also the node minima
+    by bucket (over a million incidences)."""
+    rng = np.random.default_rng(n_nodes + weighted)
+    sizes = np.array(LIST_LENGTHS * 2 + [1030, 1030, 1500, 2] * 3 + list(rng.integers(2, 6, size=3000))
+                     + ([300] * 4000 if n_nodes > 100000 else []))
+    sizes = sizes[rng.permutation(len(sizes))]
+    edges = [np.sort(rng.choice(n_nodes, size=s, replace=False)) for s in sizes]
+    ptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    idx = np.concatenate(edges).astype(np.int32)
+    w = rng.choice(np.array([0.5, 1.0, 1.5], dtype=np.float32), size=len(sizes)) if weighted else None
+    levels, maps = oracle_mod.build_hierarchy(n_nodes, len(sizes), ptr, idx, w, 2)
+    lv = H.DeviceLevel.from_host(H.HostLevel(n_nodes, len(sizes), ptr, idx, w), "cuda")
+    print("list lengths", n_nodes, weighted, len(idx), flush=True)
+    dl, dm = H.coarsen_hierarchy_device(lv, 2)
+    for l in range(2):
+        assert np.array_equal(dm[l][0].cpu().numpy(), maps[l].node_rep)
+        assert np.array_equal(dm[l][1].cpu().numpy(), maps[l].edge_rep)
+        got, ref = dl[l + 1].to_host(), levels[l + 1]
+        assert (got.n_nodes, got.n_edges) == (ref.n_nodes, ref.n_edges)
+        assert np.array_equal(got.edge_ptr, ref.eptr) and np.array_equal(got.edge_idx, ref.eidx)
+        if weighted:
+            assert np.array_equal(got.edge_w, ref.w)
+
+
+@pytest.mark.parametrize("n_edges", [1, 3, 4, 5, 63, 64, 65, 257, 40000])
+def test_window_edges(oracle_mod, H, n_edges):
+    """Hyperedge counts around the windows of the incidence walk, with lists
+    that pass a window's 4,096 incidences at a time, and bad input seen
+    wherever in the window it lies."""
+    import torch
+    rng = np.random.default_rng(n_edges)
+    n_nodes = 9000
+    sizes = rng.integers(1, 5, size=n_edges)
+    sizes[n_edges // 2] = 8500
+    edges = [np.sort(rng.choice(n_nodes, size=s, replace=False)) for s in sizes]
+    ptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    idx = np.concatenate(edges).astype(np.int32)
+    levels, maps = oracle_mod.build_hierarchy(n_nodes, n_edges, ptr, idx, None, 1)
+    lv = H.DeviceLevel.from_host(H.HostLevel(n_nodes, n_edges, ptr, idx, None), "cuda")
+    nrep, erep, c = H.coarsen_level_device(lv)
+    assert np.array_equal(nrep.cpu().numpy(), maps[0].node_rep) and np.array_equal(erep.cpu().numpy(), maps[0].edge_rep)
+    assert np.array_equal(c.to_host().edge_idx, levels[1].eidx)
+    long = int(ptr[n_edges // 2])
+    for at, value, name in ((0, -1, "HNV_ERANGE"), (len(idx) - 1, n_nodes, "HNV_ERANGE"),
+                            (long + 4097, int(idx[long + 4096]), "HNV_EUNSORTED"),
+                            (long + 8499, int(idx[long + 8498]), "HNV_EUNSORTED")):
+        bad = torch.as_tensor(idx).cuda()
+        bad[at] = value
+        with pytest.raises(H.HnvError, match=name):
+            H.coarsen_level_device(H.DeviceLevel(n_nodes, n_edges, len(idx), lv.edge_ptr, bad))
