@@ -651,6 +651,43 @@ void forward_geometry(const hnv_plan *p, const LevelPlan &L, int64_t *main_block
     *fin_blocks = fin * p->panels;
 }
 
+ResidentLayout resident_layout(const hnv_plan *p, const LevelPlan &L)
+{
+    ResidentLayout R{};
+    int64_t off = 0;
+    auto take = [&](int64_t bytes) {
+        const int64_t at = off;
+        off += (bytes + 15) & ~int64_t(15);
+        return at;
+    };
+    take(4 * L.n_nodes);
+    R.off_e[0] = take(4 * L.n_edges);
+    R.off_e[1] = p->opts.order == HNV_ORDER_JACOBI ? take(4 * L.n_edges) : R.off_e[0];   // old and new rows
+    R.off_idx[0] = take(2 * (L.nnz + 3 * L.n_edges));   // (a list per row from a multiple of 4)
+    R.off_idx[1] = take(2 * (L.nnz + 3 * L.n_nodes));
+    R.off_wn = take(L.unit_w ? 0 : 4 * (L.nnz + 3 * L.n_nodes));
+    R.off_items = take(8 * L.rows);
+    R.off_mix = take(4 * L.rows);
+    R.off_wide = take(8);
+    R.total = off;
+    return R;
+}
+
+bool resident_sizes(const hnv_plan *p, const LevelPlan &L)
+{
+    return p->panels == 1 && p->g_fwd >= 4 && p->g_fwd <= 16 && L.rows > 0 &&
+           L.nnz + 3 * std::max(L.n_nodes, L.n_edges) <= 65535 && 4 * L.rows <= 65535 &&
+           resident_layout(p, L).total <= kResidentLds;
+}
+
+bool resident_fits(const hnv_plan *p, const LevelPlan &L)
+{
+    int64_t mb = 0, fb = 0;
+    forward_geometry(p, L, &mb, &fb);
+    return fb == 0 && mb <= kResidPer && L.n_long[0] == L.n_chunks[0] && L.n_long[1] == L.n_chunks[1] &&
+           resident_sizes(p, L);
+}
+
 NoallocLayout noalloc_layout(const hnv_plan *p, const LevelPlan &L, bool resid)
 {
     auto align256 = [](int64_t x) { return (x + 255) & ~int64_t(255); };
@@ -702,6 +739,7 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base)
     int64_t max_nodes = 1;
     p->max_slots = 1;
     p->max_resid_blocks = 1;
+    p->resident_words = p->resident_blocks = 1;
     for (int l = 0; l < p->n_levels; ++l) {
         const LevelShape &h = shape[l];
         LevelPlan &L = p->lv[l];
@@ -740,12 +778,19 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base)
         int64_t mb = 0, fb = 0;
         forward_geometry(p, L, &mb, &fb);
         p->max_resid_blocks = std::max(p->max_resid_blocks, mb + fb);
+        if (resident_sizes(p, L)) {
+            p->resident_words = std::max(p->resident_words,
+                                         (kResidentBatch + 1) * L.rows * p->d * (int64_t)elem / 4);
+            p->resident_blocks = std::max(p->resident_blocks, std::min<int64_t>(mb, kResidPer));
+        }
     }
     p->zbuf = c.take<char>(p->lv[0].rows * p->d * (int64_t)elem);
     p->partials = c.take<float>(p->max_slots * p->pstride);
     p->resid_part = c.take<double>(kResidBatch * p->max_resid_blocks);
     p->resid_stage_len = blocks_for(p->max_resid_blocks, kBlock * 8) + 1;
     p->resid_stage = c.take<double>(2 * kResidBatch * p->resid_stage_len);
+    p->resident_trace = c.take<uint32_t>(p->resident_words);
+    p->resident_part = c.take<double>(kResidentBatch * p->resident_blocks);
     p->cscratch = c.take<float>(max_nodes);
     p->resid_tmp = c.take<double>(1);
     p->ctl = c.take<SweepCtl>(1);

@@ -79,6 +79,9 @@ struct SweepCtl {
     int32_t *done;        // [n_levels] sweeps run per level
     double tol;
     int64_t n_res;        // sweeps run so far (next index into res)
+    const void *redo_src; // a launch of several sweeps ran past the level's last one: the next launch
+    void *redo_dst;       //   repeats its first `redo` sweeps (0: none)
+    int32_t redo;
 };
 
 struct LevelPlan {
@@ -108,6 +111,10 @@ namespace hnv {
 constexpr int kResidBatch = 8;
 // Per-block residual partials one workgroup of a residual stage sums.
 constexpr int kResidPer = kBlock * 8;
+// Sweeps of a small level that one launch runs from LDS when residuals are
+// wanted, and the LDS bytes that it takes.
+constexpr int kResidentBatch = 2 * kResidBatch;
+constexpr int64_t kResidentLds = 160 * 1024;
 }  // namespace hnv
 
 struct hnv_plan {
@@ -124,6 +131,10 @@ struct hnv_plan {
     int64_t max_resid_blocks = 0;
     double *resid_stage = nullptr;   // [2 x kResidBatch x resid_stage_len] partial sums of the residual stages
     int64_t resid_stage_len = 0;
+    uint32_t *resident_trace = nullptr;  // [resident_words] rows before and after sweeps run from LDS
+    int64_t resident_words = 0;
+    double *resident_part = nullptr;     // [kResidentBatch x resident_blocks] their per-block partials
+    int64_t resident_blocks = 0;
     float *cscratch = nullptr;       // [max n_nodes] per-node scalar of the reverse sweep
     double *resid_tmp = nullptr;     // [1]
     hnv::SweepCtl *ctl = nullptr;    // [1] early-stop control (device)
@@ -192,6 +203,21 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base);
 
 // Forward-sweep launch geometry of a level (blocks per panel and finalize blocks).
 void forward_geometry(const hnv_plan *p, const LevelPlan &L, int64_t *main_blocks, int64_t *fin_blocks);
+
+// Where a level's arrays lie in the LDS of a launch that runs many of its
+// sweeps (bytes past the node rows), and whether the level allows such a launch:
+// by its sizes, one column panel of 4 to 16 lanes per row (so that a long
+// item's lanes are one wavefront and a row's serial chain is no longer than a
+// lane group's), its LDS bytes and its 16-bit offsets; and, once its work lists
+// are known, no split rows, a workgroup for every wavefront-tier item (as
+// levels of this size have it unless settle_long_items undid it), and residual
+// partials that one workgroup adds.
+struct ResidentLayout {
+    int64_t off_e[2], off_idx[2], off_wn, off_items, off_mix, off_wide, total;
+};
+ResidentLayout resident_layout(const hnv_plan *p, const LevelPlan &L);
+bool resident_sizes(const hnv_plan *p, const LevelPlan &L);
+bool resident_fits(const hnv_plan *p, const LevelPlan &L);
 
 // A level's sweep scratch in the static array of hnv_sweep_noalloc: residual
 // partials and stages (only with a residual), then the split-row slots.

@@ -488,7 +488,7 @@ HNV_DEV double epilogue_fwd(const GatherArgs &a, void *dst, int zrow, int deg, i
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
             const double dd = (double)o[i] - (double)z[i];
-            r2 += dd * dd;
+            r2 = fma(dd, dd, r2);
         }
     }
     return r2;
@@ -593,10 +593,10 @@ HNV_DEV void epilogue_adj_edge(const GatherArgs &a, int row, int deg, int col, b
 // block-level residual reduction (FP64, fixed order)
 // ---------------------------------------------------------------------------
 
-HNV_DEV void block_resid(const GatherArgs &a, double r2, int64_t lb)
+// Thread 0's sum over the block: each wavefront's by a butterfly, then the
+// wavefronts' in order.
+HNV_DEV double block_wave_sums(double r2)
 {
-    if (!a.resid)
-        return;
     __shared__ double wsum[kWavesPerBlock];
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1)
@@ -605,12 +605,20 @@ HNV_DEV void block_resid(const GatherArgs &a, double r2, int64_t lb)
     if ((threadIdx.x % kWave) == 0)
         wsum[wave] = r2;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
+    double s = 0.0;
+    if (threadIdx.x == 0)
         for (int i = 0; i < kWavesPerBlock; ++i)
             s += wsum[i];
+    return s;
+}
+
+HNV_DEV void block_resid(const GatherArgs &a, double r2, int64_t lb)
+{
+    if (!a.resid)
+        return;
+    const double s = block_wave_sums(r2);
+    if (threadIdx.x == 0)
         a.resid[a.resid_offset + lb] = s;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -935,8 +943,15 @@ __global__ __launch_bounds__(kBlock) void k_ctl_init(SweepCtl *ctl, int32_t *fla
         ctl->done = flags + n_levels;
         ctl->tol = tol;
         ctl->n_res = 0;
+        ctl->redo = 0;
     }
 }
+
+}  // namespace hnv
+
+#include "hnv_resident.h"
+
+namespace hnv {
 
 // After a projection (which always runs): its output is the latest iterate.
 __global__ void k_ctl_advance(SweepCtl *ctl)
@@ -1750,6 +1765,110 @@ static hnv_status run_sweep(hnv_plan *p, int level, const void *src, void *dst, 
     return HNV_OK;
 }
 
+// Whether `sweeps` sweeps of a level in a refinement run from LDS: the level
+// fits, and there is more than one sweep: the loads alone take longer than one
+// launch of k_gather; two sweeps take 18 us a call against 21, ten 30 against 47
+// (2,000 nodes / 1,000 hyperedges, FP32, d = 32).  A plan that is being profiled
+// times each sweep's own launches, so it takes the general path.
+static bool use_resident(const hnv_plan *p, const LevelPlan &L, int sweeps)
+{
+    return sweeps >= 2 && !p->profiling && resident_fits(p, L);
+}
+
+template <typename T, int EPL, int G>
+static void launch_resident(const ResidentArgs &a, int dp, double *part, int64_t part_stride,
+                            const ResidentSegments &sg, hipStream_t s)
+{
+    const int words = (int)(a.ld / Word<T>::N);
+    k_resident<T, G><<<words, kResidentThreads, 0, s>>>(a);
+    if (!a.trace)
+        return;
+    const dim3 grid((unsigned)(sg.blocks[0] + sg.blocks[1] + sg.blocks[2] + sg.blocks[3]), (unsigned)a.sweeps);
+    k_resident_blocks<T, EPL, G><<<grid, kBlock, 0, s>>>(a.trace, a.n_nodes + a.n_edges, words, dp, sg, part,
+                                                         part_stride, a.ctl, a.ctl_level);
+}
+
+// n sweeps of `level` in one launch (src -> dst, or the control block's
+// matrices), fused: the first reads the coarser level.  With resid_out (n <=
+// kResidentBatch) also their residuals, to resid_out[0 .. n).  `redo` (early
+// stop): the launch that repeats the sweeps up to the level's last one.
+static hnv_status run_resident(hnv_plan *p, int level, const void *src, void *dst, float omega, bool fused, int n,
+                               double *resid_out, hipStream_t s, SweepCtl *ctl = nullptr, bool redo = false)
+{
+    const LevelPlan &L = p->lv[level];
+    const ResidentLayout R = resident_layout(p, L);
+    const bool edge_first = p->opts.order == HNV_ORDER_EDGE_FIRST;
+    ResidentArgs a{};
+    a.side[0] = L.side[0];
+    a.side[1] = L.side[1];
+    if (L.unit_w)
+        a.side[1].wn = nullptr;
+    a.side[0].wn = nullptr;
+    a.n_nodes = (int32_t)L.n_nodes;
+    a.n_edges = (int32_t)L.n_edges;
+    a.sweeps = n;
+    a.edge_first = edge_first;
+    a.fused = fused;
+    for (int k = 0; k < 2; ++k) {
+        a.off_e[k] = (int32_t)R.off_e[k];
+        a.off_idx[k] = (int32_t)R.off_idx[k];
+    }
+    a.off_wn = (int32_t)R.off_wn;
+    a.off_items = (int32_t)R.off_items;
+    a.off_mix = (int32_t)R.off_mix;
+    a.off_wide = (int32_t)R.off_wide;
+    a.ld = p->d;
+    a.omega = omega;
+    a.r = L.r;
+    a.rowmap = L.rowmap;
+    a.src = src;
+    a.dst = dst;
+    a.trace = resid_out ? p->resident_trace : nullptr;
+    a.ctl = ctl;
+    a.ctl_level = level;
+    a.redo = redo;
+    // the general sweep's blocks: Jacobi both wavefront tiers, then both
+    // lane-group tiers; edge-first all of side 0, then all of side 1
+    ResidentSegments sg{};
+    for (int k = 0; k < 2; ++k) {
+        const int c = edge_first ? 2 * k : k, m = edge_first ? 2 * k + 1 : 2 + k;
+        const int32_t first = k == 0 ? 0 : (int32_t)L.n_edges;
+        sg.blocks[c] = L.n_chunks[k];
+        sg.items[c] = L.n_chunks[k];
+        sg.first[c] = first;
+        sg.blocks[m] = (int32_t)blocks_for(L.n_small[k], kBlock / p->g_fwd);
+        sg.items[m] = L.n_small[k];
+        sg.first[m] = first + L.n_chunks[k];
+        sg.small[m] = 1;
+    }
+    int64_t mb = 0, fb = 0;
+    forward_geometry(p, L, &mb, &fb);
+    if (resid_out && (n > kResidentBatch || mb > p->resident_blocks ||
+                      (n + 1) * L.rows * (p->dtype == HNV_BF16 ? p->d / 2 : p->d) > p->resident_words))
+        return fail(HNV_EDEVICE, "residual scratch of sweeps from LDS exceeds its bound");
+#define HNV_RES(TT, EE, GG) launch_resident<TT, EE, GG>(a, p->dp, p->resident_part, mb, sg, s)
+    if (p->dtype == HNV_BF16) {
+        switch (p->g_fwd) {
+        case 4: HNV_RES(bf16_t, 8, 4); break;
+        case 8: HNV_RES(bf16_t, 8, 8); break;
+        default: HNV_RES(bf16_t, 8, 16); break;
+        }
+    } else if (p->epl_fwd == 8) {
+        HNV_RES(float, 8, 16);
+    } else {
+        switch (p->g_fwd) {
+        case 4: HNV_RES(float, 4, 4); break;
+        case 8: HNV_RES(float, 4, 8); break;
+        default: HNV_RES(float, 4, 16); break;
+        }
+    }
+#undef HNV_RES
+    hnv_status st = dev_check("sweeps from LDS");
+    if (st != HNV_OK || !a.trace)
+        return st;
+    return reduce_resid(p->resident_part, mb, n, mb, resid_out, plan_scratch(p), nullptr, level, s);
+}
+
 // The projection onto `level` (zc -> zf); with ctl (an early-stop
 // refinement) the matrices come from the control block, which then takes
 // the projection's output as the latest iterate.
@@ -1969,7 +2088,14 @@ extern "C" hnv_status hnv_project(hnv_plan *plan, int level, const void *z_coars
 // that would do nothing: O(log K) waits per level instead of one per sweep.
 // While the stream is being captured into a graph every sweep is enqueued
 // and nothing waits for the host.
+// Sweeps that run from LDS (k_resident) come up to kResidentBatch to a launch;
+// the launch goes on past the level's last sweep, which its residuals then
+// show, and a second one repeats the sweeps up to it: a sweep too many costs
+// about 1 us there, a wait for the host ten, so the first launch has
+// kResidentFirst.
 constexpr int kMaxStopBatch = 16;
+constexpr int kResidentFirst = 8;
+static_assert(kResidentBatch <= 2 * kResidBatch, "an early stop's residuals wait in the stage sums' scratch");
 
 static hnv_status refine_early_stop(hnv_plan *plan, const void *z_coarsest, void *z_finest,
                                     const int32_t *sweeps_per_level, float omega, double tol,
@@ -1989,9 +2115,20 @@ static hnv_status refine_early_stop(hnv_plan *plan, const void *z_coarsest, void
         const int K = sweeps_per_level[l];
         if (K == 0 && l < Lc)
             st = run_project(plan, l, nullptr, nullptr, s, plan->ctl);
-        int k = 0, batch = 1;
+        const bool resident = use_resident(plan, plan->lv[l], K);
+        int k = 0, batch = resident ? kResidentFirst : 1;
         while (k < K && st == HNV_OK) {
-            for (const int end = std::min(K, k + batch); k < end && st == HNV_OK; ++k)
+            if (resident) {   // a launch of up to kResidentBatch sweeps, and the repeat if it ran past the last one
+                const int n = std::min({batch, kResidentBatch, K - k});
+                const bool fused = k == 0 && l < Lc;
+                st = run_resident(plan, l, nullptr, nullptr, omega, fused, n, plan->resid_stage, s, plan->ctl);
+                if (st == HNV_OK) {
+                    k_resident_decide<<<1, 1, 0, s>>>(plan->ctl, l, n, plan->resid_stage);
+                    if (n > 1)
+                        st = run_resident(plan, l, nullptr, nullptr, omega, fused, n, nullptr, s, plan->ctl, true);
+                }
+                k += n;
+            } else for (const int end = std::min(K, k + batch); k < end && st == HNV_OK; ++k)
                 st = run_sweep(plan, l, nullptr, nullptr, omega, k == 0 && l < Lc, nullptr, s, plan->ctl);
             if (st != HNV_OK || k >= K)
                 break;
@@ -2029,6 +2166,8 @@ static hnv_status refine_early_stop(hnv_plan *plan, const void *z_coarsest, void
     return HNV_OK;
 }
 
+constexpr int kResidentMost = 256;   // sweeps per launch without residuals (a launch stays below a millisecond)
+
 extern "C" hnv_status hnv_refine(hnv_plan *plan, const void *z_coarsest, void *z_finest,
                                  const int32_t *sweeps_per_level, float omega, double tol, double *residuals_dev,
                                  int32_t *sweeps_done, void *stream)
@@ -2052,9 +2191,13 @@ extern "C" hnv_status hnv_refine(hnv_plan *plan, const void *z_coarsest, void *z
     // Operations in order: per level (coarsest first) the sweeps, or a bare
     // projection when a finer level has no sweeps.  Writes alternate between
     // z_finest and the scratch buffer.
+    // A level whose sweeps run from LDS has an operation per launch of sweeps.
     int64_t n_ops = 0;
-    for (int l = Lc; l >= 0; --l)
-        n_ops += (sweeps_per_level[l] > 0) ? sweeps_per_level[l] : (l < Lc ? 1 : 0);
+    const int per_launch = residuals_dev ? kResidentBatch : kResidentMost;
+    for (int l = Lc; l >= 0; --l) {
+        const int K = sweeps_per_level[l];
+        n_ops += use_resident(plan, plan->lv[l], K) ? blocks_for(K, per_launch) : (K > 0) ? K : (l < Lc ? 1 : 0);
+    }
     if (n_ops == 0) {
         hipError_t e = hipMemcpyAsync(z_finest, z_coarsest, plan->lv[0].rows * plan->d * eb,
                                       hipMemcpyDeviceToDevice, s);
@@ -2082,6 +2225,20 @@ extern "C" hnv_status hnv_refine(hnv_plan *plan, const void *z_coarsest, void *z
             if ((st = run_project(plan, l, cur, out, s)) != HNV_OK)
                 return st;
             cur = out;
+        }
+        if (use_resident(plan, plan->lv[l], K)) {
+            for (int k = 0; k < K; k += per_launch) {
+                const int n = std::min(per_launch, K - k);
+                void *out = target(op++);
+                if ((st = run_resident(plan, l, cur, out, omega, k == 0 && l < Lc, n,
+                                       residuals_dev ? residuals_dev + resid_k : nullptr, s)) != HNV_OK)
+                    return st;
+                resid_k += n;
+                cur = out;
+            }
+            if (sweeps_done)
+                sweeps_done[l] = K;
+            continue;
         }
         // the level's residuals reduced kResidBatch sweeps at a time
         int64_t mb = 0, fb = 0;
