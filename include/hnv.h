@@ -354,6 +354,14 @@ hnv_status hnv_project(hnv_plan *plan, int level, const void *z_coarse, void *z_
 hnv_status hnv_sweep(hnv_plan *plan, int level, const void *z_in, void *z_out, float omega,
                      int from_coarse, double *resid_dev, void *stream);
 
+/* n sweeps at `level` in a row, the first as hnv_sweep(z_in, from_coarse), each
+ * further one on the one before.  z_out: HOST array of n device matrices; sweep
+ * i's result goes to z_out[i], or is not kept where that is NULL (the last one
+ * is).  No entry may alias z_in or another one.  The same results as n calls of
+ * hnv_sweep; sweeps that aren't kept use the plan's scratch embedding. */
+hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, void *const *z_out, int n, float omega,
+                      int from_coarse, void *stream);
+
 /* Reverse mode of one sweep at `level` (from_coarse = 0), in the plan's
  * sweep order.  With y = z_prev (the sweep's input), z = z_cur (its output)
  * and g_in = dL/dz, writes g_out = dL/dy.  Jacobi order:
@@ -393,6 +401,16 @@ hnv_status hnv_sweep_adjoint(hnv_plan *plan, int level, const void *g_in, void *
 hnv_status hnv_sweep_adjoint_split(hnv_plan *plan, int level, const void *g_in, void *g_out,
                                    const void *z_prev, const void *z_cur, float *dw_accum, float *node_accum,
                                    float omega, void *stream);
+/* Several reverse sweeps in a row: sweep j (0 .. n - 1) reads the cotangent
+ * g_in (j = 0) or g_out[j - 1] and writes g_out[j], going back over the forward
+ * sweep from states[n - 1 - j] to states[n - j].  states and g_out are HOST
+ * arrays of n + 1 and n device matrices; an entry of g_out may appear again two
+ * places later.  With dw_accum and node_accum the weight gradient is split as
+ * hnv_sweep_adjoint_split has it, with neither none is formed (one without the
+ * other is an error).  The same results as n calls. */
+hnv_status hnv_sweeps_adjoint(hnv_plan *plan, int level, const void *g_in, void *const *g_out,
+                              const void *const *states, int n, float *dw_accum, float *node_accum, float omega,
+                              void *stream);
 hnv_status hnv_weight_grad_finish(hnv_plan *plan, int level, const float *node_accum, float *dw_accum,
                                   void *stream);
 

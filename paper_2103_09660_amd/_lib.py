@@ -27,6 +27,7 @@ i32p = ctypes.POINTER(ctypes.c_int32)
 f32p = ctypes.POINTER(ctypes.c_float)
 f64p = ctypes.POINTER(ctypes.c_double)
 vp = ctypes.c_void_p
+vpp = ctypes.POINTER(ctypes.c_void_p)
 
 
 class HnvLevel(ctypes.Structure):
@@ -91,6 +92,8 @@ _SIGS = {
     "hnv_project": (ctypes.c_int, [vp, ctypes.c_int, vp, vp, vp]),
     "hnv_sweep": (ctypes.c_int, [vp, ctypes.c_int, vp, vp, ctypes.c_float, ctypes.c_int, vp, vp]),
     "hnv_sweep_noalloc": (ctypes.c_int, [vp, ctypes.c_int, vp, vp, ctypes.c_float, ctypes.c_int, vp, vp]),
+    "hnv_sweeps": (ctypes.c_int, [vp, ctypes.c_int, vp, vpp, ctypes.c_int, ctypes.c_float, ctypes.c_int, vp]),
+    "hnv_sweeps_adjoint": (ctypes.c_int, [vp, ctypes.c_int, vp, vpp, vpp, ctypes.c_int, vp, vp, ctypes.c_float, vp]),
     "hnv_sweep_adjoint": (ctypes.c_int, [vp, ctypes.c_int, vp, vp, vp, vp, vp, ctypes.c_float, vp]),
     "hnv_sweep_adjoint_split": (ctypes.c_int, [vp, ctypes.c_int, vp, vp, vp, vp, vp, vp, ctypes.c_float, vp]),
     "hnv_weight_grad_finish": (ctypes.c_int, [vp, ctypes.c_int, vp, vp, vp]),

@@ -563,6 +563,20 @@ class Plan:
                _ptr(resid), _stream(self.device))
         return z_out
 
+    def sweeps(self, level: int, z_in, keep: Sequence[bool], omega: float = 0.5, from_coarse: bool = False):
+        """``len(keep)`` sweeps in a row; returns the results of those with
+        ``keep`` set (the last one must be), in order."""
+        self._check(z_in, level + 1 if from_coarse else level, "z_in")
+        if not keep or not keep[-1]:
+            raise ValueError("keep: at least one sweep, and the last one kept")
+        shape = (self.rows(level), self.d)
+        kept = [_torch().empty(shape, dtype=self.torch_dtype, device=self.device) for k in keep if k]
+        at = iter(kept)
+        outs = (ctypes.c_void_p * len(keep))(*(next(at).data_ptr() if k else None for k in keep))
+        L.call("hnv_sweeps", self._h, level, z_in.data_ptr(), outs, len(keep), float(omega), 1 if from_coarse else 0,
+               _stream(self.device))
+        return kept
+
     def sweep_noalloc(self, level: int, z_in, omega: float = 0.5, from_coarse: bool = False, out=None, resid=None):
         """The same sweep through hnv_sweep_noalloc (scratch in the library's
         static device array, no allocation by the call itself; ``out`` should
@@ -605,6 +619,25 @@ class Plan:
             L.call("hnv_sweep_adjoint_split", self._h, level, g_in.data_ptr(), g_out.data_ptr(), z_prev.data_ptr(),
                    z_cur.data_ptr(), _ptr(dw), _ptr(node_acc), float(omega), _stream(self.device))
         return g_out
+
+    def sweeps_adjoint(self, level: int, g_in, states, omega: float = 0.5, dw=None, node_acc=None):
+        """Reverse mode of the sweeps states[0] -> states[1] -> .. in a row:
+        the cotangent of states[0] from that of the last one.  ``dw`` and
+        ``node_acc`` (both or neither) as in :meth:`sweep_adjoint`."""
+        self._check(g_in, level, "g_in")
+        for t in states:
+            self._check(t, level, "states")
+        if (dw is None) != (node_acc is None):
+            raise ValueError("dw and node_acc go together")
+        self._check_edge_vec(level, dw, "dw")
+        _check_vec(node_acc, self.level_info(level)[0], _torch().float32, "node_acc")
+        n = len(states) - 1
+        out = [_torch().empty_like(g_in) for _ in range(min(n, 2))]
+        g_out = (ctypes.c_void_p * n)(*(out[j % 2].data_ptr() for j in range(n)))
+        zs = (ctypes.c_void_p * (n + 1))(*(t.data_ptr() for t in states))
+        L.call("hnv_sweeps_adjoint", self._h, level, g_in.data_ptr(), g_out, zs, n, _ptr(dw), _ptr(node_acc),
+               float(omega), _stream(self.device))
+        return out[(n - 1) % 2]
 
     def weight_grad_finish(self, level: int, node_acc, dw):
         """dw[e] -= sum of node_acc over the members of e (completes a split weight gradient)."""
@@ -777,13 +810,12 @@ def _refine_function():
             ck = max(1, int(ckpt_every))
             K = int(sweeps)
             saved = {0: z_start.detach()}
-            cur = z_start.detach()
-            for i in range(1, K + 1):
-                nxt = plan.sweep(level, cur, omega, from_coarse=(from_coarse and i == 1))
-                if i % ck == 0 or i == K:
-                    saved[i] = nxt
-                cur = nxt
-            if K == 0:
+            if K > 0:
+                keep = [i % ck == 0 or i == K for i in range(1, K + 1)]
+                kept = plan.sweeps(level, saved[0], keep, omega, from_coarse=from_coarse)
+                saved.update(zip([i for i in range(1, K + 1) if keep[i - 1]], kept))
+                cur = kept[-1]
+            else:
                 cur = plan.project(level, z_start.detach()) if from_coarse else z_start.detach().clone()
             ctx.plan, ctx.level, ctx.K, ctx.omega, ctx.from_coarse, ctx.ck = plan, level, K, omega, from_coarse, ck
             ctx.ckpt_keys = sorted(saved)
@@ -811,17 +843,12 @@ def _refine_function():
             bounds = ctx.ckpt_keys
             for si in range(len(bounds) - 1, 0, -1):
                 s0, s1 = bounds[si - 1], bounds[si]
-                states = {}
                 start = ckpts[s0]
-                if ctx.from_coarse and s0 == 0:
-                    states[0] = plan.project(level, start)
-                else:
-                    states[s0] = start
-                for i in range(s0 + 1, s1):
-                    states[i] = plan.sweep(level, states[i - 1], omega)
-                states[s1] = ckpts[s1]
-                for i in range(s1, s0, -1):
-                    g = plan.sweep_adjoint(level, g, states[i - 1], states[i], omega, dw=dw, node_acc=nacc)
+                states = [plan.project(level, start) if ctx.from_coarse and s0 == 0 else start]
+                if s1 - s0 > 1:
+                    states += plan.sweeps(level, states[0], [True] * (s1 - s0 - 1), omega)
+                states.append(ckpts[s1])
+                g = plan.sweeps_adjoint(level, g, states, omega, dw=dw, node_acc=nacc)
             if K == 0 and not ctx.from_coarse:
                 gz = g
             elif ctx.from_coarse:

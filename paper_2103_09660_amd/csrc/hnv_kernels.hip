@@ -1765,7 +1765,10 @@ static hnv_status run_sweep(hnv_plan *p, int level, const void *src, void *dst, 
     return HNV_OK;
 }
 
-// Whether `sweeps` sweeps of a level in a refinement run from LDS: the level
+// Sweeps per launch from LDS without residuals (a launch stays below a millisecond).
+constexpr int kResidentMost = 256;
+
+// Whether `sweeps` sweeps of a level in a row run from LDS: the level
 // fits, and there is more than one sweep: the loads alone take longer than one
 // launch of k_gather; two sweeps take 18 us a call against 21, ten 30 against 47
 // (2,000 nodes / 1,000 hyperedges, FP32, d = 32).  A plan that is being profiled
@@ -1992,6 +1995,61 @@ extern "C" hnv_status hnv_sweep(hnv_plan *plan, int level, const void *z_in, voi
                      reinterpret_cast<hipStream_t>(stream));
 }
 
+// The sweeps between two kept states in one call: a call per sweep from a
+// scripting language takes about 9 us, more than a sweep of a small level (a
+// training step of 10 sweeps at each of five levels, 20K nodes / 8K hyperedges,
+// d = 64, with hnv_sweeps_adjoint: 2,840 -> 1,723 us, of which the kernels are
+// 1,600).  Results that aren't kept go to the plan's scratch embedding and the
+// next kept result in turn.
+extern "C" hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, void *const *z_out, int n,
+                                 float omega, int from_coarse, void *stream)
+{
+    clear_error();
+    hnv_status st = check_level(plan, level);
+    if (st != HNV_OK)
+        return st;
+    if (!z_in || !z_out || n < 1 || !z_out[n - 1])
+        return fail(HNV_EINVAL, "z_in / z_out / the last result is NULL, or no sweeps");
+    if (!aligned16(z_in))
+        return fail(HNV_EINVAL, "z_in must be 16-byte aligned");
+    const void *last = z_in;
+    for (int i = 0; i < n; ++i) {
+        if (!z_out[i])
+            continue;
+        if (!aligned16(z_out[i]))
+            return fail(HNV_EINVAL, "z_out must be 16-byte aligned");
+        if (z_out[i] == z_in || z_out[i] == last || z_out[i] == plan->zbuf)
+            return fail(HNV_EINVAL, "an entry of z_out aliases z_in or another one");
+        last = z_out[i];
+    }
+    if (!(omega >= 0.0f && omega <= 1.0f))
+        return fail(HNV_EINVAL, "omega must be in [0, 1]");
+    if (from_coarse && !plan->lv[level].has_coarse)
+        return fail(HNV_EINVAL, "from_coarse at the coarsest level");
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    const void *cur = z_in;
+    for (int i = 0; i < n; ) {
+        int end = i;   // the run of sweeps up to the next kept result
+        while (!z_out[end])
+            ++end;
+        if (use_resident(plan, plan->lv[level], end + 1 - i) && end + 1 - i <= kResidentMost) {
+            if ((st = run_resident(plan, level, cur, z_out[end], omega, from_coarse && i == 0, end + 1 - i, nullptr,
+                                   s)) != HNV_OK)
+                return st;
+            cur = z_out[end];
+        } else {
+            for (int k = i; k <= end; ++k) {   // (alternating, so that the last one writes z_out[end])
+                void *out = (end - k) % 2 == 0 ? z_out[end] : plan->zbuf;
+                if ((st = run_sweep(plan, level, cur, out, omega, from_coarse && k == 0, nullptr, s)) != HNV_OK)
+                    return st;
+                cur = out;
+            }
+        }
+        i = end + 1;
+    }
+    return HNV_OK;
+}
+
 // ---------------------------------------------------------------------------
 // the forward sweep for callers that cannot allocate: its scratch lives in a
 // static device array instead of the plan's workspace
@@ -2165,8 +2223,6 @@ static hnv_status refine_early_stop(hnv_plan *plan, const void *z_coarsest, void
     }
     return HNV_OK;
 }
-
-constexpr int kResidentMost = 256;   // sweeps per launch without residuals (a launch stays below a millisecond)
 
 extern "C" hnv_status hnv_refine(hnv_plan *plan, const void *z_coarsest, void *z_finest,
                                  const int32_t *sweeps_per_level, float omega, double tol, double *residuals_dev,
@@ -2378,6 +2434,32 @@ extern "C" hnv_status hnv_sweep_adjoint_split(hnv_plan *plan, int level, const v
         return fail(HNV_EINVAL, "dw_accum / node_accum is NULL");
     return run_adjoint(plan, level, g_in, g_out, z_prev, z_cur, dw_accum, node_accum, omega, 2,
                        reinterpret_cast<hipStream_t>(stream));
+}
+
+extern "C" hnv_status hnv_sweeps_adjoint(hnv_plan *plan, int level, const void *g_in, void *const *g_out,
+                                         const void *const *states, int n, float *dw_accum, float *node_accum,
+                                         float omega, void *stream)
+{
+    clear_error();
+    hnv_status st = check_level(plan, level);
+    if (st != HNV_OK)
+        return st;
+    if (!g_out || !states || n < 1)
+        return fail(HNV_EINVAL, "g_out / states is NULL, or no sweeps");
+    const LevelPlan &L = plan->lv[level];
+    const bool wgrad = dw_accum || node_accum;
+    if (wgrad && ((!dw_accum && L.n_edges > 0) || (!node_accum && L.n_nodes > 0)))
+        return fail(HNV_EINVAL, "dw_accum / node_accum is NULL");
+    for (int j = 0; j < n; ++j)
+        if ((st = check_adjoint_args(plan, level, j == 0 ? g_in : g_out[j - 1], g_out[j], states[n - 1 - j],
+                                     states[n - j], omega)) != HNV_OK)
+            return st;
+    for (int j = 0; j < n; ++j)
+        if ((st = run_adjoint(plan, level, j == 0 ? g_in : g_out[j - 1], g_out[j], states[n - 1 - j], states[n - j],
+                              dw_accum, node_accum, omega, wgrad ? 2 : 0, reinterpret_cast<hipStream_t>(stream))) !=
+            HNV_OK)
+            return st;
+    return HNV_OK;
 }
 
 extern "C" hnv_status hnv_weight_grad_finish(hnv_plan *plan, int level, const float *node_accum, float *dw_accum,
