@@ -45,6 +45,11 @@ __global__ __launch_bounds__(kThreads) void k_check_node_map(const int32_t *__re
         atomicOr(flag, 1 << 4);
 }
 
+// Members of a removed hyperedge that its own thread follows; the wavefront
+// follows longer lists together (a thread per list whatever its length took 26
+// us where this takes 6, levels of 0.3M to 0.7M nodes).
+constexpr int kMapThread = 16;
+
 // Runs after the level's own checks in the same stream and does nothing
 // when they found bad offsets or member ids (level_flag bits 0 and 1), so
 // every member it follows is in range.
@@ -57,20 +62,34 @@ __global__ __launch_bounds__(kThreads) void k_check_edge_map(const int32_t *__re
                                                              int *__restrict__ flag)
 {
     const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= n_edges || (*level_flag & 3))
+    if (*level_flag & 3)
         return;
-    const int32_t r = edge_rep[e];
+    const int32_t r = e < n_edges ? edge_rep[e] : 0;
     int bad = 0;
-    if (r < -1 || r >= n_edges_c) {
+    int32_t a = 0, b = 0, first = 0;   // a removed hyperedge's members, and its coarse node
+    if (e < n_edges && (r < -1 || r >= n_edges_c)) {
         bad = 1 << 5;
     } else if (r == -1) {
-        const int32_t a = ptr[e], b = ptr[e + 1];
-        if (b == a) {
+        a = ptr[e];
+        b = ptr[e + 1];
+        if (b == a)
             bad = 1 << 6;
-        } else if (full) {
-            const int32_t first = node_rep[idx[a]];
+        else
+            first = node_rep[idx[a]];
+    }
+    if (full) {
+        const bool is_long = b - a > kMapThread;
+        if (!is_long)
             for (int32_t j = a + 1; j < b; ++j)
                 if (node_rep[idx[j]] != first)
+                    bad = 1 << 7;
+        uint64_t todo = __ballot(is_long);
+        while (todo) {   // uniform over the wavefront
+            const int of = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const int32_t lo = __shfl(a, of, kWave), hi = __shfl(b, of, kWave), rep = __shfl(first, of, kWave);
+            for (int32_t j = lo + 1 + (int)(threadIdx.x % kWave); j < hi; j += kWave)
+                if (node_rep[idx[j]] != rep)
                     bad = 1 << 7;
         }
     }
@@ -117,31 +136,19 @@ __global__ __launch_bounds__(kThreads) void k_offsets_sorted(const uint32_t *__r
         ptr[v] = (int32_t)j;
 }
 
-__global__ __launch_bounds__(kThreads) void k_iota(int64_t n, int32_t *__restrict__ out)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n)
-        out[i] = (int32_t)i;
-}
-
-__global__ __launch_bounds__(kThreads) void k_fill_f32(float *__restrict__ p, int64_t n, float v)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n)
-        p[i] = v;
-}
-
 // projection row map: node v -> rep(v); kept hyperedge -> n_nodes_c + rep(e);
-// removed hyperedge -> the coarse node its members were merged into
+// removed hyperedge -> the coarse node its members were merged into; and the
+// rows 0, 1, 2, .., the values of the inverse map's sort
 __global__ __launch_bounds__(kThreads) void k_rowmap(const int32_t *__restrict__ ptr, const int32_t *__restrict__ idx,
                                                      const int32_t *__restrict__ node_rep,
                                                      const int32_t *__restrict__ edge_rep, int64_t n_nodes,
                                                      int64_t n_edges, int64_t n_nodes_c, const int *__restrict__ bad,
-                                                     int32_t *__restrict__ rowmap)
+                                                     int32_t *__restrict__ rowmap, int32_t *__restrict__ row_ids)
 {
     const int64_t u = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (u >= n_nodes + n_edges)
         return;
+    row_ids[u] = (int32_t)u;
     if (level_failed(bad)) {
         rowmap[u] = 0;
         return;
@@ -155,15 +162,23 @@ __global__ __launch_bounds__(kThreads) void k_rowmap(const int32_t *__restrict__
     rowmap[u] = (r >= 0) ? (int32_t)(n_nodes_c + r) : node_rep[idx[ptr[e]]];
 }
 
-// Side 0's neighbour arrays: the member lists as given, and with a coarser
-// level each member's coarse row (a node's row maps to rep(v), so
-// cidx = node_rep[idx]; 0 when the level failed its checks).
-__global__ __launch_bounds__(kThreads) void k_side0_idx(const int32_t *__restrict__ edge_idx,
-                                                        const int32_t *__restrict__ node_rep, int64_t nnz,
-                                                        const int *__restrict__ bad, int32_t *__restrict__ idx,
-                                                        int32_t *__restrict__ cidx)
+// Side 0's arrays: the offsets and the member lists as given, the weights (1
+// without any), and with a coarser level each member's coarse row (a node's row
+// maps to rep(v), so cidx = node_rep[idx]; 0 when the level failed its checks).
+// One launch: at 20K nodes each costs more than the arrays it copies.
+__global__ __launch_bounds__(kThreads) void k_side0(const int32_t *__restrict__ edge_ptr,
+                                                    const int32_t *__restrict__ edge_idx,
+                                                    const float *__restrict__ edge_w,
+                                                    const int32_t *__restrict__ node_rep, int64_t n_edges,
+                                                    int64_t nnz, const int *__restrict__ bad,
+                                                    int32_t *__restrict__ ptr, int32_t *__restrict__ idx,
+                                                    int32_t *__restrict__ cidx, float *__restrict__ w)
 {
     const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (j <= n_edges)
+        ptr[j] = edge_ptr[j];
+    if (j < n_edges)
+        w[j] = edge_w ? edge_w[j] : 1.0f;
     if (j >= nnz)
         return;
     const int32_t v = edge_idx[j];
@@ -814,14 +829,10 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
     // projection row map (first: the composed indices below read it)
     if (C)
         k_rowmap<<<grid_for(nV + nE), kThreads, 0, s>>>(lv.edge_ptr, lv.edge_idx, m->node_rep, m->edge_rep, nV, nE,
-                                                        C->n_nodes, bad, L.rowmap);
-    // side 0: the member lists as given, and their coarse rows
-    if ((st = copy_d2d((void *)S0.ptr, lv.edge_ptr, 4 * (nE + 1), s)) != HNV_OK)
-        return st;
-    if (nnz > 0)
-        k_side0_idx<<<grid_for(nnz), kThreads, 0, s>>>(lv.edge_idx, C ? m->node_rep : nullptr, nnz, bad,
-                                                       const_cast<int32_t *>(S0.idx),
-                                                       C ? const_cast<int32_t *>(S0.cidx) : nullptr);
+                                                        C->n_nodes, bad, L.rowmap, S.tier.row_ids);
+    k_side0<<<grid_for(std::max(nnz, nE + 1)), kThreads, 0, s>>>(
+        lv.edge_ptr, lv.edge_idx, lv.edge_w, C ? m->node_rep : nullptr, nE, nnz, bad, const_cast<int32_t *>(S0.ptr),
+        const_cast<int32_t *>(S0.idx), C ? const_cast<int32_t *>(S0.cidx) : nullptr, L.w);
     // side 1: node -> hyperedges in ascending id (stable sort of incidences
     // by node; the offsets come from the sorted node ids)
     size_t tb = S.temp_bytes;
@@ -842,7 +853,6 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
     if (C) {
         const int64_t rows = nV + nE, rows_c = L.rows_coarse;
         if (rows > 0) {
-            k_iota<<<grid_for(rows), kThreads, 0, s>>>(rows, S.tier.row_ids);
             tb = S.temp_bytes;
             if (prim_sort_pairs(S.temp, tb, reinterpret_cast<const uint32_t *>(L.rowmap),
                                                    reinterpret_cast<uint32_t *>(S.keys_out), S.tier.row_ids, L.inv_idx,
@@ -866,15 +876,6 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
     if ((st = tier_scan(TS, sm, chunk, bad, S, M->counts, s)) != HNV_OK ||
         (st = tier_emit(TS, chunk, (int64_t)S0.n_chunks + S1.n_chunks, bad, S, M->counts, long_key(L.rows, chunk),
                         M->n_long, s)) != HNV_OK)
-        return st;
-    // weights and reciprocals
-    if (lv.edge_w) {
-        if ((st = copy_d2d(L.w, lv.edge_w, 4 * nE, s)) != HNV_OK)
-            return st;
-    } else if (nE > 0) {
-        k_fill_f32<<<grid_for(nE), kThreads, 0, s>>>(L.w, nE, 1.0f);
-    }
-    if ((st = dev_check("weights")) != HNV_OK)
         return st;
     return dev_recompute_reciprocals(p, l, s);
 }

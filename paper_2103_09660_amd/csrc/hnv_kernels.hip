@@ -1323,73 +1323,137 @@ __global__ __launch_bounds__(kBlock) void k_score_final(ScoreArgs a)
 // reciprocals (FP64) and per-star-edge scale arrays
 // ---------------------------------------------------------------------------
 
-// node v: S_v = sum_{e ∋ v} w_e in FP64, r_v = 1 / S_v (0 without
-// hyperedges).  A group of kRecipLanes lanes per node: lane i adds the
-// positions i, i + 16, i + 32, ... in that order (four loads in flight),
-// then a fixed butterfly over the group.
-constexpr int kRecipLanes = 16;
-__global__ __launch_bounds__(kBlock) void k_recip_nodes(const int32_t *__restrict__ ptr,
-                                                        const int32_t *__restrict__ idx,
-                                                        const float *__restrict__ w, int64_t n_nodes,
-                                                        int64_t row_base_edges, float *__restrict__ r)
+// Every row's reciprocal weight sum with unit weights: a node's S_v is its
+// degree (the FP64 sum of that many ones, exactly), and a hyperedge's weight
+// cancels in its own mean, r_e = 1 / |e|; 0 for rows without neighbours.
+HNV_DEV float recip_degree(int deg) { return (deg > 0) ? (float)(1.0 / (double)deg) : 0.0f; }
+
+__global__ __launch_bounds__(kBlock) void k_recip_unit(const int32_t *__restrict__ node_ptr,
+                                                       const int32_t *__restrict__ edge_ptr, int64_t n_nodes,
+                                                       int64_t rows, float *__restrict__ r)
 {
-    const int64_t v = (linear_block() * kBlock + threadIdx.x) / kRecipLanes;
-    const int gl = threadIdx.x % kRecipLanes;
-    double s = 0.0;
+    const int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (u >= rows)
+        return;
+    const int32_t *p = u < n_nodes ? node_ptr + u : edge_ptr + (u - n_nodes);
+    r[u] = recip_degree(p[1] - p[0]);
+}
+
+// With given weights, node v: S_v = sum_{e ∋ v} w_e in FP64, r_v = 1 / S_v, and
+// on the way each star edge's weight wn, which the forward sweep multiplies by.
+// kRecipLanes lanes per node (most nodes have a few hyperedges) add its
+// positions i, i + kRecipLanes, .. and a fixed butterfly adds the lanes; nodes
+// of more than kRecipLong hyperedges are then done by the whole wavefront, and
+// those of more than kRecipHuge (the merged hubs of coarse levels) by the whole
+// workgroup, one after another.  The last blocks take the hyperedges (r_e = 1 /
+// |e|).
+// One pass over the ids and one gather of weights: 38 us per level of
+// a hierarchy of 0.7M nodes / 0.45M hyperedges (averages), where 16 lanes per
+// node, a second gather for wn and a launch for the hyperedges took 67.  Long
+// nodes lie together in coarse levels (the first groups hold the largest
+// hyperedges), so there (more than 8 hyperedges per node on average) a block
+// takes nodes a grid apart (`strided`), 60 -> 40 us; in order, the offsets of a
+// level of short lists are read once.
+constexpr int kRecipLanes = 4;
+constexpr int kRecipLong = 64;
+constexpr int kRecipHuge = 2048;
+constexpr int kRecipRows = kBlock / kRecipLanes;   // nodes per block
+
+// The lane's share (positions first, first + step, ..) of the weights of the
+// star edges [j, end): written to wn, and their sum.
+HNV_DEV double sum_weights(const int32_t *__restrict__ idx, const float *__restrict__ w, int64_t n_nodes, int32_t j,
+                           int32_t end, int step, float *__restrict__ wn)
+{
+    constexpr int U = 8;   // gathers in flight
+    double t = 0.0;
+    for (; j < end; j += U * step) {
+        float x[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            x[k] = j + k * step < end ? w[idx[j + k * step] - n_nodes] : 0.0f;
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (j + k * step < end) {
+                wn[j + k * step] = x[k];
+                t += (double)x[k];
+            }
+    }
+    return t;
+}
+
+__global__ __launch_bounds__(kBlock) void k_recip_weighted(const int32_t *__restrict__ ptr,
+                                                           const int32_t *__restrict__ idx,
+                                                           const int32_t *__restrict__ edge_ptr,
+                                                           const float *__restrict__ w, int64_t n_nodes,
+                                                           int64_t n_edges, int64_t node_blocks, bool strided,
+                                                           float *__restrict__ wn, float *__restrict__ r)
+{
+    const int64_t b = linear_block();
+    if (b >= node_blocks) {
+        const int64_t e = (b - node_blocks) * kBlock + threadIdx.x;
+        if (e < n_edges)
+            r[n_nodes + e] = recip_degree(edge_ptr[e + 1] - edge_ptr[e]);
+        return;
+    }
+    const int lane = threadIdx.x % kWave, gl = lane % kRecipLanes;
+    const int row = threadIdx.x / kRecipLanes;
+    auto node_of = [&](int i) { return strided ? i * node_blocks + b : b * kRecipRows + i; };
+    const int64_t v = node_of(row);
+    int32_t begin = 0, end = 0;
     if (v < n_nodes) {
-        const int32_t end = ptr[v + 1];
-        int32_t j = ptr[v] + gl;
-        for (; j + 3 * kRecipLanes < end; j += 4 * kRecipLanes) {
-            const float w0 = w[idx[j] - row_base_edges], w1 = w[idx[j + kRecipLanes] - row_base_edges];
-            const float w2 = w[idx[j + 2 * kRecipLanes] - row_base_edges];
-            const float w3 = w[idx[j + 3 * kRecipLanes] - row_base_edges];
+        begin = ptr[v];
+        end = ptr[v + 1];
+    }
+    const bool is_long = end - begin > kRecipLong;
+    double s = 0.0;
+    if (!is_long) {
+        for (int32_t j = begin + gl; j < end; j += 2 * kRecipLanes) {   // (two gathers in flight)
+            const bool two = j + kRecipLanes < end;
+            const float w0 = w[idx[j] - n_nodes];
+            const float w1 = two ? w[idx[j + kRecipLanes] - n_nodes] : 0.0f;
+            wn[j] = w0;
             s += (double)w0;
-            s += (double)w1;
-            s += (double)w2;
-            s += (double)w3;
+            if (two) {
+                wn[j + kRecipLanes] = w1;
+                s += (double)w1;
+            }
         }
-        for (; j < end; j += kRecipLanes)
-            s += (double)w[idx[j] - row_base_edges];
     }
 #pragma unroll
     for (int off = 1; off < kRecipLanes; off <<= 1)
         s += __shfl_xor(s, off, kWave);
+    const bool is_huge = end - begin > kRecipHuge;
+    uint64_t todo = __ballot(is_long && !is_huge && gl == 0);
+    while (todo) {   // uniform
+        const int of = __ffsll((unsigned long long)todo) - 1;
+        todo &= todo - 1;
+        double t = sum_weights(idx, w, n_nodes, __shfl(begin, of, kWave) + lane, __shfl(end, of, kWave), kWave, wn);
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1)
+            t += __shfl_xor(t, off, kWave);
+        if (lane == of)
+            s = t;
+    }
+    __shared__ int32_t huge[kRecipRows];
+    __shared__ int n_huge;
+    if (threadIdx.x == 0)
+        n_huge = 0;
+    __syncthreads();
+    if (is_huge && gl == 0)
+        huge[atomicAdd(&n_huge, 1)] = row;
+    __syncthreads();
+    const int n = n_huge;
+    for (int i = 0; i < n; ++i) {
+        const int64_t u = node_of(huge[i]);
+        const double t = block_wave_sums(sum_weights(idx, w, n_nodes, ptr[u] + (int)threadIdx.x, ptr[u + 1], kBlock, wn));
+        if (threadIdx.x == 0)
+            r[u] = (t > 0.0) ? (float)(1.0 / t) : 0.0f;
+        __syncthreads();   // (the sums' LDS is free again)
+    }
+    if (is_huge)
+        return;
     if (v < n_nodes && gl == 0)
         r[v] = (s > 0.0) ? (float)(1.0 / s) : 0.0f;
-}
-
-// node v with unit weights: S_v is v's degree (the FP64 sum of that many
-// ones, exactly), so r_v = 1 / degree without reading the hyperedge ids
-__global__ __launch_bounds__(kBlock) void k_recip_nodes_unit(const int32_t *__restrict__ ptr, int64_t n_nodes,
-                                                             float *__restrict__ r)
-{
-    const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (v >= n_nodes)
-        return;
-    const int deg = ptr[v + 1] - ptr[v];
-    r[v] = (deg > 0) ? (float)(1.0 / (double)deg) : 0.0f;
-}
-
-// hyperedge e: r_e = 1 / |e| (its weight cancels in its own mean)
-__global__ __launch_bounds__(kBlock) void k_recip_edges(const int32_t *__restrict__ ptr, int64_t n_edges,
-                                                        int64_t n_nodes, float *__restrict__ r)
-{
-    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e >= n_edges)
-        return;
-    const int deg = ptr[e + 1] - ptr[e];
-    r[n_nodes + e] = (deg > 0) ? (float)(1.0 / (double)deg) : 0.0f;
-}
-
-// per star edge of the node side (neighbour = hyperedge e): its weight w_e,
-// which the forward sweep multiplies by (not needed for unit weights)
-__global__ __launch_bounds__(kBlock) void k_fill_weights(const int32_t *__restrict__ idx_node_side,
-                                                         const float *__restrict__ w, int64_t nnz, int64_t n_nodes,
-                                                         float *__restrict__ wn)
-{
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j < nnz)
-        wn[j] = w[idx_node_side[j] - n_nodes];
 }
 
 // per star edge, the reverse sweep's scale, the reciprocal row sum of the
@@ -1462,15 +1526,13 @@ hnv_status dev_recompute_reciprocals(hnv_plan *p, int level, void *stream)
 {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     LevelPlan &L = p->lv[level];
-    if (L.n_nodes > 0 && L.unit_w)
-        k_recip_nodes_unit<<<grid1d(L.n_nodes, kBlock), kBlock, 0, s>>>(L.side[1].ptr, L.n_nodes, L.r);
-    else if (L.n_nodes > 0)
-        k_recip_nodes<<<fold_grid(blocks_for(L.n_nodes, kBlock / kRecipLanes)), kBlock, 0, s>>>(
-            L.side[1].ptr, L.side[1].idx, L.w, L.n_nodes, L.n_nodes, L.r);
-    if (L.n_edges > 0)
-        k_recip_edges<<<grid1d(L.n_edges, kBlock), kBlock, 0, s>>>(L.side[0].ptr, L.n_edges, L.n_nodes, L.r);
-    if (L.nnz > 0 && !L.unit_w)
-        k_fill_weights<<<grid1d(L.nnz, kBlock), kBlock, 0, s>>>(L.side[1].idx, L.w, L.nnz, L.n_nodes, L.side[1].wn);
+    const int64_t node_blocks = blocks_for(L.n_nodes, kRecipRows);
+    if (L.rows > 0 && L.unit_w)
+        k_recip_unit<<<grid1d(L.rows, kBlock), kBlock, 0, s>>>(L.side[1].ptr, L.side[0].ptr, L.n_nodes, L.rows, L.r);
+    else if (L.rows > 0)
+        k_recip_weighted<<<fold_grid(node_blocks + blocks_for(L.n_edges, kBlock)), kBlock, 0, s>>>(
+            L.side[1].ptr, L.side[1].idx, L.side[0].ptr, L.w, L.n_nodes, L.n_edges, node_blocks, L.nnz > 8 * L.n_nodes,
+            L.side[1].wn, L.r);
     L.scales_ready = false;   // the reverse sweep refills them from these reciprocals
     return dev_check("reciprocal kernels");
 }
