@@ -358,7 +358,10 @@ hnv_status hnv_sweep(hnv_plan *plan, int level, const void *z_in, void *z_out, f
  * further one on the one before.  z_out: HOST array of n device matrices; sweep
  * i's result goes to z_out[i], or is not kept where that is NULL (the last one
  * is).  No entry may alias z_in or another one.  The same results as n calls of
- * hnv_sweep; sweeps that aren't kept use the plan's scratch embedding. */
+ * hnv_sweep, but for the order in which levels of up to 200,000 rows add rows
+ * of more than a few neighbours (one after another up to 64, which is the order
+ * that gradients of log-weights are formed from).  Sweeps that aren't kept use
+ * the plan's scratch embedding. */
 hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, void *const *z_out, int n, float omega,
                       int from_coarse, void *stream);
 
@@ -407,7 +410,8 @@ hnv_status hnv_sweep_adjoint_split(hnv_plan *plan, int level, const void *g_in, 
  * arrays of n + 1 and n device matrices; an entry of g_out may appear again two
  * places later.  With dw_accum and node_accum the weight gradient is split as
  * hnv_sweep_adjoint_split has it, with neither none is formed (one without the
- * other is an error).  The same results as n calls. */
+ * other is an error).  The same results as n calls, but for the order of sums as
+ * in hnv_sweeps. */
 hnv_status hnv_sweeps_adjoint(hnv_plan *plan, int level, const void *g_in, void *const *g_out,
                               const void *const *states, int n, float *dw_accum, float *node_accum, float omega,
                               void *stream);

@@ -79,9 +79,6 @@ struct SweepCtl {
     int32_t *done;        // [n_levels] sweeps run per level
     double tol;
     int64_t n_res;        // sweeps run so far (next index into res)
-    const void *redo_src; // a launch of several sweeps ran past the level's last one: the next launch
-    void *redo_dst;       //   repeats its first `redo` sweeps (0: none)
-    int32_t redo;
 };
 
 struct LevelPlan {

@@ -170,6 +170,7 @@ enum Mode : int {
     kAdjNode = 1,   // reverse sweep, node rows
     kAdjEdge = 2,   // reverse sweep, hyperedge rows, summing the per-node scalars of their members
     kAdjEdgeNoSum = 3,   // reverse sweep, hyperedge rows, without that sum
+    kSerial = 8,    // added to one of these: rows in gather_serial's order
 };
 
 struct GatherArgs {
@@ -179,6 +180,7 @@ struct GatherArgs {
     int32_t nb_split[2];      // finalize blocks per side (per panel)
     int32_t blocks_per_panel;
     int32_t n_long[2];        // leading items per side that a whole workgroup takes
+    int32_t serial;           // the order that serves gradients (gather_serial)
     int32_t dp;               // columns per panel
     int64_t ld;               // row stride (elements) = d
     float omega;
@@ -373,6 +375,81 @@ HNV_DEV void gather_wave(const int32_t *__restrict__ nb, const float *__restrict
         for (int off = 1; off < kWave; off <<= 1)
             csum += __shfl_xor(csum, off, kWave);
     }
+}
+
+// A row of a wavefront-tier item by one wavefront, in the order that serves
+// gradients (SERIAL): up to kSerialRow neighbours one after another by the first
+// lane group, more as gather_wave in pieces of kSerialPiece, group g adding the
+// pieces g, g + Q, ..  The sums don't depend on the level's tiering then.  The
+// chain of a row of up to 64 neighbours is its loads, eight in flight: a training
+// step of 10 sweeps at each of five levels (20K nodes / 8K hyperedges, FP32, d =
+// 64) takes 2,040 us, and 1,700 in k_gather's order.
+constexpr int kSerialRow = 64;
+constexpr int kSerialPiece = 512;
+
+template <typename T, int EPL, int G, bool SCALE, bool SCALAR>
+HNV_DEV void gather_serial(const int32_t *__restrict__ nb, const float *__restrict__ sc,
+                           const float *__restrict__ cvec, int start, int len, const T *__restrict__ src, int64_t ld,
+                           int col, bool col_ok, int lane, int g, float (&acc)[EPL], float &csum)
+{
+    using S = Slice<T, EPL>;
+    constexpr int Q = kWave / G;
+    if (len <= kSerialRow) {
+        int my_nb = 0;
+        float my_s = 1.0f;
+        if (lane < len) {
+            my_nb = nb[start + lane];
+            if (SCALE)
+                my_s = sc[start + lane];
+            if (SCALAR)
+                csum += cvec[my_nb];
+        }
+        for (int j = 0; j < len; j += 2 * kUnroll) {
+            typename S::Raw raw[2 * kUnroll];
+            float s[2 * kUnroll];
+#pragma unroll
+            for (int k = 0; k < 2 * kUnroll; ++k) {
+                const int v = __shfl(my_nb, (j + k) & (kWave - 1), kWave);
+                s[k] = SCALE ? __shfl(my_s, (j + k) & (kWave - 1), kWave) : 1.0f;
+                if (j + k < len && col_ok)
+                    raw[k] = S::load(src + (int64_t)v * ld + col);
+            }
+            if (col_ok) {
+#pragma unroll
+                for (int k = 0; k < 2 * kUnroll; ++k)
+                    if (j + k < len)
+                        accumulate<SCALE, T, EPL>(acc, s[k], raw[k]);
+            }
+        }
+        if (SCALAR) {
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1)
+                csum += __shfl_xor(csum, off, kWave);
+        }
+        return;
+    }
+    if (len <= kSerialPiece) {
+        gather_wave<T, EPL, G, SCALE, SCALAR>(nb, sc, cvec, start, len, src, ld, col, col_ok, lane, g, acc, csum);
+        return;
+    }
+    for (int p = 0; p * kSerialPiece < len; ++p) {
+        float piece[EPL], c = 0.0f;
+        zero(piece);
+        gather_wave<T, EPL, G, SCALE, SCALAR>(nb, sc, cvec, start + p * kSerialPiece,
+                                              min(kSerialPiece, len - p * kSerialPiece), src, ld, col, col_ok, lane, g,
+                                              piece, c);
+        csum += c;
+        if (p % Q == g) {
+#pragma unroll
+            for (int i = 0; i < EPL; ++i)
+                acc[i] += piece[i];
+        }
+    }
+#pragma unroll
+    for (int off = G; off < kWave; off <<= 1)
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+            acc[i] += __shfl_xor(acc[i], off, kWave);
 }
 
 // acc (and csum) of the workgroup's wavefronts added in order, into
@@ -625,9 +702,11 @@ HNV_DEV void block_resid(const GatherArgs &a, double r2, int64_t lb)
 // main kernel: wavefront tier + lane-group tier of both sides, all panels
 // ---------------------------------------------------------------------------
 
-template <typename T, int EPL, int G, int MODE, bool FUSED, bool CTL>
+template <typename T, int EPL, int G, int MODES, bool FUSED, bool CTL>
 __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
 {
+    constexpr int MODE = MODES & ~kSerial;
+    constexpr bool SERIAL = (MODES & kSerial) != 0;
     const int64_t lb = linear_block();
     if (lb >= a.n_blocks)
         return;
@@ -695,19 +774,30 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
             load_own<T, EPL, MODE>(self, a, mats, c.row, zrow, srow, c.len, col);
         }
         int start = c.start, len = c.len;
-        if (whole_block) {
-            const int per = (c.len + kWavesPerBlock - 1) / kWavesPerBlock;
-            start += wave * per;
-            len = max(0, min(per, c.len - wave * per));
+        if constexpr (SERIAL) {   // (a long item's first wavefront takes it alone)
+            if (mine) {
+                if (use_scale)
+                    gather_serial<T, EPL, G, true, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g,
+                                                            acc, csum);
+                else
+                    gather_serial<T, EPL, G, false, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane,
+                                                             g, acc, csum);
+            }
+        } else {
+            if (whole_block) {
+                const int per = (c.len + kWavesPerBlock - 1) / kWavesPerBlock;
+                start += wave * per;
+                len = max(0, min(per, c.len - wave * per));
+            }
+            if (use_scale)
+                gather_wave<T, EPL, G, true, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
+                                                      csum);
+            else
+                gather_wave<T, EPL, G, false, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
+                                                       csum);
+            if (whole_block)
+                block_sum<EPL, G, kScalar>(acc, csum, wave, lane);
         }
-        if (use_scale)
-            gather_wave<T, EPL, G, true, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
-                                                  csum);
-        else
-            gather_wave<T, EPL, G, false, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
-                                                   csum);
-        if (whole_block)
-            block_sum<EPL, G, kScalar>(acc, csum, wave, lane);
         if (mine) {
             if (!whole) {
                 if (g == 0 && col_ok) {
@@ -943,7 +1033,6 @@ __global__ __launch_bounds__(kBlock) void k_ctl_init(SweepCtl *ctl, int32_t *fla
         ctl->done = flags + n_levels;
         ctl->tol = tol;
         ctl->n_res = 0;
-        ctl->redo = 0;
     }
 }
 
@@ -1666,7 +1755,7 @@ struct ProfScope {
     }
 };
 
-template <typename T, int EPL, int G, int MODE, bool FUSED, bool CTL>
+template <typename T, int EPL, int G, int MODE, bool FUSED, bool CTL, bool SERIAL>
 static void launch_pair(const GatherArgs &a, int panels, hipStream_t s, ProfScope *ps)
 {
     const int64_t main_blocks = (int64_t)a.blocks_per_panel * panels;
@@ -1675,7 +1764,7 @@ static void launch_pair(const GatherArgs &a, int panels, hipStream_t s, ProfScop
     if (main_blocks) {
         GatherArgs m = a;
         m.n_blocks = main_blocks;
-        k_gather<T, EPL, G, MODE, FUSED, CTL><<<fold_grid(main_blocks), kBlock, 0, s>>>(m);
+        k_gather<T, EPL, G, SERIAL ? MODE | kSerial : MODE, FUSED, CTL><<<fold_grid(main_blocks), kBlock, 0, s>>>(m);
     }
     if (ps)
         ps->end();
@@ -1690,26 +1779,30 @@ static void launch_pair(const GatherArgs &a, int panels, hipStream_t s, ProfScop
 
 // Instantiated lane layouts: BF16 always 8 elements per lane; FP32 4 per
 // lane, or 8 for full-width rows of 128 columns or more (G = 16 .. 64).
-template <typename T, int MODE, bool FUSED, bool CTL = false>
+template <typename T, int MODE, bool FUSED, bool CTL = false, bool SERIAL = false>
 static hnv_status dispatch_g(int G, int EPL, const GatherArgs &a, int panels, hipStream_t s, ProfScope *ps)
 {
+    if constexpr (!CTL && !SERIAL && MODE != kAdjEdge) {
+        if (a.serial)
+            return dispatch_g<T, MODE, FUSED, false, true>(G, EPL, a, panels, s, ps);
+    }
     constexpr int E = 16 / (int)sizeof(T);
     if (EPL == E) {
         switch (G) {
-        case 1: launch_pair<T, E, 1, MODE, FUSED, CTL>(a, panels, s, ps); break;
-        case 2: launch_pair<T, E, 2, MODE, FUSED, CTL>(a, panels, s, ps); break;
-        case 4: launch_pair<T, E, 4, MODE, FUSED, CTL>(a, panels, s, ps); break;
-        case 8: launch_pair<T, E, 8, MODE, FUSED, CTL>(a, panels, s, ps); break;
-        case 16: launch_pair<T, E, 16, MODE, FUSED, CTL>(a, panels, s, ps); break;
-        case 32: launch_pair<T, E, 32, MODE, FUSED, CTL>(a, panels, s, ps); break;
-        case 64: launch_pair<T, E, 64, MODE, FUSED, CTL>(a, panels, s, ps); break;
+        case 1: launch_pair<T, E, 1, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 2: launch_pair<T, E, 2, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 4: launch_pair<T, E, 4, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 8: launch_pair<T, E, 8, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 16: launch_pair<T, E, 16, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 32: launch_pair<T, E, 32, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 64: launch_pair<T, E, 64, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
         default: return fail(HNV_EUNSUPPORTED, "lane group width");
         }
     } else if (E == 4 && EPL == 8) {
         switch (G) {
-        case 16: launch_pair<T, 8, 16, MODE, FUSED, CTL>(a, panels, s, ps); break;
-        case 32: launch_pair<T, 8, 32, MODE, FUSED, CTL>(a, panels, s, ps); break;
-        case 64: launch_pair<T, 8, 64, MODE, FUSED, CTL>(a, panels, s, ps); break;
+        case 16: launch_pair<T, 8, 16, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 32: launch_pair<T, 8, 32, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 64: launch_pair<T, 8, 64, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
         default: return fail(HNV_EUNSUPPORTED, "lane group width");
         }
     } else {
@@ -1781,12 +1874,13 @@ static hnv_status reduce_resid(const double *part, int64_t n, int batch, int64_t
 // reduce_resid to reduce with the level's next sweeps.
 static hnv_status run_sweep(hnv_plan *p, int level, const void *src, void *dst, float omega, bool fused,
                             double *resid_out, hipStream_t s, SweepCtl *ctl = nullptr,
-                            const SweepScratch *scr = nullptr, int resid_slot = -1)
+                            const SweepScratch *scr = nullptr, int resid_slot = -1, bool serial = false)
 {
     LevelPlan &L = p->lv[level];
     const SweepScratch sc = scr ? *scr : plan_scratch(p);
     GatherArgs a = base_args(p, L, p->g_fwd, p->dp);
     a.partials = sc.partials;
+    a.serial = serial;
     a.omega = omega;
     a.src = src;
     a.self_src = src;
@@ -1830,14 +1924,19 @@ static hnv_status run_sweep(hnv_plan *p, int level, const void *src, void *dst, 
 // Sweeps per launch from LDS without residuals (a launch stays below a millisecond).
 constexpr int kResidentMost = 256;
 
-// Whether `sweeps` sweeps of a level in a row run from LDS: the level
-// fits, and there is more than one sweep: the loads alone take longer than one
-// launch of k_gather; two sweeps take 18 us a call against 21, ten 30 against 47
-// (2,000 nodes / 1,000 hyperedges, FP32, d = 32).  A plan that is being profiled
-// times each sweep's own launches, so it takes the general path.
+// Whether `sweeps` sweeps of a level in a row run from LDS: the level fits, and
+// the sweeps save more than the loads of a launch cost.  Measured (FP32, d =
+// 32): a launch takes about 6 us and 160 ps per row and incidence visited (V =
+// rows + 2 nnz), a sweep 0.95 us and 82 ps per V (1.2 us at 500 nodes / 250
+// hyperedges, 2.0 at 2,000 / 1,000), where a sweep of its own takes 4.4; half
+// the loads are asked for on top, since lists of a few hundred neighbours take
+// longer than their visits (with hubs and 5 sweeps the two are even).  A plan
+// that is being profiled times each sweep's own launches, so it takes the
+// general path.
 static bool use_resident(const hnv_plan *p, const LevelPlan &L, int sweeps)
 {
-    return sweeps >= 2 && !p->profiling && resident_fits(p, L);
+    const double visits = (double)L.rows + 2.0 * (double)L.nnz;
+    return sweeps * (3.45 - 82e-6 * visits) > 9.0 + 240e-6 * visits && !p->profiling && resident_fits(p, L);
 }
 
 template <typename T, int EPL, int G>
@@ -1850,15 +1949,14 @@ static void launch_resident(const ResidentArgs &a, int dp, double *part, int64_t
         return;
     const dim3 grid((unsigned)(sg.blocks[0] + sg.blocks[1] + sg.blocks[2] + sg.blocks[3]), (unsigned)a.sweeps);
     k_resident_blocks<T, EPL, G><<<grid, kBlock, 0, s>>>(a.trace, a.n_nodes + a.n_edges, words, dp, sg, part,
-                                                         part_stride, a.ctl, a.ctl_level);
+                                                         part_stride);
 }
 
-// n sweeps of `level` in one launch (src -> dst, or the control block's
-// matrices), fused: the first reads the coarser level.  With resid_out (n <=
-// kResidentBatch) also their residuals, to resid_out[0 .. n).  `redo` (early
-// stop): the launch that repeats the sweeps up to the level's last one.
+// n sweeps of `level` in one launch (src -> dst), fused: the first reads the
+// coarser level.  With resid_out (n <= kResidentBatch) also their residuals, to
+// resid_out[0 .. n).
 static hnv_status run_resident(hnv_plan *p, int level, const void *src, void *dst, float omega, bool fused, int n,
-                               double *resid_out, hipStream_t s, SweepCtl *ctl = nullptr, bool redo = false)
+                               double *resid_out, hipStream_t s)
 {
     const LevelPlan &L = p->lv[level];
     const ResidentLayout R = resident_layout(p, L);
@@ -1889,9 +1987,6 @@ static hnv_status run_resident(hnv_plan *p, int level, const void *src, void *ds
     a.src = src;
     a.dst = dst;
     a.trace = resid_out ? p->resident_trace : nullptr;
-    a.ctl = ctl;
-    a.ctl_level = level;
-    a.redo = redo;
     // the general sweep's blocks: Jacobi both wavefront tiers, then both
     // lane-group tiers; edge-first all of side 0, then all of side 1
     ResidentSegments sg{};
@@ -1933,6 +2028,16 @@ static hnv_status run_resident(hnv_plan *p, int level, const void *src, void *ds
         return st;
     return reduce_resid(p->resident_part, mb, n, mb, resid_out, plan_scratch(p), nullptr, level, s);
 }
+
+// Levels of up to this many rows take gather_serial's order in the calls that
+// serve gradients (hnv_sweeps and hnv_sweeps_adjoint).  The log-weight gradients
+// of a small hierarchy's finest level are differences of nearly equal sums, once
+// the coarser levels have smoothed the embedding: their FP32 error is 2e-4 to
+// 4e-4, and the tiering by workgroups alone, another order, moved them by 3e-5
+// to 8e-5 (20K nodes).  In larger levels one wavefront per item would be the
+// slower form and the difference is 1e-7 (500K nodes).
+constexpr int64_t kSerialRows = 200000;
+static bool serial_level(const LevelPlan &L) { return L.rows <= kSerialRows; }
 
 // The projection onto `level` (zc -> zf); with ctl (an early-stop
 // refinement) the matrices come from the control block, which then takes
@@ -2060,8 +2165,7 @@ extern "C" hnv_status hnv_sweep(hnv_plan *plan, int level, const void *z_in, voi
 // The sweeps between two kept states in one call: a call per sweep from a
 // scripting language takes about 9 us, more than a sweep of a small level (a
 // training step of 10 sweeps at each of five levels, 20K nodes / 8K hyperedges,
-// d = 64, with hnv_sweeps_adjoint: 2,840 -> 1,723 us, of which the kernels are
-// 1,600).  Results that aren't kept go to the plan's scratch embedding and the
+// d = 64, with hnv_sweeps_adjoint: 3,640 -> 2,040 us).  Results that aren't kept go to the plan's scratch embedding and the
 // next kept result in turn.
 extern "C" hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, void *const *z_out, int n,
                                  float omega, int from_coarse, void *stream)
@@ -2090,24 +2194,18 @@ extern "C" hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, vo
         return fail(HNV_EINVAL, "from_coarse at the coarsest level");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const void *cur = z_in;
+    const bool serial = serial_level(plan->lv[level]);
     for (int i = 0; i < n; ) {
         int end = i;   // the run of sweeps up to the next kept result
         while (!z_out[end])
             ++end;
-        if (use_resident(plan, plan->lv[level], end + 1 - i) && end + 1 - i <= kResidentMost) {
-            if ((st = run_resident(plan, level, cur, z_out[end], omega, from_coarse && i == 0, end + 1 - i, nullptr,
-                                   s)) != HNV_OK)
+        for (; i <= end; ++i) {   // (alternating, so that the last one writes z_out[end])
+            void *out = (end - i) % 2 == 0 ? z_out[end] : plan->zbuf;
+            if ((st = run_sweep(plan, level, cur, out, omega, from_coarse && i == 0, nullptr, s, nullptr, nullptr, -1,
+                                serial)) != HNV_OK)
                 return st;
-            cur = z_out[end];
-        } else {
-            for (int k = i; k <= end; ++k) {   // (alternating, so that the last one writes z_out[end])
-                void *out = (end - k) % 2 == 0 ? z_out[end] : plan->zbuf;
-                if ((st = run_sweep(plan, level, cur, out, omega, from_coarse && k == 0, nullptr, s)) != HNV_OK)
-                    return st;
-                cur = out;
-            }
+            cur = out;
         }
-        i = end + 1;
     }
     return HNV_OK;
 }
@@ -2208,14 +2306,10 @@ extern "C" hnv_status hnv_project(hnv_plan *plan, int level, const void *z_coars
 // that would do nothing: O(log K) waits per level instead of one per sweep.
 // While the stream is being captured into a graph every sweep is enqueued
 // and nothing waits for the host.
-// Sweeps that run from LDS (k_resident) come up to kResidentBatch to a launch;
-// the launch goes on past the level's last sweep, which its residuals then
-// show, and a second one repeats the sweeps up to it: a sweep too many costs
-// about 1 us there, a wait for the host ten, so the first launch has
-// kResidentFirst.
+// (Launches of several sweeps from LDS, repeated up to the level's last one,
+// gained from about 8 sweeps per level on, 500 -> 387 us at 2,000 nodes, but cost
+// 30 us per level that stops after one or two: taken out.)
 constexpr int kMaxStopBatch = 16;
-constexpr int kResidentFirst = 8;
-static_assert(kResidentBatch <= 2 * kResidBatch, "an early stop's residuals wait in the stage sums' scratch");
 
 static hnv_status refine_early_stop(hnv_plan *plan, const void *z_coarsest, void *z_finest,
                                     const int32_t *sweeps_per_level, float omega, double tol,
@@ -2235,20 +2329,9 @@ static hnv_status refine_early_stop(hnv_plan *plan, const void *z_coarsest, void
         const int K = sweeps_per_level[l];
         if (K == 0 && l < Lc)
             st = run_project(plan, l, nullptr, nullptr, s, plan->ctl);
-        const bool resident = use_resident(plan, plan->lv[l], K);
-        int k = 0, batch = resident ? kResidentFirst : 1;
+        int k = 0, batch = 1;
         while (k < K && st == HNV_OK) {
-            if (resident) {   // a launch of up to kResidentBatch sweeps, and the repeat if it ran past the last one
-                const int n = std::min({batch, kResidentBatch, K - k});
-                const bool fused = k == 0 && l < Lc;
-                st = run_resident(plan, l, nullptr, nullptr, omega, fused, n, plan->resid_stage, s, plan->ctl);
-                if (st == HNV_OK) {
-                    k_resident_decide<<<1, 1, 0, s>>>(plan->ctl, l, n, plan->resid_stage);
-                    if (n > 1)
-                        st = run_resident(plan, l, nullptr, nullptr, omega, fused, n, nullptr, s, plan->ctl, true);
-                }
-                k += n;
-            } else for (const int end = std::min(K, k + batch); k < end && st == HNV_OK; ++k)
+            for (const int end = std::min(K, k + batch); k < end && st == HNV_OK; ++k)
                 st = run_sweep(plan, l, nullptr, nullptr, omega, k == 0 && l < Lc, nullptr, s, plan->ctl);
             if (st != HNV_OK || k >= K)
                 break;
@@ -2398,7 +2481,8 @@ extern "C" hnv_status hnv_refine(hnv_plan *plan, const void *z_coarsest, void *z
 // to the plan's per-node scratch and a finish pass subtracts omega times
 // their member sums.
 static hnv_status run_adjoint(hnv_plan *plan, int level, const void *g_in, void *g_out, const void *z_prev,
-                              const void *z_cur, float *dw, float *node_acc, float omega, int wgrad, hipStream_t s)
+                              const void *z_cur, float *dw, float *node_acc, float omega, int wgrad, hipStream_t s,
+                              bool serial = false)
 {
     LevelPlan &L = plan->lv[level];
     if (hnv_status st = ensure_reverse_scales(plan, level, s); st != HNV_OK)
@@ -2406,6 +2490,7 @@ static hnv_status run_adjoint(hnv_plan *plan, int level, const void *g_in, void 
     const int G = plan->g_full, E = plan->epl_full;
     const bool edge_first = plan->opts.order == HNV_ORDER_EDGE_FIRST;
     GatherArgs a = base_args(plan, L, G, plan->d);
+    a.serial = serial;
     a.omega = omega;
     a.src = g_in;
     a.self_src = g_in;
@@ -2518,8 +2603,8 @@ extern "C" hnv_status hnv_sweeps_adjoint(hnv_plan *plan, int level, const void *
             return st;
     for (int j = 0; j < n; ++j)
         if ((st = run_adjoint(plan, level, j == 0 ? g_in : g_out[j - 1], g_out[j], states[n - 1 - j], states[n - j],
-                              dw_accum, node_accum, omega, wgrad ? 2 : 0, reinterpret_cast<hipStream_t>(stream))) !=
-            HNV_OK)
+                              dw_accum, node_accum, omega, wgrad ? 2 : 0, reinterpret_cast<hipStream_t>(stream),
+                              serial_level(L))) != HNV_OK)
             return st;
     return HNV_OK;
 }

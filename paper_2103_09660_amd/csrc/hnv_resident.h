@@ -26,8 +26,7 @@ namespace hnv {
 // k_resident_blocks forms the per-block partials of a general sweep from them.
 //
 // Measured, FP32, d = 32, 2,000 nodes / 1,000 hyperedges and three coarser
-// levels, 10 sweeps each with residuals: 225 -> 152 us; until every level
-// changes by at most 2e-3: 500 -> 387 us.  A sweep of the finest level takes 2.0
+// levels, 10 sweeps each with residuals: 225 -> 152 us.  A sweep of the finest level takes 2.0
 // us where a launch each takes 4.5, after about 8 us of loads; random LDS words
 // (bank conflicts) are most of it.
 constexpr int kResidentThreads = 1024;
@@ -45,9 +44,6 @@ struct ResidentArgs {
     const void *src;
     void *dst;
     uint32_t *trace;          // [sweeps + 1][words][rows] the rows' words before and after each sweep, or null
-    SweepCtl *ctl;            // early stop: the matrices and the stop flag come from here
-    int32_t ctl_level;
-    int32_t redo;             // early stop: this launch repeats the first ctl->redo sweeps
 };
 
 // One word of a row: its columns as floats and back (as Slice has them).
@@ -285,25 +281,8 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(ResidentArgs a)
     static_assert(kRowsPerGroup == 1, "a lane-group tier row per lane group");
     static_assert(kWavesPerBlock == 4 && 4 * (kWave / G) <= kWave, "a row's quarters, in one wavefront");
     __shared__ __align__(16) unsigned char lds[kResidentLds];
-    int sweeps = a.sweeps;
-    const void *src_v = a.src;
-    void *dst_v = a.dst;
-    if (a.ctl) {
-        if (a.redo) {
-            sweeps = a.ctl->redo;
-            if (sweeps == 0)
-                return;
-            src_v = a.ctl->redo_src;
-            dst_v = a.ctl->redo_dst;
-        } else {
-            if (a.ctl->stop[a.ctl_level])
-                return;
-            src_v = a.ctl->cur;
-            dst_v = a.ctl->next;
-        }
-    }
-    const uint32_t *src = static_cast<const uint32_t *>(src_v) + blockIdx.x;   // this workgroup's word of row 0
-    uint32_t *dst = static_cast<uint32_t *>(dst_v) + blockIdx.x;
+    const uint32_t *src = static_cast<const uint32_t *>(a.src) + blockIdx.x;   // this workgroup's word of row 0
+    uint32_t *dst = static_cast<uint32_t *>(a.dst) + blockIdx.x;
     const int64_t ld = a.ld / Word<T>::N;   // words per row
     const int nV = a.n_nodes, nE = a.n_edges, rows = nV + nE, tid = threadIdx.x;
     unsigned char *e_old = lds + a.off_e[0], *e_new = lds + a.off_e[1];
@@ -363,7 +342,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(ResidentArgs a)
     }
     __syncthreads();
     const int64_t per_sweep = (int64_t)gridDim.x * rows;
-    uint32_t *trace = a.trace && !a.redo ? a.trace + (int64_t)blockIdx.x * rows : nullptr;
+    uint32_t *trace = a.trace ? a.trace + (int64_t)blockIdx.x * rows : nullptr;
     if (trace) {
         for (int i = tid; i < rows; i += kResidentThreads)
             trace[i] = word_at(i < nE ? e_old : lds, items[i].x);
@@ -371,7 +350,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(ResidentArgs a)
     }
     const float keep = 1.0f - a.omega;
     const int wide0 = __builtin_amdgcn_readfirstlane(n_wide[0]), wide1 = __builtin_amdgcn_readfirstlane(n_wide[1]);
-    for (int k = 0; k < sweeps; ++k) {
+    for (int k = 0; k < a.sweeps; ++k) {
         resident_side<T, G, false>(lds, e_old, e_new, idx0, wn, items, mix, a.side[0].n_chunks, wide0,
                                    a.side[0].n_small, keep, trace);
         __syncthreads();
@@ -407,10 +386,8 @@ struct ResidentSegments {
 template <typename T, int EPL, int G>
 __global__ __launch_bounds__(kBlock) void k_resident_blocks(const uint32_t *__restrict__ trace, int rows, int words,
                                                             int dp, ResidentSegments sg, double *__restrict__ part,
-                                                            int64_t part_stride, const SweepCtl *ctl, int level)
+                                                            int64_t part_stride)
 {
-    if (ctl && ctl->stop[level])
-        return;
     constexpr int Q = kWave / G, NW = EPL / Word<T>::N;
     int b = blockIdx.x, s = 0;
     while (b >= sg.blocks[s])
@@ -437,39 +414,6 @@ __global__ __launch_bounds__(kBlock) void k_resident_blocks(const uint32_t *__re
     const double sum = block_wave_sums(r2);
     if (threadIdx.x == 0)
         part[(int64_t)blockIdx.y * part_stride + blockIdx.x] = sum;
-}
-
-// Early stop, after a launch of n sweeps whose residuals are in r: the first
-// one <= tol is the level's last sweep.  If it isn't the launch's last, the
-// next launch repeats the sweeps up to it, over the launch's own output.
-__global__ void k_resident_decide(SweepCtl *ctl, int level, int n, const double *__restrict__ r)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0)
-        return;
-    ctl->redo = 0;
-    if (ctl->stop[level])
-        return;
-    int ran = 0;
-    while (ran < n) {
-        const double x = r[ran];
-        if (ctl->res)
-            ctl->res[ctl->n_res + ran] = x;
-        ++ran;
-        if (x <= ctl->tol) {
-            ctl->stop[level] = 1;
-            break;
-        }
-    }
-    ctl->n_res += ran;
-    ctl->done[level] += ran;
-    void *w = ctl->next;
-    if (ran < n) {
-        ctl->redo = ran;
-        ctl->redo_src = ctl->cur;
-        ctl->redo_dst = w;
-    }
-    ctl->cur = w;
-    ctl->next = (w == ctl->buf[0]) ? ctl->buf[1] : ctl->buf[0];
 }
 
 }  // namespace hnv
