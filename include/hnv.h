@@ -100,7 +100,7 @@ typedef struct {
     int32_t panel_cols;  /* columns per pass of a forward sweep (divides d, multiple of 8) */
     int32_t small_max;   /* rows with at most this many neighbours go to a lane group (capped
                             at 4 lanes' worth of indices per lane of the group); default 8, 16
-                            or 64 by the level's size */
+                            or 64 by the level's size, 64 where chunk is given */
     int32_t chunk;       /* neighbours per wavefront or workgroup work item; longer rows are split
                             (default 2048) */
     int32_t order;       /* HNV_ORDER_*: update order of a sweep (Section 3.3 describes both; the
@@ -350,7 +350,8 @@ hnv_status hnv_project(hnv_plan *plan, int level, const void *z_coarse, void *z_
  * z_in is the embedding of level+1 and the sweep runs on its projection
  * (fused; equal to hnv_project then hnv_sweep).  z_out must not alias z_in,
  * except for an edge-first plan with from_coarse = 0 (in place).
- * resid_dev: DEVICE double[1] or NULL, receives ||z_out - z_start||_F. */
+ * resid_dev: DEVICE double[1] or NULL, receives ||z_out - z_start||_F.  Rows are
+ * added in the order that hnv_refine takes (hnv_sweeps has another). */
 hnv_status hnv_sweep(hnv_plan *plan, int level, const void *z_in, void *z_out, float omega,
                      int from_coarse, double *resid_dev, void *stream);
 
@@ -358,10 +359,13 @@ hnv_status hnv_sweep(hnv_plan *plan, int level, const void *z_in, void *z_out, f
  * further one on the one before.  z_out: HOST array of n device matrices; sweep
  * i's result goes to z_out[i], or is not kept where that is NULL (the last one
  * is).  No entry may alias z_in or another one.  The same results as n calls of
- * hnv_sweep, but for the order in which levels of up to 200,000 rows add rows
- * of more than a few neighbours (one after another up to 64, which is the order
- * that gradients of log-weights are formed from).  Sweeps that aren't kept use
- * the plan's scratch embedding. */
+ * hnv_sweep, but for the order in which rows of more than a few neighbours are
+ * added: here one that the plan's default tiers don't change (one neighbour
+ * after another up to 64, longer rows 512 at a time; with options of the
+ * caller's, up to small_max and chunk at a time).  The reverse sweeps take the
+ * same order.  Gradients of log-weights can be differences of nearly equal sums:
+ * between states of the one order and of the other they may differ by some 1e-5
+ * of their norm.  Sweeps that aren't kept use the plan's scratch embedding. */
 hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, void *const *z_out, int n, float omega,
                       int from_coarse, void *stream);
 
@@ -410,8 +414,7 @@ hnv_status hnv_sweep_adjoint_split(hnv_plan *plan, int level, const void *g_in, 
  * arrays of n + 1 and n device matrices; an entry of g_out may appear again two
  * places later.  With dw_accum and node_accum the weight gradient is split as
  * hnv_sweep_adjoint_split has it, with neither none is formed (one without the
- * other is an error).  The same results as n calls, but for the order of sums as
- * in hnv_sweeps. */
+ * other is an error).  The same results as n calls. */
 hnv_status hnv_sweeps_adjoint(hnv_plan *plan, int level, const void *g_in, void *const *g_out,
                               const void *const *states, int n, float *dw_accum, float *node_accum, float omega,
                               void *stream);

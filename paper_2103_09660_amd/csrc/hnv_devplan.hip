@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kThreads) void k_small_items(TierSides T, const int
 }
 
 // wavefront tier items of both sides in entry order (pieces of a row in order),
-// with the sort key side * keys + (chunk - len) >> shift (a stable ascending
+// with the sort key side * keys + item_key (a stable ascending
 // sort keeps the sides apart and puts each side's longest first; keys and
 // shift as chunk_keys and chunk_shift give them)
 __global__ __launch_bounds__(kThreads) void k_chunk_items(TierSides T, int chunk, int shift, int keys,
@@ -395,29 +395,33 @@ __global__ __launch_bounds__(kThreads) void k_chunk_items(TierSides T, int chunk
         const int32_t s = S.ptr[r] + k * chunk;
         const int32_t len = min(chunk, S.ptr[r + 1] - s);
         items[pos] = Item{r, s, len, pc == 1 ? -1 : at.slots + k};
-        key[pos] = (uint32_t)(sd * keys + ((chunk - len) >> shift));
+        key[pos] = (uint32_t)(sd * keys + item_key(chunk, shift, len, pc > 1));
         id[pos] = pos;
     }
 }
 
 // the sorted chunk items into each side's list (side 0's come first), and
-// per side the number of leading items whose length key is below `lkey`
-// (n_long, zeroed before; null: not wanted)
+// per side the numbers of leading items whose key is below each of the marks
+// (n_marked[mark][side], zeroed before; null: not wanted)
 __global__ __launch_bounds__(kThreads) void k_gather_items(TierSides T, const Item *__restrict__ in,
                                                            const int32_t *__restrict__ order,
+                                                           const uint32_t *__restrict__ key,
                                                            const int64_t *__restrict__ counts,
-                                                           const int64_t *__restrict__ n, int chunk, int shift,
-                                                           int lkey, int32_t *__restrict__ n_long)
+                                                           const int64_t *__restrict__ n, int keys, ItemMarks marks,
+                                                           int32_t *__restrict__ n_marked)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= *n)
         return;
     const int64_t c0 = counts[1];
-    if (n_long && (chunk - in[order[i]].len) >> shift < lkey) {
+    if (n_marked) {
         const int sd = (T.n == 2 && i >= c0) ? 1 : 0;
         const int64_t first = sd ? c0 : 0, end = sd ? *n : min(c0, *n);
-        if (i + 1 == end || (chunk - in[order[i + 1]].len) >> shift >= lkey)
-            n_long[sd] = (int32_t)(i + 1 - first);   // the last of the side's long items
+        const int k = (int)key[i] - sd * keys, next = i + 1 == end ? keys : (int)key[i + 1] - sd * keys;
+#pragma unroll
+        for (int m = 0; m < kItemMarks; ++m)
+            if (k < marks.key[m] && next >= marks.key[m])
+                n_marked[2 * m + sd] = (int32_t)(i + 1 - first);   // the last of the side's items below the mark
     }
     if (T.n == 2 && i >= c0)
         T.s[1].chunks[i - c0] = in[order[i]];
@@ -447,8 +451,10 @@ __global__ __launch_bounds__(kThreads) void k_split_items(TierSides T, const Tie
 // Work-list bounds from the sizes alone (see the tiering rules above): rows
 // longer than small_max number at most nnz / (small_max + 1), each has at
 // most degree / chunk + 1 pieces, and only rows longer than chunk split.
-LevelShape bound_shape(const hnv_level_dev &lv, const hnv_level_dev *coarse, int small_max, int chunk)
+LevelShape bound_shape(const hnv_plan *p, int level, const hnv_level_dev &lv, const hnv_level_dev *coarse)
 {
+    const LevelPlan &L = p->lv[level];
+    const int small_max = L.small_max, chunk = p->opts.chunk;
     LevelShape sh;
     sh.nV = lv.n_nodes;
     sh.nE = lv.n_edges;
@@ -464,8 +470,10 @@ LevelShape bound_shape(const hnv_level_dev &lv, const hnv_level_dev *coarse, int
         sh.n_small[s] = cap(n_rows);
         sh.n_chunks[s] = cap(std::min<int64_t>(sh.nnz / chunk + sh.nnz / (small_max + 1) + 1, sh.nnz + 1));
         sh.n_splits[s] = cap(sh.nnz / (chunk + 1) + 1);
-        const int shortest = chunk - (long_key(sh.rows, chunk) << chunk_shift(chunk)) + 1;   // of a long item
-        sh.n_long[s] = (int32_t)std::min<int64_t>(sh.n_chunks[s], sh.nnz / std::max(shortest, 1) + 1);
+        // of an item that is long by its key (items of split rows may be shorter)
+        const int shortest = chunk - (item_marks(p, L).key[0] << chunk_shift(chunk)) + 1;
+        const int64_t many = sh.nnz / std::max(shortest, 1) + sh.n_splits[s] + 1;
+        sh.n_long[s] = (int32_t)std::min<int64_t>(sh.n_chunks[s], std::max<int64_t>(many, L.few_items));
         slots += 2 * (sh.nnz / chunk) + 1;
     }
     sh.n_slots = cap(slots);
@@ -566,11 +574,11 @@ hnv_status scratch_layout(int64_t nnz, int64_t rows, int64_t n_chunks, int tier_
 
 // What the build leaves on the device per level, read back once at its end:
 // the check flags (the level's word, the map's word) and the tier counts of
-// both sides (small rows, chunks, split rows, partial slots; long chunks).
+// both sides (small rows, chunks, split rows, partial slots; chunks by key).
 // Kept ahead of the per-level temporaries.
 struct LevelMeta {
     int32_t flags[4];
-    int32_t n_long[2], pad[2];
+    int32_t marks[kItemMarks][2], pad[2];
     int64_t counts[8];
 };
 size_t meta_bytes(int n_levels) { return ((size_t)n_levels * sizeof(LevelMeta) + 255) & ~size_t(255); }
@@ -592,7 +600,7 @@ hnv_status device_layout(const hnv_level_dev *levels, int n_levels, int d, hnv_d
     scratch_bytes = 0;
     for (int l = 0; l < n_levels; ++l) {
         const int sm = p->lv[l].small_max;
-        bounds[l] = bound_shape(levels[l], l + 1 < n_levels ? &levels[l + 1] : nullptr, sm, o.chunk);
+        bounds[l] = bound_shape(p, l, levels[l], l + 1 < n_levels ? &levels[l + 1] : nullptr);
         Scratch S{};
         const int64_t nch = (int64_t)bounds[l].n_chunks[0] + bounds[l].n_chunks[1];
         if (hnv_status st = scratch_layout(bounds[l].nnz, bounds[l].rows, nch, 2 * (sm + 3), nullptr, S);
@@ -769,23 +777,24 @@ hnv_status tier_scan(const TierSides &T, int small_max, int chunk, const int *ba
 // the device without reading them: grids cover the bounds (max_chunks
 // wavefront-tier items of both sides) and the kernels stop at the counts.
 hnv_status tier_emit(const TierSides &T, int chunk, int64_t max_chunks, const int *bad, Scratch &S,
-                     const int64_t *counts, int lkey, int32_t *n_long, hipStream_t s)
+                     const int64_t *counts, const ItemMarks &marks, int32_t *n_marked, hipStream_t s)
 {
     if (T.total == 0)
         return HNV_OK;
     const TierArrays &A = S.tier;
     k_small_items<<<grid_for(T.total), kThreads, 0, s>>>(T, A.pos, counts, bad);
     if (max_chunks > 0) {
-        k_chunk_items<<<grid_for(T.total), kThreads, 0, s>>>(T, chunk, chunk_shift(chunk), chunk_keys(chunk), A.tc, A.tpos, S.items, S.ckey_a, S.ids_a);
+        k_chunk_items<<<grid_for(T.total), kThreads, 0, s>>>(T, chunk, chunk_shift(chunk), chunk_keys(chunk), A.tc,
+                                                             A.tpos, S.items, S.ckey_a, S.ids_a);
         // each side's longest first: a stable sort on the side and the length
         bool in_b = false;
         if (hnv_status st = bin_sort(S.ckey_a, S.ids_a, S.ckey_b, S.ids_b, max_chunks, S.n_chunks,
                                      (int64_t)T.n * chunk_keys(chunk), S, s, in_b);
             st != HNV_OK)
             return st;
-        k_gather_items<<<grid_for(max_chunks), kThreads, 0, s>>>(T, S.items, in_b ? S.ids_b : S.ids_a, counts,
-                                                                 S.n_chunks, chunk, chunk_shift(chunk), lkey,
-                                                                 n_long);
+        k_gather_items<<<grid_for(max_chunks), kThreads, 0, s>>>(T, S.items, in_b ? S.ids_b : S.ids_a,
+                                                                 in_b ? S.ckey_b : S.ckey_a, counts, S.n_chunks,
+                                                                 chunk_keys(chunk), marks, n_marked);
     }
     k_split_items<<<grid_for(T.total), kThreads, 0, s>>>(T, A.tc, A.tpos, counts);
     return dev_check("work lists");
@@ -874,8 +883,8 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
     TS.s[1] = tier_side(S1, nV, side1_offset(nE), C ? L.rowmap : nullptr);
     TS.total = side1_offset(nE) + nV;
     if ((st = tier_scan(TS, sm, chunk, bad, S, M->counts, s)) != HNV_OK ||
-        (st = tier_emit(TS, chunk, (int64_t)S0.n_chunks + S1.n_chunks, bad, S, M->counts, long_key(L.rows, chunk),
-                        M->n_long, s)) != HNV_OK)
+        (st = tier_emit(TS, chunk, (int64_t)S0.n_chunks + S1.n_chunks, bad, S, M->counts, item_marks(p, L),
+                        &M->marks[0][0], s)) != HNV_OK)
         return st;
     return dev_recompute_reciprocals(p, l, s);
 }
@@ -890,8 +899,10 @@ hnv_status finish_level(hnv_plan *p, int l, const LevelMeta &M)
     for (int sd = 0; sd < 2; ++sd) {
         const int64_t *cnt = counts + 4 * sd;
         DevSide &D = L.side[sd];
-        if (cnt[0] > D.n_small || cnt[1] > D.n_chunks || cnt[2] > D.n_splits || M.n_long[sd] > L.n_long[sd] ||
-            M.n_long[sd] > cnt[1])
+        bool marks_ok = true;
+        for (int m = 0; m < kItemMarks; ++m)
+            marks_ok = marks_ok && M.marks[m][sd] >= 0 && M.marks[m][sd] <= cnt[1];
+        if (cnt[0] > D.n_small || cnt[1] > D.n_chunks || cnt[2] > D.n_splits || !marks_ok)
             return fail(HNV_EDEVICE, "work lists exceed their bounds");
         D.n_small = (int32_t)cnt[0];
         D.n_chunks = (int32_t)cnt[1];
@@ -899,8 +910,11 @@ hnv_status finish_level(hnv_plan *p, int l, const LevelMeta &M)
         L.n_small[sd] = D.n_small;
         L.n_chunks[sd] = D.n_chunks;
         L.n_splits[sd] = D.n_splits;
-        L.n_long[sd] = M.n_long[sd];
     }
+    const int32_t most_long[2] = {L.n_long[0], L.n_long[1]};
+    set_item_counts(p, L, L.n_chunks, M.marks, L.n_long, L.n_pieced, L.n_wide);
+    if (L.n_long[0] > most_long[0] || L.n_long[1] > most_long[1])
+        return fail(HNV_EDEVICE, "workgroup items exceed their bound");
     const int64_t slots = counts[3] + counts[7];
     if (slots > p->max_slots)
         return fail(HNV_EDEVICE, "partial slots exceed their bound");
@@ -1144,7 +1158,7 @@ extern "C" hnv_status hnv_score_plan_create_device(const int32_t *cand_ptr, cons
         TS.s[0] = tier_side(D, n_cand, 0, nullptr);
         TS.total = n_cand;
         if ((st = tier_scan(TS, L.small_max, kScoreChunk, nullptr, S, S.counts, s)) != HNV_OK ||
-            (st = tier_emit(TS, kScoreChunk, L.n_chunks, nullptr, S, S.counts, 0, nullptr, s)) != HNV_OK ||
+            (st = tier_emit(TS, kScoreChunk, L.n_chunks, nullptr, S, S.counts, ItemMarks{}, nullptr, s)) != HNV_OK ||
             (st = read_back(cnt, S.counts, sizeof(cnt), s)) != HNV_OK)
             return st;
         if (cnt[0] > L.n_small || cnt[1] > L.n_chunks || cnt[2] > L.n_splits || cnt[3] > L.n_slots)

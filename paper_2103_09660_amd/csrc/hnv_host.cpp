@@ -60,6 +60,10 @@ static constexpr int kDefaultSmallMax = 64;
 // 5.74 ms, of 150K nodes (BF16, edge-first) 4.25, 3.93 and 3.93 ms, of 2M
 // nodes (BF16) 154.2, 152.9 and 151.5 ms.
 static constexpr int kDefaultChunk = 2048;
+// Neighbours per piece of an item in the order that serves gradients: a
+// wavefront each, so that a chunk is a workgroup's.
+static constexpr int kDefaultPiece = 512;
+static_assert(kDefaultChunk == kWavesPerBlock * kDefaultPiece, "a piece per wavefront of a workgroup");
 
 // Levels of up to kIdleRows rows do not fill the chip for long, and the
 // longest chain of dependent loads sets a sweep's time there: every item of
@@ -72,20 +76,16 @@ static constexpr int kDefaultChunk = 2048;
 static constexpr int64_t kIdleRows = 98304;
 static constexpr int kLongItem = 256;
 
-// The lane-group tier bound of a level of `rows` rows when the caller gives
-// none.  A sweep in us with bounds 8 / 16 / 64 (FP32 d = 64, then BF16 d =
+// The lane-group tier bound of a level (given chunks keep 64).  A sweep in us
+// with bounds 8 / 16 / 64 (FP32 d = 64, then BF16 d =
 // 128): 12K rows 6.9 / 7.4 / 14.4, 7.6 / 8.0 / 16.5; 28K rows 8.0 / 9.0 /
 // 16.6, 8.9 / 9.4 / 18.4; 60K rows 15.4 / 14.0 / 20.4, 16.8 / 14.9 / 21.7;
 // 130K rows 39.8 / 32.7 / 31.7, 42.2 / 33.8 / 32.1.
-static int default_small_max(int64_t rows)
+static void default_tiers(LevelPlan &L)
 {
-    return rows <= kIdleRows / 3 ? 8 : rows <= kIdleRows ? 16 : kDefaultSmallMax;
-}
-
-// (by the sort key, so that the long items lead each side's list)
-int long_key(int64_t rows, int chunk)
-{
-    return rows <= kIdleRows ? chunk_keys(chunk) : std::max(0, chunk - kLongItem) >> chunk_shift(chunk);
+    L.small_max = L.rows <= kIdleRows / 3 ? 8 : L.rows <= kIdleRows ? 16 : kDefaultSmallMax;
+    L.long_len = kLongItem;
+    L.few_items = L.rows <= kIdleRows ? std::numeric_limits<int>::max() : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -435,8 +435,9 @@ static void tier_side(const int32_t *ptr, int32_t n_rows, int small_max, int chu
         }
         *slot_base += pieces;
     }
-    std::stable_sort(t.chunks.begin(), t.chunks.end(),
-                     [=](const Item &a, const Item &b) { return chunk_key(chunk, a.len) < chunk_key(chunk, b.len); });
+    std::stable_sort(t.chunks.begin(), t.chunks.end(), [=](const Item &a, const Item &b) {
+        return item_key(chunk, a.len, a.aux >= 0) < item_key(chunk, b.len, b.aux >= 0);
+    });
 }
 
 struct HostLevel {
@@ -462,7 +463,7 @@ void resolve_options(const hnv_options *in, int d, hnv_dtype dtype, hnv_options 
         o.panel_cols = (d > pc && d % pc == 0) ? pc : d;
     }
     if (o.small_max < 0)
-        o.small_max = 0;   // by the level's size (init_plan_shape)
+        o.small_max = 0;   // default_tiers'
     if (o.chunk <= 0)
         o.chunk = kDefaultChunk;
     *out = o;
@@ -708,7 +709,26 @@ void settle_long_items(const hnv_plan *p, LevelPlan &L)
         L.n_long[0] = L.n_long[1] = 0;
 }
 
-static LevelShape shape_of(const HostLevel &h, bool unit_w, int chunk)
+// Counts of leading items from the marks (items whose key is below each mark).
+void set_item_counts(const hnv_plan *p, const LevelPlan &L, const int32_t (&n_chunks)[2],
+                     const int32_t (&marks)[kItemMarks][2], int32_t (&n_long)[2], int32_t (&n_pieced)[2],
+                     int32_t (&n_wide)[2])
+{
+    const bool few = (int64_t)n_chunks[0] + n_chunks[1] <= L.few_items;
+    for (int s = 0; s < 2; ++s) {
+        n_long[s] = few ? n_chunks[s] : marks[0][s];
+        n_pieced[s] = marks[1][s];
+        n_wide[s] = L.small_max < p->lane_most ? marks[2][s] : n_chunks[s];
+    }
+}
+
+ItemMarks item_marks(const hnv_plan *p, const LevelPlan &L)
+{
+    const int chunk = p->opts.chunk;
+    return ItemMarks{{key_above(chunk, L.long_len), key_above(chunk, p->piece), key_above(chunk, p->lane_most)}};
+}
+
+static LevelShape shape_of(const hnv_plan *p, int level, const HostLevel &h, bool unit_w)
 {
     LevelShape sh;
     sh.nV = h.nV;
@@ -722,10 +742,15 @@ static LevelShape shape_of(const HostLevel &h, bool unit_w, int chunk)
         sh.n_small[s] = (int32_t)h.tier[s].small.size();
         sh.n_chunks[s] = (int32_t)h.tier[s].chunks.size();
         sh.n_splits[s] = (int32_t)h.tier[s].splits.size();
-        const int key = long_key(h.rows, chunk);
-        while (sh.n_long[s] < sh.n_chunks[s] && chunk_key(chunk, h.tier[s].chunks[sh.n_long[s]].len) < key)
-            ++sh.n_long[s];
     }
+    const int chunk = p->opts.chunk;
+    const ItemMarks m = item_marks(p, p->lv[level]);
+    int32_t marks[kItemMarks][2] = {};
+    for (int s = 0; s < 2; ++s)
+        for (const Item &it : h.tier[s].chunks)
+            for (int k = 0; k < kItemMarks; ++k)
+                marks[k][s] += item_key(chunk, it.len, it.aux >= 0) < m.key[k];
+    set_item_counts(p, p->lv[level], sh.n_chunks, marks, sh.n_long, sh.n_pieced, sh.n_wide);
     sh.n_slots = h.n_slots;
     return sh;
 }
@@ -764,6 +789,8 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base)
             L.n_chunks[s] = S.n_chunks;
             L.n_splits[s] = S.n_splits;
             L.n_long[s] = h.n_long[s];
+            L.n_pieced[s] = h.n_pieced[s];
+            L.n_wide[s] = h.n_wide[s];
         }
         L.r = c.take<float>(h.rows);
         L.w = c.take<float>(h.nE);
@@ -785,7 +812,7 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base)
         }
     }
     p->zbuf = c.take<char>(p->lv[0].rows * p->d * (int64_t)elem);
-    p->partials = c.take<float>(p->max_slots * p->pstride);
+    p->partials = c.take<float>(p->max_slots * p->slot_pieces * p->pstride);
     p->resid_part = c.take<double>(kResidBatch * p->max_resid_blocks);
     p->resid_stage_len = blocks_for(p->max_resid_blocks, kBlock * 8) + 1;
     p->resid_stage = c.take<double>(2 * kResidBatch * p->resid_stage_len);
@@ -812,6 +839,9 @@ void init_plan_shape(hnv_plan *p, const std::vector<LevelShape> &shape, int d, h
     lane_layout(p->dp, elem, &p->g_fwd, &p->epl_fwd);
     lane_layout(d, elem, &p->g_full, &p->epl_full);
     p->pstride = d + 8;
+    p->piece = std::min(o.chunk, o.chunk == kDefaultChunk ? kDefaultPiece : o.chunk);
+    p->slot_pieces = (o.chunk + p->piece - 1) / p->piece;
+    p->lane_most = std::min(o.small_max > 0 ? o.small_max : kDefaultSmallMax, kIdxRegs * p->g_fwd);
     p->lv.assign(n_levels, LevelPlan{});
     for (int l = 0; l < n_levels; ++l) {
         LevelPlan &L = p->lv[l];
@@ -822,7 +852,10 @@ void init_plan_shape(hnv_plan *p, const std::vector<LevelShape> &shape, int d, h
         L.has_coarse = (l + 1 < n_levels);
         L.rows_coarse = L.has_coarse ? shape[l + 1].nV + shape[l + 1].nE : 0;
         L.unit_w = shape[l].unit_w;
-        L.small_max = std::min(o.small_max > 0 ? o.small_max : default_small_max(L.rows), kIdxRegs * p->g_fwd);
+        default_tiers(L);
+        if (o.small_max > 0 || o.chunk != kDefaultChunk)
+            L.small_max = p->lane_most;
+        L.small_max = std::min(L.small_max, p->lane_most);
     }
 }
 
@@ -896,7 +929,7 @@ extern "C" hnv_status hnv_plan_workspace_bytes(const hnv_level *levels, const hn
         for (int l = 0; l < n_levels; ++l) {
             HostLevel h;
             build_level(levels, maps, n_levels, l, o, p.lv[l].small_max, false, h);
-            sh[l] = shape_of(h, sh[l].unit_w, o.chunk);
+            sh[l] = shape_of(&p, l, h, sh[l].unit_w);
         }
         carve(&p, sh, nullptr);
         *bytes = p.ws_bytes;
@@ -954,7 +987,7 @@ extern "C" hnv_status hnv_plan_create(const hnv_level *levels, const hnv_map *ma
             for (int l = 0; l < n_levels; ++l) {
                 HostLevel h;
                 build_level(levels, maps, n_levels, l, o, p->lv[l].small_max, false, h);
-                sh[l] = shape_of(h, sh[l].unit_w, o.chunk);
+                sh[l] = shape_of(p, l, h, sh[l].unit_w);
             }
             carve(p, sh, nullptr);
             if (p->ws_bytes > ws_bytes) {

@@ -10,6 +10,12 @@
 
 typedef struct ihipStream_t *hipStream_t;
 
+#ifdef __HIP__
+#define HNV_HD __attribute__((host)) __attribute__((device))
+#else
+#define HNV_HD
+#endif
+
 namespace hnv {
 
 constexpr int kBlock = 256;   // threads per workgroup (4 wavefronts of 64)
@@ -87,6 +93,8 @@ struct LevelPlan {
     bool has_coarse = false;
     bool unit_w = true;
     int small_max = 0;               // lane-group tier bound of the level
+    int long_len = 0;                // items of more neighbours than this take a workgroup,
+    int few_items = 0;               // or all of them if there are at most this many
     bool scales_ready = false;       // the reverse-mode scales (side[*].sn) hold the current weights
     DevSide side[2];
     float *r = nullptr;              // [rows] 1 / (row weight sum), 0 for rows without neighbours
@@ -98,6 +106,9 @@ struct LevelPlan {
     // host copies of the work-list sizes (for launch geometry)
     int32_t n_small[2] = {0, 0}, n_chunks[2] = {0, 0}, n_splits[2] = {0, 0};
     int32_t n_long[2] = {0, 0};      // leading chunks that a whole workgroup takes
+    // in the order that serves gradients: leading chunks of more than a piece,
+    // and of more than lane_most neighbours (the others take a lane group)
+    int32_t n_pieced[2] = {0, 0}, n_wide[2] = {0, 0};
 };
 
 }  // namespace hnv
@@ -121,9 +132,12 @@ struct hnv_plan {
     hnv_options opts{};
     std::vector<hnv::LevelPlan> lv;
     void *zbuf = nullptr;            // scratch embedding [rows of level 0 x d]
-    float *partials = nullptr;       // [max_slots x pstride]
+    float *partials = nullptr;       // [max_slots x slot_pieces x pstride]
     int32_t pstride = 0;             // floats per partial slot (d + 8)
     int64_t max_slots = 0;
+    // the order that serves gradients: rows of up to lane_most neighbours one
+    // after another, longer ones in pieces, at most slot_pieces to a chunk
+    int lane_most = 0, piece = 0, slot_pieces = 1;
     double *resid_part = nullptr;    // [kResidBatch x max_resid_blocks] per-block partials, one slot per sweep
     int64_t max_resid_blocks = 0;
     double *resid_stage = nullptr;   // [2 x kResidBatch x resid_stage_len] partial sums of the residual stages
@@ -172,9 +186,17 @@ inline int chunk_shift(int chunk)
     return s;
 }
 inline int chunk_keys(int chunk) { return ((chunk - 1) >> chunk_shift(chunk)) + 1; }
-inline int chunk_key(int chunk, int len) { return (chunk - len) >> chunk_shift(chunk); }
-// Items whose key is below this take a whole workgroup (LevelPlan::n_long).
-int long_key(int64_t rows, int chunk);
+// (an item of a split row counts as one of at least 65 neighbours, so that the
+// last ones of an ascending list are whole rows)
+constexpr int kSplitKeyLen = 65;
+HNV_HD inline int item_key(int chunk, int shift, int len, bool split)
+{
+    const int least = chunk < kSplitKeyLen ? chunk : kSplitKeyLen;
+    return (chunk - (split && len < least ? least : len)) >> shift;
+}
+inline int item_key(int chunk, int len, bool split) { return item_key(chunk, chunk_shift(chunk), len, split); }
+// Items of more than `len` neighbours have keys below this (to within 1/512 of a chunk).
+inline int key_above(int chunk, int len) { return (chunk > len ? chunk - len : 0) >> chunk_shift(chunk); }
 // Lane layout of a row slice of `cols` elements of `elem` bytes: lanes move
 // 16 B each, or 32 B for FP32 slices of 128 columns or more.
 void lane_layout(int cols, int elem, int *lanes, int *elems_per_lane);
@@ -186,8 +208,20 @@ struct LevelShape {
     int64_t nV = 0, nE = 0, nnz = 0, rows = 0, rows_c = 0;
     bool has_coarse = false, unit_w = true;
     int32_t n_small[2] = {0, 0}, n_chunks[2] = {0, 0}, n_splits[2] = {0, 0}, n_long[2] = {0, 0};
+    int32_t n_pieced[2] = {0, 0}, n_wide[2] = {0, 0};
     int32_t n_slots = 0;
 };
+
+// Where a level's lists of items are divided: an item's list is ascending by
+// key, and its leading items below each of these keys are counted.
+constexpr int kItemMarks = 3;   // LevelPlan's n_long (unless all items are), n_pieced, n_wide
+struct ItemMarks {
+    int32_t key[kItemMarks];
+};
+ItemMarks item_marks(const hnv_plan *p, const LevelPlan &L);
+void set_item_counts(const hnv_plan *p, const LevelPlan &L, const int32_t (&n_chunks)[2],
+                     const int32_t (&marks)[kItemMarks][2], int32_t (&n_long)[2], int32_t (&n_pieced)[2],
+                     int32_t (&n_wide)[2]);
 
 // Plan set-up shared by the host-built and the device-built plan
 // (hnv_host.cpp): option defaults and limits, the plan's shape, and the

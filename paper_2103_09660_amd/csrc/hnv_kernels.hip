@@ -170,7 +170,6 @@ enum Mode : int {
     kAdjNode = 1,   // reverse sweep, node rows
     kAdjEdge = 2,   // reverse sweep, hyperedge rows, summing the per-node scalars of their members
     kAdjEdgeNoSum = 3,   // reverse sweep, hyperedge rows, without that sum
-    kSerial = 8,    // added to one of these: rows in gather_serial's order
 };
 
 struct GatherArgs {
@@ -180,7 +179,10 @@ struct GatherArgs {
     int32_t nb_split[2];      // finalize blocks per side (per panel)
     int32_t blocks_per_panel;
     int32_t n_long[2];        // leading items per side that a whole workgroup takes
-    int32_t serial;           // the order that serves gradients (gather_serial)
+    int32_t n_wide[2];        // items from here on take a lane group (the order that serves gradients; else none)
+    int32_t pieces;           // the order that serves gradients (k_gather's PIECES)
+    int32_t piece;            // neighbours per piece there
+    int32_t slot_pieces;      // partial slots per item there
     int32_t dp;               // columns per panel
     int64_t ld;               // row stride (elements) = d
     float omega;
@@ -311,6 +313,61 @@ HNV_DEV void gather_group(const int32_t *__restrict__ nb, const float *__restric
     }
 }
 
+// Bytes of neighbour rows a lane has in flight in gather_deep.
+constexpr int kDeepBytes = 256;
+
+// gather_group's sum, with more rows in flight (and no first ids at hand): for
+// levels that don't fill the chip.  Loads past the row's end take its first
+// neighbour again, since loads under a mask wait for each other here.
+template <typename T, int EPL, int G, bool SCALE, bool SCALAR>
+HNV_DEV void gather_deep(const int32_t *__restrict__ nb, const float *__restrict__ sc,
+                         const float *__restrict__ cvec, int start, int deg, const T *__restrict__ src, int64_t ld,
+                         int col, bool col_ok, int gl, int gbase, float (&acc)[EPL], float &csum)
+{
+    using S = Slice<T, EPL>;
+    constexpr int U = kDeepBytes / (int)sizeof(typename S::Raw);
+    int ix[kIdxRegs];
+    float sv[kIdxRegs];
+#pragma unroll
+    for (int r = 0; r < kIdxRegs; ++r) {
+        const int p = gl + r * G;
+        ix[r] = 0;
+        sv[r] = 1.0f;
+        if (p < deg) {
+            ix[r] = nb[start + p];
+            if (SCALE)
+                sv[r] = sc[start + p];
+        }
+    }
+    if (SCALAR) {
+#pragma unroll
+        for (int r = 0; r < kIdxRegs; ++r)
+            if (gl + r * G < deg)
+                csum += cvec[ix[r]];
+    }
+    const int first = __shfl(ix[0], gbase, kWave);
+    const T *base = src + (col_ok ? col : 0);
+    for (int j = 0; j < deg; j += U) {
+        typename S::Raw raw[U];
+        float s[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int q = j + k;
+            const int r = q / G;
+            const int xr = (r == 0) ? ix[0] : (r == 1) ? ix[1] : (r == 2) ? ix[2] : ix[3];
+            const float sr = (r == 0) ? sv[0] : (r == 1) ? sv[1] : (r == 2) ? sv[2] : sv[3];
+            const int lane_src = gbase + (q & (G - 1));
+            const int v = __shfl(xr, lane_src, kWave);
+            s[k] = SCALE ? __shfl(sr, lane_src, kWave) : 1.0f;
+            raw[k] = S::load(base + (int64_t)(q < deg ? v : first) * ld);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (j + k < deg)
+                accumulate<SCALE, T, EPL>(acc, s[k], raw[k]);
+    }
+}
+
 // A whole wavefront gathers `len` neighbours: group g takes neighbours
 // g, g + Q, g + 2Q, ... (Q = 64 / G), then the Q group sums are added with an
 // xor butterfly (every lane ends with the same, order-fixed total).  The
@@ -377,81 +434,6 @@ HNV_DEV void gather_wave(const int32_t *__restrict__ nb, const float *__restrict
     }
 }
 
-// A row of a wavefront-tier item by one wavefront, in the order that serves
-// gradients (SERIAL): up to kSerialRow neighbours one after another by the first
-// lane group, more as gather_wave in pieces of kSerialPiece, group g adding the
-// pieces g, g + Q, ..  The sums don't depend on the level's tiering then.  The
-// chain of a row of up to 64 neighbours is its loads, eight in flight: a training
-// step of 10 sweeps at each of five levels (20K nodes / 8K hyperedges, FP32, d =
-// 64) takes 2,040 us, and 1,700 in k_gather's order.
-constexpr int kSerialRow = 64;
-constexpr int kSerialPiece = 512;
-
-template <typename T, int EPL, int G, bool SCALE, bool SCALAR>
-HNV_DEV void gather_serial(const int32_t *__restrict__ nb, const float *__restrict__ sc,
-                           const float *__restrict__ cvec, int start, int len, const T *__restrict__ src, int64_t ld,
-                           int col, bool col_ok, int lane, int g, float (&acc)[EPL], float &csum)
-{
-    using S = Slice<T, EPL>;
-    constexpr int Q = kWave / G;
-    if (len <= kSerialRow) {
-        int my_nb = 0;
-        float my_s = 1.0f;
-        if (lane < len) {
-            my_nb = nb[start + lane];
-            if (SCALE)
-                my_s = sc[start + lane];
-            if (SCALAR)
-                csum += cvec[my_nb];
-        }
-        for (int j = 0; j < len; j += 2 * kUnroll) {
-            typename S::Raw raw[2 * kUnroll];
-            float s[2 * kUnroll];
-#pragma unroll
-            for (int k = 0; k < 2 * kUnroll; ++k) {
-                const int v = __shfl(my_nb, (j + k) & (kWave - 1), kWave);
-                s[k] = SCALE ? __shfl(my_s, (j + k) & (kWave - 1), kWave) : 1.0f;
-                if (j + k < len && col_ok)
-                    raw[k] = S::load(src + (int64_t)v * ld + col);
-            }
-            if (col_ok) {
-#pragma unroll
-                for (int k = 0; k < 2 * kUnroll; ++k)
-                    if (j + k < len)
-                        accumulate<SCALE, T, EPL>(acc, s[k], raw[k]);
-            }
-        }
-        if (SCALAR) {
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1)
-                csum += __shfl_xor(csum, off, kWave);
-        }
-        return;
-    }
-    if (len <= kSerialPiece) {
-        gather_wave<T, EPL, G, SCALE, SCALAR>(nb, sc, cvec, start, len, src, ld, col, col_ok, lane, g, acc, csum);
-        return;
-    }
-    for (int p = 0; p * kSerialPiece < len; ++p) {
-        float piece[EPL], c = 0.0f;
-        zero(piece);
-        gather_wave<T, EPL, G, SCALE, SCALAR>(nb, sc, cvec, start + p * kSerialPiece,
-                                              min(kSerialPiece, len - p * kSerialPiece), src, ld, col, col_ok, lane, g,
-                                              piece, c);
-        csum += c;
-        if (p % Q == g) {
-#pragma unroll
-            for (int i = 0; i < EPL; ++i)
-                acc[i] += piece[i];
-        }
-    }
-#pragma unroll
-    for (int off = G; off < kWave; off <<= 1)
-#pragma unroll
-        for (int i = 0; i < EPL; ++i)
-            acc[i] += __shfl_xor(acc[i], off, kWave);
-}
-
 // acc (and csum) of the workgroup's wavefronts added in order, into
 // wavefront 0 (its first lane group).  Every thread of the block calls it once.
 template <int EPL, int G, bool SCALAR>
@@ -474,6 +456,44 @@ HNV_DEV void block_sum(float (&acc)[EPL], float &csum, int wave, int lane)
             if (SCALAR)
                 csum += part[w][lane][EPL];
         }
+    }
+}
+
+// acc (and csum) of the first n wavefronts, a piece of a row each, added as
+// k_finalize adds partial slots: group g takes the pieces g, g + Q, .., the
+// groups are added by a butterfly.  Into wavefront 0; every thread of the block
+// calls it once.
+template <int EPL, int G, bool SCALAR>
+HNV_DEV void sum_pieces(float (&acc)[EPL], float &csum, int n, int wave, int lane)
+{
+    __shared__ float part[kWavesPerBlock][G][EPL + 1];
+    if (lane < G) {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+            part[wave][lane][i] = acc[i];
+        if (SCALAR)
+            part[wave][lane][EPL] = csum;
+    }
+    __syncthreads();
+    if (wave != 0)
+        return;
+    const int g = lane / G, gl = lane % G;
+    zero(acc);
+    csum = 0.0f;
+    for (int k = g; k < n; k += kWave / G) {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+            acc[i] += part[k][gl][i];
+        if (SCALAR && gl == 0)
+            csum += part[k][gl][EPL];
+    }
+#pragma unroll
+    for (int off = G; off < kWave; off <<= 1) {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+            acc[i] += __shfl_xor(acc[i], off, kWave);
+        if (SCALAR)
+            csum += __shfl_xor(csum, off, kWave);
     }
 }
 
@@ -702,11 +722,25 @@ HNV_DEV void block_resid(const GatherArgs &a, double r2, int64_t lb)
 // main kernel: wavefront tier + lane-group tier of both sides, all panels
 // ---------------------------------------------------------------------------
 
-template <typename T, int EPL, int G, int MODES, bool FUSED, bool CTL>
+// PIECES (1 and 2): the order of sums of the calls that serve gradients
+// (hnv_sweeps and the reverse sweeps).  The log-weight gradients of a small hierarchy's finest
+// level are differences of nearly equal sums, once the coarser levels have
+// smoothed the embedding: their FP32 error is 2e-4 to 4e-4, and another order
+// alone moves them by 2e-5 to 8e-5.  So this one doesn't depend on a level's
+// tiers: rows of up to lane_most (64) neighbours are added one after another by a
+// lane group, longer ones by a wavefront, 512 neighbours (a piece) at a time, and
+// their pieces as sum_pieces and k_finalize do.  The lists are the level's, cut
+// by length: items of more than a piece take a workgroup, a piece per wavefront,
+// items of up to lane_most neighbours a lane group each, as lane-group rows do, but
+// with all 64 neighbours' loads in four batches (levels with such items don't fill
+// the chip; PIECES = 1 is for levels without).
+// Against a wavefront per item of any length in that order, a training step with
+// hubs (8K nodes / 4K hyperedges, FP32, d = 128, 4 sweeps at each of six levels)
+// takes 2,470 us instead of 6,120, without (36K / 25K, d = 256, 7 sweeps at each
+// of three) 3,950 instead of 6,760.
+template <typename T, int EPL, int G, int MODE, bool FUSED, bool CTL, int PIECES>
 __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
 {
-    constexpr int MODE = MODES & ~kSerial;
-    constexpr bool SERIAL = (MODES & kSerial) != 0;
     const int64_t lb = linear_block();
     if (lb >= a.n_blocks)
         return;
@@ -754,14 +788,30 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
     if ((MODE == kAdjNode && side != 1) || ((MODE == kAdjEdge || MODE == kAdjEdgeNoSum) && side != 0))
         return;
 
+    const Item *lane_items = Sd.small;
+    int n_lane_items = Sd.n_small;
+    bool listed = true;   // a lane group's item of the lane-group tier: its first ids and coarse row are known
+    if constexpr (PIECES == 2) {
+        const int n_long = a.n_long[side], n_wide = a.n_wide[side];
+        const int wide_blocks = n_long + (n_wide - n_long + kWavesPerBlock - 1) / kWavesPerBlock;
+        if (tier == 0 && b >= wide_blocks) {
+            tier = 1;
+            b -= wide_blocks;
+            lane_items = Sd.chunks + n_wide;
+            n_lane_items = Sd.n_chunks - n_wide;
+            listed = false;
+        }
+    }
+
     if (tier == 0) {
         // The first n_long blocks take one item each: every wavefront gathers
-        // a quarter of its neighbours, and wavefront 0 adds the others' sums
-        // in order and finishes the row.  The other items take a wavefront each.
+        // a quarter of its neighbours (PIECES: a piece), and wavefront 0 adds
+        // the others' sums in order and finishes the row.  The other items take
+        // a wavefront each.
         const int n_long = a.n_long[side];
         const bool whole_block = b < n_long;   // uniform over the block
         const int item = whole_block ? b : n_long + (b - n_long) * kWavesPerBlock + wave;
-        const bool valid = item < Sd.n_chunks;   // uniform over the wavefront
+        const bool valid = item < (PIECES ? a.n_wide[side] : Sd.n_chunks);   // uniform over the wavefront
         Item c{0, 0, 0, 0};
         if (valid)
             c = Sd.chunks[item];
@@ -774,39 +824,36 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
             load_own<T, EPL, MODE>(self, a, mats, c.row, zrow, srow, c.len, col);
         }
         int start = c.start, len = c.len;
-        if constexpr (SERIAL) {   // (a long item's first wavefront takes it alone)
-            if (mine) {
-                if (use_scale)
-                    gather_serial<T, EPL, G, true, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g,
-                                                            acc, csum);
-                else
-                    gather_serial<T, EPL, G, false, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane,
-                                                             g, acc, csum);
-            }
-        } else {
-            if (whole_block) {
-                const int per = (c.len + kWavesPerBlock - 1) / kWavesPerBlock;
-                start += wave * per;
-                len = max(0, min(per, c.len - wave * per));
-            }
-            if (use_scale)
-                gather_wave<T, EPL, G, true, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
-                                                      csum);
-            else
-                gather_wave<T, EPL, G, false, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
-                                                       csum);
-            if (whole_block)
-                block_sum<EPL, G, kScalar>(acc, csum, wave, lane);
+        if (whole_block) {
+            const int per = PIECES ? a.piece : (c.len + kWavesPerBlock - 1) / kWavesPerBlock;
+            start += wave * per;
+            len = max(0, min(per, c.len - wave * per));
         }
-        if (mine) {
+        if (use_scale)
+            gather_wave<T, EPL, G, true, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
+                                                  csum);
+        else
+            gather_wave<T, EPL, G, false, kScalar>(nb, sc, a.cvec, start, len, src, a.ld, col, col_ok, lane, g, acc,
+                                                   csum);
+        int64_t slot = c.aux;
+        bool stores = mine;
+        if constexpr (PIECES) {   // a slot per piece
+            slot = (int64_t)c.aux * a.slot_pieces + (whole_block ? wave : 0);
+            stores = valid && len > 0;
+            if (whole_block && whole)   // uniform over the block
+                sum_pieces<EPL, G, kScalar>(acc, csum, (c.len + a.piece - 1) / a.piece, wave, lane);
+        } else if (whole_block) {
+            block_sum<EPL, G, kScalar>(acc, csum, wave, lane);
+        }
+        if (whole ? mine : stores) {
             if (!whole) {
                 if (g == 0 && col_ok) {
-                    float *pp = a.partials + (int64_t)c.aux * a.pstride + col;
+                    float *pp = a.partials + slot * a.pstride + col;
 #pragma unroll
                     for (int i = 0; i < EPL; i += 4)
                         *reinterpret_cast<float4 *>(pp + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
                     if (kScalar && gl == 0)
-                        a.partials[(int64_t)c.aux * a.pstride + a.ld] = csum;
+                        a.partials[slot * a.pstride + a.ld] = csum;
                 }
             } else if (MODE == kFwd) {
                 if (g == 0)
@@ -820,25 +867,34 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
     } else {
         for (int rr = 0; rr < kRowsPerGroup; ++rr) {
             const int item = (b * kRowsPerGroup + rr) * (kBlock / G) + (int)(threadIdx.x / G);
-            const bool valid = item < Sd.n_small;
+            const bool valid = item < n_lane_items;
             Item it{0, 0, 0, 0};
             int my_id = 0;   // lane gl < kInlineIds: the row's neighbour gl, loaded with the item
             if (valid) {
-                it = Sd.small[item];
-                if (gl < kInlineIds && G >= kInlineIds)
+                it = lane_items[item];
+                if (gl < kInlineIds && G >= kInlineIds && listed)
                     my_id = (FUSED ? Sd.small_cids : Sd.small_ids)[item].id[gl];
             }
             const int zrow = Sd.row_base + it.row;
             Own<T, EPL> self{};
             if (valid && col_ok) {
-                const int64_t srow = (MODE == kFwd && (FUSED || a.self_mapped)) ? (int64_t)it.aux : (int64_t)zrow;
+                const int64_t srow = !(MODE == kFwd && (FUSED || a.self_mapped)) ? zrow
+                                     : listed                                    ? it.aux
+                                                                                 : a.rowmap[zrow];
                 load_own<T, EPL, MODE>(self, a, mats, it.row, zrow, srow, it.len, col);
             }
             if (rr > 0) {
                 zero(acc);
                 csum = 0.0f;
             }
-            if (use_scale)
+            if (PIECES == 2 && !listed) {   // uniform over the block
+                if (use_scale)
+                    gather_deep<T, EPL, G, true, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
+                                                          g * G, acc, csum);
+                else
+                    gather_deep<T, EPL, G, false, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
+                                                           g * G, acc, csum);
+            } else if (use_scale)
                 gather_group<T, EPL, G, true, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
                                                        g * G, my_id, acc, csum);
             else
@@ -914,14 +970,15 @@ __global__ __launch_bounds__(kBlock) void k_finalize(GatherArgs a)
         }
         // kSlotsInFlight slots' loads go out together (slots past the row's
         // end re-read its first slot) and are added in slot order
-        const float *first = a.partials + (int64_t)sp.first_slot * a.pstride;
-        for (int k0 = g; k0 < sp.n_slots; k0 += Q * kSlotsInFlight) {
+        const float *first = a.partials + (int64_t)sp.first_slot * (a.pieces ? a.slot_pieces : 1) * a.pstride;
+        const int n_slots = a.pieces ? (sp.deg + a.piece - 1) / a.piece : sp.n_slots;
+        for (int k0 = g; k0 < n_slots; k0 += Q * kSlotsInFlight) {
             float4 x[kSlotsInFlight][EPL / 4];
             float c[kSlotsInFlight];
 #pragma unroll
             for (int u = 0; u < kSlotsInFlight; ++u) {
                 const int k = k0 + u * Q;
-                const float *pp = first + (int64_t)(k < sp.n_slots ? k : 0) * a.pstride;
+                const float *pp = first + (int64_t)(k < n_slots ? k : 0) * a.pstride;
 #pragma unroll
                 for (int i = 0; i < EPL; i += 4)
                     x[u][i / 4] = *reinterpret_cast<const float4 *>(pp + (col_ok ? col : 0) + i);
@@ -929,7 +986,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(GatherArgs a)
             }
 #pragma unroll
             for (int u = 0; u < kSlotsInFlight; ++u) {
-                const bool ok = k0 + u * Q < sp.n_slots;
+                const bool ok = k0 + u * Q < n_slots;
 #pragma unroll
                 for (int i = 0; i < EPL; i += 4) {
                     acc[i] = ok ? acc[i] + x[u][i / 4].x : acc[i];
@@ -1683,9 +1740,11 @@ static hnv_status ensure_reverse_scales(hnv_plan *p, int level, hipStream_t s)
     return st;
 }
 
-static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp)
+static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp, bool pieces)
 {
     GatherArgs a{};
+    a.piece = p->piece;
+    a.slot_pieces = p->slot_pieces;
     a.side[0] = L.side[0];
     a.side[1] = L.side[1];
     if (L.unit_w)
@@ -1693,12 +1752,15 @@ static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp)
     const int rows_per_block = kRowsPerGroup * kBlock / G;
     int32_t per_panel = 0;
     for (int s = 0; s < 2; ++s) {
-        a.n_long[s] = L.n_long[s];
-        a.nb_chunk[s] = a.n_long[s] + (int32_t)blocks_for(L.n_chunks[s] - a.n_long[s], kWavesPerBlock);
+        a.n_long[s] = pieces ? L.n_pieced[s] : L.n_long[s];
+        a.n_wide[s] = pieces ? L.n_wide[s] : L.n_chunks[s];
+        a.nb_chunk[s] = a.n_long[s] + (int32_t)blocks_for(a.n_wide[s] - a.n_long[s], kWavesPerBlock) +
+                        (int32_t)blocks_for(L.n_chunks[s] - a.n_wide[s], kBlock / G);
         a.nb_small[s] = (int32_t)blocks_for(L.n_small[s], rows_per_block);
         a.nb_split[s] = (int32_t)blocks_for(L.n_splits[s], kWavesPerBlock);
         per_panel += a.nb_chunk[s] + a.nb_small[s];
     }
+    a.pieces = !pieces ? 0 : L.n_wide[0] < L.n_chunks[0] || L.n_wide[1] < L.n_chunks[1] ? 2 : 1;
     a.blocks_per_panel = per_panel;
     a.dp = dp;
     a.ld = p->d;
@@ -1755,7 +1817,7 @@ struct ProfScope {
     }
 };
 
-template <typename T, int EPL, int G, int MODE, bool FUSED, bool CTL, bool SERIAL>
+template <typename T, int EPL, int G, int MODE, bool FUSED, bool CTL, int PIECES>
 static void launch_pair(const GatherArgs &a, int panels, hipStream_t s, ProfScope *ps)
 {
     const int64_t main_blocks = (int64_t)a.blocks_per_panel * panels;
@@ -1764,7 +1826,7 @@ static void launch_pair(const GatherArgs &a, int panels, hipStream_t s, ProfScop
     if (main_blocks) {
         GatherArgs m = a;
         m.n_blocks = main_blocks;
-        k_gather<T, EPL, G, SERIAL ? MODE | kSerial : MODE, FUSED, CTL><<<fold_grid(main_blocks), kBlock, 0, s>>>(m);
+        k_gather<T, EPL, G, MODE, FUSED, CTL, PIECES><<<fold_grid(main_blocks), kBlock, 0, s>>>(m);
     }
     if (ps)
         ps->end();
@@ -1779,30 +1841,30 @@ static void launch_pair(const GatherArgs &a, int panels, hipStream_t s, ProfScop
 
 // Instantiated lane layouts: BF16 always 8 elements per lane; FP32 4 per
 // lane, or 8 for full-width rows of 128 columns or more (G = 16 .. 64).
-template <typename T, int MODE, bool FUSED, bool CTL = false, bool SERIAL = false>
+template <typename T, int MODE, bool FUSED, bool CTL = false, int PIECES = (MODE == kFwd ? 0 : 1)>
 static hnv_status dispatch_g(int G, int EPL, const GatherArgs &a, int panels, hipStream_t s, ProfScope *ps)
 {
-    if constexpr (!CTL && !SERIAL && MODE != kAdjEdge) {
-        if (a.serial)
-            return dispatch_g<T, MODE, FUSED, false, true>(G, EPL, a, panels, s, ps);
+    if constexpr (!CTL && PIECES < 2) {
+        if (a.pieces > PIECES)
+            return dispatch_g<T, MODE, FUSED, false, PIECES + 1>(G, EPL, a, panels, s, ps);
     }
     constexpr int E = 16 / (int)sizeof(T);
     if (EPL == E) {
         switch (G) {
-        case 1: launch_pair<T, E, 1, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
-        case 2: launch_pair<T, E, 2, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
-        case 4: launch_pair<T, E, 4, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
-        case 8: launch_pair<T, E, 8, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
-        case 16: launch_pair<T, E, 16, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
-        case 32: launch_pair<T, E, 32, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
-        case 64: launch_pair<T, E, 64, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 1: launch_pair<T, E, 1, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
+        case 2: launch_pair<T, E, 2, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
+        case 4: launch_pair<T, E, 4, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
+        case 8: launch_pair<T, E, 8, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
+        case 16: launch_pair<T, E, 16, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
+        case 32: launch_pair<T, E, 32, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
+        case 64: launch_pair<T, E, 64, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
         default: return fail(HNV_EUNSUPPORTED, "lane group width");
         }
     } else if (E == 4 && EPL == 8) {
         switch (G) {
-        case 16: launch_pair<T, 8, 16, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
-        case 32: launch_pair<T, 8, 32, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
-        case 64: launch_pair<T, 8, 64, MODE, FUSED, CTL, SERIAL>(a, panels, s, ps); break;
+        case 16: launch_pair<T, 8, 16, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
+        case 32: launch_pair<T, 8, 32, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
+        case 64: launch_pair<T, 8, 64, MODE, FUSED, CTL, PIECES>(a, panels, s, ps); break;
         default: return fail(HNV_EUNSUPPORTED, "lane group width");
         }
     } else {
@@ -1874,13 +1936,12 @@ static hnv_status reduce_resid(const double *part, int64_t n, int batch, int64_t
 // reduce_resid to reduce with the level's next sweeps.
 static hnv_status run_sweep(hnv_plan *p, int level, const void *src, void *dst, float omega, bool fused,
                             double *resid_out, hipStream_t s, SweepCtl *ctl = nullptr,
-                            const SweepScratch *scr = nullptr, int resid_slot = -1, bool serial = false)
+                            const SweepScratch *scr = nullptr, int resid_slot = -1, bool pieces = false)
 {
     LevelPlan &L = p->lv[level];
     const SweepScratch sc = scr ? *scr : plan_scratch(p);
-    GatherArgs a = base_args(p, L, p->g_fwd, p->dp);
+    GatherArgs a = base_args(p, L, p->g_fwd, p->dp, pieces);
     a.partials = sc.partials;
-    a.serial = serial;
     a.omega = omega;
     a.src = src;
     a.self_src = src;
@@ -2029,16 +2090,6 @@ static hnv_status run_resident(hnv_plan *p, int level, const void *src, void *ds
     return reduce_resid(p->resident_part, mb, n, mb, resid_out, plan_scratch(p), nullptr, level, s);
 }
 
-// Levels of up to this many rows take gather_serial's order in the calls that
-// serve gradients (hnv_sweeps and hnv_sweeps_adjoint).  The log-weight gradients
-// of a small hierarchy's finest level are differences of nearly equal sums, once
-// the coarser levels have smoothed the embedding: their FP32 error is 2e-4 to
-// 4e-4, and the tiering by workgroups alone, another order, moved them by 3e-5
-// to 8e-5 (20K nodes).  In larger levels one wavefront per item would be the
-// slower form and the difference is 1e-7 (500K nodes).
-constexpr int64_t kSerialRows = 200000;
-static bool serial_level(const LevelPlan &L) { return L.rows <= kSerialRows; }
-
 // The projection onto `level` (zc -> zf); with ctl (an early-stop
 // refinement) the matrices come from the control block, which then takes
 // the projection's output as the latest iterate.
@@ -2165,8 +2216,9 @@ extern "C" hnv_status hnv_sweep(hnv_plan *plan, int level, const void *z_in, voi
 // The sweeps between two kept states in one call: a call per sweep from a
 // scripting language takes about 9 us, more than a sweep of a small level (a
 // training step of 10 sweeps at each of five levels, 20K nodes / 8K hyperedges,
-// d = 64, with hnv_sweeps_adjoint: 3,640 -> 2,040 us).  Results that aren't kept go to the plan's scratch embedding and the
-// next kept result in turn.
+// d = 64, with hnv_sweeps_adjoint and the shorter chains of k_gather's PIECES = 2:
+// 3,640 -> 2,030 us).  Results that aren't kept go to the plan's scratch embedding
+// and the next kept result in turn.
 extern "C" hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, void *const *z_out, int n,
                                  float omega, int from_coarse, void *stream)
 {
@@ -2194,7 +2246,6 @@ extern "C" hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, vo
         return fail(HNV_EINVAL, "from_coarse at the coarsest level");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const void *cur = z_in;
-    const bool serial = serial_level(plan->lv[level]);
     for (int i = 0; i < n; ) {
         int end = i;   // the run of sweeps up to the next kept result
         while (!z_out[end])
@@ -2202,7 +2253,7 @@ extern "C" hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, vo
         for (; i <= end; ++i) {   // (alternating, so that the last one writes z_out[end])
             void *out = (end - i) % 2 == 0 ? z_out[end] : plan->zbuf;
             if ((st = run_sweep(plan, level, cur, out, omega, from_coarse && i == 0, nullptr, s, nullptr, nullptr, -1,
-                                serial)) != HNV_OK)
+                                true)) != HNV_OK)
                 return st;
             cur = out;
         }
@@ -2481,16 +2532,14 @@ extern "C" hnv_status hnv_refine(hnv_plan *plan, const void *z_coarsest, void *z
 // to the plan's per-node scratch and a finish pass subtracts omega times
 // their member sums.
 static hnv_status run_adjoint(hnv_plan *plan, int level, const void *g_in, void *g_out, const void *z_prev,
-                              const void *z_cur, float *dw, float *node_acc, float omega, int wgrad, hipStream_t s,
-                              bool serial = false)
+                              const void *z_cur, float *dw, float *node_acc, float omega, int wgrad, hipStream_t s)
 {
     LevelPlan &L = plan->lv[level];
     if (hnv_status st = ensure_reverse_scales(plan, level, s); st != HNV_OK)
         return st;
     const int G = plan->g_full, E = plan->epl_full;
     const bool edge_first = plan->opts.order == HNV_ORDER_EDGE_FIRST;
-    GatherArgs a = base_args(plan, L, G, plan->d);
-    a.serial = serial;
+    GatherArgs a = base_args(plan, L, G, plan->d, true);
     a.omega = omega;
     a.src = g_in;
     a.self_src = g_in;
@@ -2603,8 +2652,8 @@ extern "C" hnv_status hnv_sweeps_adjoint(hnv_plan *plan, int level, const void *
             return st;
     for (int j = 0; j < n; ++j)
         if ((st = run_adjoint(plan, level, j == 0 ? g_in : g_out[j - 1], g_out[j], states[n - 1 - j], states[n - j],
-                              dw_accum, node_accum, omega, wgrad ? 2 : 0, reinterpret_cast<hipStream_t>(stream),
-                              serial_level(L))) != HNV_OK)
+                              dw_accum, node_accum, omega, wgrad ? 2 : 0,
+                              reinterpret_cast<hipStream_t>(stream))) != HNV_OK)
             return st;
     return HNV_OK;
 }
