@@ -100,7 +100,8 @@ typedef struct {
     int32_t panel_cols;  /* columns per pass of a forward sweep (divides d, multiple of 8) */
     int32_t small_max;   /* rows with at most this many neighbours go to a lane group (capped
                             at 4 lanes' worth of indices per lane of the group); default 8, 16
-                            or 64 by the level's size, 64 where chunk is given */
+                            or 64 by the bytes that the level's sweeps gather, 64 where chunk
+                            is given */
     int32_t chunk;       /* neighbours per wavefront or workgroup work item; longer rows are split
                             (default 2048) */
     int32_t order;       /* HNV_ORDER_*: update order of a sweep (Section 3.3 describes both; the

@@ -65,27 +65,35 @@ static constexpr int kDefaultChunk = 2048;
 static constexpr int kDefaultPiece = 512;
 static_assert(kDefaultChunk == kWavesPerBlock * kDefaultPiece, "a piece per wavefront of a workgroup");
 
-// Levels of up to kIdleRows rows do not fill the chip for long, and the
-// longest chain of dependent loads sets a sweep's time there: every item of
-// the wavefront tier takes a workgroup, and rows leave the lane-group tier
-// early.  Larger levels hide the chains behind other rows and lose by idle
-// lanes instead, so only items of more than kLongItem neighbours take a
-// workgroup there (with all of them, BF16 refinement went from 151.1 to 151.8
-// ms at 2M nodes, and from 12.9 to 14.0 ms in the whole method at 700K nodes,
-// d = 64).
-static constexpr int64_t kIdleRows = 98304;
-static constexpr int kLongItem = 256;
+// A sweep takes as long as its longest chain of dependent loads, or as the
+// rows it gathers take at full rate, whichever is longer.  So the tiers follow
+// the bytes that a level's gathers read (2 nnz rows of d elements): while they
+// are few, rows leave the lane-group tier early and shorter items take a
+// workgroup; where they are many, a short row in a wavefront or workgroup of
+// its own only leaves lanes idle.  Rows of more than 12 neighbours on average
+// fill the chip from 80 MB on, where most of them would leave the lane-group
+// tier.  A sweep in us with lane-group bound / workgroup items of more than
+// 8/64, 16/64, 16/256 and 64/256 neighbours:
+//   12K rows, 0.20M incidences, FP32, d = 128 (200 MB)       26, 26, 26, 31
+//   66K rows, 0.85M incidences, FP32, d = 16 (108 MB)        26, 26, 26, 26
+//   90K rows, 0.87M incidences, FP32, d = 256 (1.8 GB)       200, 203, 203, 166
+//   17K rows, 0.27M incidences, BF16, d = 256 (278 MB)       47, 45, 43, 37
+// and over 587 levels of 300 to 400K rows these bounds take 0.72 of the time of
+// a bound of 64 with a wavefront per 512 neighbours (1.10 at most), where
+// bounds by the number of rows took 0.80 (2.6 at most).  Given chunks keep the
+// bound of 64.
+static constexpr double kFewBytes = 40e6, kSomeBytes = 80e6, kManyBytes = 320e6;
+// Up to this many items (times panels) all take a workgroup (what launches from
+// LDS reproduce): 1.02 times the best at 512 to 1,024 of them, 1.14 at 2,048 to
+// 4,096.
+static constexpr int kFewItems = 1024;
 
-// The lane-group tier bound of a level (given chunks keep 64).  A sweep in us
-// with bounds 8 / 16 / 64 (FP32 d = 64, then BF16 d =
-// 128): 12K rows 6.9 / 7.4 / 14.4, 7.6 / 8.0 / 16.5; 28K rows 8.0 / 9.0 /
-// 16.6, 8.9 / 9.4 / 18.4; 60K rows 15.4 / 14.0 / 20.4, 16.8 / 14.9 / 21.7;
-// 130K rows 39.8 / 32.7 / 31.7, 42.2 / 33.8 / 32.1.
-static void default_tiers(LevelPlan &L)
+static void default_tiers(LevelPlan &L, double bytes, int panels)
 {
-    L.small_max = L.rows <= kIdleRows / 3 ? 8 : L.rows <= kIdleRows ? 16 : kDefaultSmallMax;
-    L.long_len = kLongItem;
-    L.few_items = L.rows <= kIdleRows ? std::numeric_limits<int>::max() : 0;
+    const bool dense = 2 * L.nnz > 12 * L.rows;
+    L.small_max = bytes <= kFewBytes ? 8 : bytes <= kSomeBytes || (bytes <= kManyBytes && !dense) ? 16 : kDefaultSmallMax;
+    L.long_len = bytes <= kSomeBytes ? 64 : 256;
+    L.few_items = bytes <= kSomeBytes ? kFewItems / panels : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -852,7 +860,7 @@ void init_plan_shape(hnv_plan *p, const std::vector<LevelShape> &shape, int d, h
         L.has_coarse = (l + 1 < n_levels);
         L.rows_coarse = L.has_coarse ? shape[l + 1].nV + shape[l + 1].nE : 0;
         L.unit_w = shape[l].unit_w;
-        default_tiers(L);
+        default_tiers(L, 2.0 * (double)L.nnz * d * elem, p->panels);
         if (o.small_max > 0 || o.chunk != kDefaultChunk)
             L.small_max = p->lane_most;
         L.small_max = std::min(L.small_max, p->lane_most);

@@ -1,0 +1,36 @@
+"""The default degree tiers of small and middle levels take no longer than lane
+groups of up to 64 neighbours and a wavefront per 512, whatever the shape of the
+hypergraph: many rows of a middle length (where a workgroup or a wavefront each
+only leaves lanes idle), few long ones, wide and narrow rows.  A quarter over is
+the margin for noise; a workgroup for each row of 9 (17) to 64 neighbours took up
+to 2.5 times as long."""
+import numpy as np
+import pytest
+
+from synth.hypergraph import Hypergraph
+from tests.test_gpu_gradient_order import _time
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nodes,edges,largest,d,dtype", [
+    (3000, 1500, 60, 64, "f32"), (9000, 9000, 20, 256, "f32"), (20000, 10000, 40, 64, "f32"),
+    (20000, 30000, 60, 128, "bf16"), (30000, 60000, 30, 32, "f32"), (60000, 30000, 40, 64, "f32"),
+    (60000, 35000, 24, 16, "bf16")])
+def test_default_tiers_are_not_slower(nodes, edges, largest, d, dtype):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2103_09660_amd as H
+    print("tier rule", nodes, edges, largest, d, dtype, flush=True)
+    rng = np.random.default_rng(nodes + edges)
+    lists = [np.unique(rng.integers(0, nodes, k)).astype(np.int32) for k in rng.integers(2, largest + 1, edges)]
+    ptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    hg = Hypergraph(nodes, edges, ptr, np.concatenate(lists), None)
+    hier = H.Hierarchy.build(hg.n_nodes, hg.n_edges, hg.edge_ptr, hg.edge_idx, hg.edge_w, 0)
+    took = []
+    for options in ({}, {"small_max": 64, "chunk": 512}):
+        plan = H.Plan(hier, d, dtype, options=options)
+        z = torch.randn(nodes + edges, d, device="cuda").to(plan.torch_dtype)
+        took.append(_time(lambda: plan.refine(z, [20], 0.5)))
+    assert took[0] <= 1.25 * took[1], f"{took[0]:.3f} ms by the default tiers, {took[1]:.3f} ms by plain ones"
