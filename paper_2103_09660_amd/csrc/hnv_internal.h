@@ -117,8 +117,11 @@ namespace hnv {
 // Sweeps of one level whose residuals a fixed-count refinement reduces
 // together (their per-block partials wait in as many slots).
 constexpr int kResidBatch = 8;
-// Per-block residual partials one workgroup of a residual stage sums.
+// Per-block residual partials one workgroup of a residual stage sums, and the
+// most that one workgroup takes where that ends the reduction: each stage is a
+// launch of about 4 us, as much as a sweep of a small level.
 constexpr int kResidPer = kBlock * 8;
+constexpr int kResidLast = 4 * kResidPer;
 // Sweeps of a small level that one launch runs from LDS when residuals are
 // wanted, and the LDS bytes that it takes.
 constexpr int kResidentBatch = 2 * kResidBatch;

@@ -1019,9 +1019,9 @@ __global__ __launch_bounds__(kBlock) void k_finalize(GatherArgs a)
         block_resid(a, r2, lb);
 }
 
-// Residual reduction, one stage: block b sums partials [b*2048, (b+1)*2048)
-// (each thread eight strided loads, all in flight at once, added in a fixed
-// order, then a tree over the block) and writes one value; the last stage
+// Residual reduction, one stage: block b sums partials [b*per, (b+1)*per)
+// (each thread eight strided loads at a time, all in flight at once, added in a
+// fixed order, then a tree over the block) and writes one value; the last stage
 // (a single block) writes the square root.  In an early-stop refinement
 // (ctl != null) nothing runs once the level has stopped, and the last stage
 // instead stores the residual at the next packed position, counts the
@@ -1029,7 +1029,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(GatherArgs a)
 // the sweep's output the latest iterate.  Several sweeps' reductions run
 // side by side along blockIdx.y, sweep y reading part + y * part_stride and
 // writing out + y * out_stride (each in the order one sweep alone takes).
-__global__ __launch_bounds__(kBlock) void k_resid_stage(const double *__restrict__ part, int64_t n,
+__global__ __launch_bounds__(kBlock) void k_resid_stage(const double *__restrict__ part, int64_t n, int per,
                                                         int64_t part_stride, double *__restrict__ out,
                                                         int64_t out_stride, int final_sqrt, SweepCtl *ctl, int level)
 {
@@ -1038,14 +1038,18 @@ __global__ __launch_bounds__(kBlock) void k_resid_stage(const double *__restrict
     part += (int64_t)blockIdx.y * part_stride;
     out += (int64_t)blockIdx.y * out_stride;
     __shared__ double s[kBlock];
-    const int64_t base = (int64_t)blockIdx.x * kResidPer + threadIdx.x;
-    double x[8];
+    const int64_t first = (int64_t)blockIdx.x * per, end = min(first + per, n);
+    double sum = 0.0;
+    for (int64_t base = first; base < end; base += 8 * kBlock) {   // uniform
+        double x[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int64_t i = base + (int64_t)k * kBlock;
-        x[k] = (i < n) ? part[i] : 0.0;
+        for (int k = 0; k < 8; ++k) {
+            const int64_t i = base + threadIdx.x + (int64_t)k * kBlock;
+            x[k] = (i < end) ? part[i] : 0.0;
+        }
+        sum += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
     }
-    s[threadIdx.x] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+    s[threadIdx.x] = sum;
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w)
@@ -1910,17 +1914,17 @@ static hnv_status reduce_resid(const double *part, int64_t n, int batch, int64_t
     const double *in = part;
     int64_t stride = part_stride;
     int which = 0;
-    while (n > kResidPer) {
+    while (n > kResidLast) {
         const int64_t nb = blocks_for(n, kResidPer);
         double *o = sc.resid_stage + (int64_t)which * batch * sc.resid_stage_len;
-        k_resid_stage<<<dim3((unsigned)nb, (unsigned)batch), kBlock, 0, s>>>(in, n, stride, o, sc.resid_stage_len, 0,
-                                                                            ctl, level);
+        k_resid_stage<<<dim3((unsigned)nb, (unsigned)batch), kBlock, 0, s>>>(in, n, kResidPer, stride, o,
+                                                                            sc.resid_stage_len, 0, ctl, level);
         in = o;
         stride = sc.resid_stage_len;
         n = nb;
         which ^= 1;
     }
-    k_resid_stage<<<dim3(1, (unsigned)batch), kBlock, 0, s>>>(in, n, stride, out, 1, 1, ctl, level);
+    k_resid_stage<<<dim3(1, (unsigned)batch), kBlock, 0, s>>>(in, n, kResidLast, stride, out, 1, 1, ctl, level);
     return dev_check("residual kernels");
 }
 
