@@ -103,7 +103,8 @@ typedef struct {
                             or 64 by the bytes that the level's sweeps gather, 64 where chunk
                             is given */
     int32_t chunk;       /* neighbours per wavefront or workgroup work item; longer rows are split
-                            (default 2048) */
+                            (default 2048; levels with longer rows whose sweeps gather few bytes
+                            split rows of more than 1024, at 512) */
     int32_t order;       /* HNV_ORDER_*: update order of a sweep (Section 3.3 describes both; the
                             edge-first order is the text's SOR reading, two half-sweeps that may
                             run in place; the reverse sweep follows the plan's order) */

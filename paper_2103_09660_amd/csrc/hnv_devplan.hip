@@ -120,7 +120,8 @@ __device__ inline bool level_failed(const int *bad) { return bad && (bad[0] | ba
 // and keys missing from the list (rows without entries) get empty ranges.
 __global__ __launch_bounds__(kThreads) void k_offsets_sorted(const uint32_t *__restrict__ keys, int64_t n,
                                                              int64_t n_keys, const int *__restrict__ bad,
-                                                             int32_t *__restrict__ ptr)
+                                                             int32_t *__restrict__ ptr, int chunk,
+                                                             int32_t *__restrict__ hubs)
 {
     const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (j > n)
@@ -134,6 +135,8 @@ __global__ __launch_bounds__(kThreads) void k_offsets_sorted(const uint32_t *__r
     const int64_t hi = (j == n) ? n_keys : (int64_t)keys[j];
     for (int64_t v = lo + 1; v <= hi; ++v)
         ptr[v] = (int32_t)j;
+    if (hubs && j >= chunk && j < n && keys[j - chunk] == keys[j])
+        *hubs = 1;
 }
 
 // projection row map: node v -> rep(v); kept hyperedge -> n_nodes_c + rep(e);
@@ -165,20 +168,25 @@ __global__ __launch_bounds__(kThreads) void k_rowmap(const int32_t *__restrict__
 // Side 0's arrays: the offsets and the member lists as given, the weights (1
 // without any), and with a coarser level each member's coarse row (a node's row
 // maps to rep(v), so cidx = node_rep[idx]; 0 when the level failed its checks).
-// One launch: at 20K nodes each costs more than the arrays it copies.
+// One launch: at 20K nodes each costs more than the arrays it copies.  hubs (may
+// be null): 1 if a list is longer than a chunk.
 __global__ __launch_bounds__(kThreads) void k_side0(const int32_t *__restrict__ edge_ptr,
                                                     const int32_t *__restrict__ edge_idx,
                                                     const float *__restrict__ edge_w,
                                                     const int32_t *__restrict__ node_rep, int64_t n_edges,
                                                     int64_t nnz, const int *__restrict__ bad,
                                                     int32_t *__restrict__ ptr, int32_t *__restrict__ idx,
-                                                    int32_t *__restrict__ cidx, float *__restrict__ w)
+                                                    int32_t *__restrict__ cidx, float *__restrict__ w, int chunk,
+                                               int32_t *__restrict__ hubs)
 {
     const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (j <= n_edges)
         ptr[j] = edge_ptr[j];
-    if (j < n_edges)
+    if (j < n_edges) {
         w[j] = edge_w ? edge_w[j] : 1.0f;
+        if (hubs && (int64_t)edge_ptr[j + 1] - edge_ptr[j] > chunk)
+            *hubs = 1;
+    }
     if (j >= nnz)
         return;
     const int32_t v = edge_idx[j];
@@ -258,12 +266,19 @@ __device__ inline int side_of(const TierSides &T, int64_t p)
     return __builtin_amdgcn_readfirstlane((T.n == 2 && p0 >= T.s[1].off) ? 1 : 0);
 }
 
+// Rows of more than chunk neighbours, or of more than split_over if *hubs (a row
+// of more than a chunk was found), are cut into items of `cut`.
+struct TierCuts {
+    int32_t chunk, split_over, cut;
+    const int32_t *hubs;   // null: no
+};
+
 // Tier sort key of a side's row: small_max - degree for the lane-group tier,
 // small_max + 1 for longer rows, small_max + 2 for padding, plus the side
 // times small_max + 3.
 __device__ inline uint32_t tier_key_base(int sd, int small_max) { return (uint32_t)sd * (uint32_t)(small_max + 3); }
 
-__global__ __launch_bounds__(kThreads) void k_tier_keys(TierSides T, int small_max, int chunk,
+__global__ __launch_bounds__(kThreads) void k_tier_keys(TierSides T, int small_max, TierCuts C,
                                                         const int *__restrict__ bad, uint32_t *__restrict__ key,
                                                         TierCount *__restrict__ tc)
 {
@@ -281,7 +296,7 @@ __global__ __launch_bounds__(kThreads) void k_tier_keys(TierSides T, int small_m
     }
     const int32_t deg = level_failed(bad) ? 0 : S.ptr[r + 1] - S.ptr[r];
     const bool small = deg <= small_max;
-    const int32_t pc = small ? 0 : (deg + chunk - 1) / chunk;
+    const int32_t pc = small ? 0 : deg <= (C.hubs && *C.hubs ? C.split_over : C.chunk) ? 1 : (deg + C.cut - 1) / C.cut;
     key[p] = kb + (small ? (uint32_t)(small_max - deg) : (uint32_t)(small_max + 1));
     tc[p] = TierCount{pc, pc > 1 ? 1 : 0, pc > 1 ? pc : 0};
 }
@@ -374,7 +389,7 @@ __global__ __launch_bounds__(kThreads) void k_small_items(TierSides T, const int
 // with the sort key side * keys + item_key (a stable ascending
 // sort keeps the sides apart and puts each side's longest first; keys and
 // shift as chunk_keys and chunk_shift give them)
-__global__ __launch_bounds__(kThreads) void k_chunk_items(TierSides T, int chunk, int shift, int keys,
+__global__ __launch_bounds__(kThreads) void k_chunk_items(TierSides T, int chunk, int cut, int shift, int keys,
                                                           const TierCount *__restrict__ tc,
                                                           const TierCount *__restrict__ tpos,
                                                           Item *__restrict__ items, uint32_t *__restrict__ key,
@@ -392,8 +407,8 @@ __global__ __launch_bounds__(kThreads) void k_chunk_items(TierSides T, int chunk
     const TierCount at = tpos[p];
     for (int32_t k = 0; k < pc; ++k) {
         const int32_t pos = at.pieces + k;
-        const int32_t s = S.ptr[r] + k * chunk;
-        const int32_t len = min(chunk, S.ptr[r + 1] - s);
+        const int32_t s = S.ptr[r] + k * cut;
+        const int32_t len = min(pc == 1 ? chunk : cut, S.ptr[r + 1] - s);
         items[pos] = Item{r, s, len, pc == 1 ? -1 : at.slots + k};
         key[pos] = (uint32_t)(sd * keys + item_key(chunk, shift, len, pc > 1));
         id[pos] = pos;
@@ -450,11 +465,11 @@ __global__ __launch_bounds__(kThreads) void k_split_items(TierSides T, const Tie
 
 // Work-list bounds from the sizes alone (see the tiering rules above): rows
 // longer than small_max number at most nnz / (small_max + 1), each has at
-// most degree / chunk + 1 pieces, and only rows longer than chunk split.
+// most degree / cut + 1 pieces, and only rows longer than chunk split.
 LevelShape bound_shape(const hnv_plan *p, int level, const hnv_level_dev &lv, const hnv_level_dev *coarse)
 {
     const LevelPlan &L = p->lv[level];
-    const int small_max = L.small_max, chunk = p->opts.chunk;
+    const int small_max = L.small_max, chunk = L.chunk, cut = L.cut;
     LevelShape sh;
     sh.nV = lv.n_nodes;
     sh.nE = lv.n_edges;
@@ -468,13 +483,13 @@ LevelShape bound_shape(const hnv_plan *p, int level, const hnv_level_dev &lv, co
     for (int s = 0; s < 2; ++s) {
         const int64_t n_rows = s == 0 ? sh.nE : sh.nV;
         sh.n_small[s] = cap(n_rows);
-        sh.n_chunks[s] = cap(std::min<int64_t>(sh.nnz / chunk + sh.nnz / (small_max + 1) + 1, sh.nnz + 1));
-        sh.n_splits[s] = cap(sh.nnz / (chunk + 1) + 1);
+        sh.n_chunks[s] = cap(std::min<int64_t>(sh.nnz / cut + sh.nnz / (small_max + 1) + 1, sh.nnz + 1));
+        sh.n_splits[s] = cap(sh.nnz / (L.split_over + 1) + 1);
         // of an item that is long by its key (items of split rows may be shorter)
         const int shortest = chunk - (item_marks(p, L).key[0] << chunk_shift(chunk)) + 1;
         const int64_t many = sh.nnz / std::max(shortest, 1) + sh.n_splits[s] + 1;
         sh.n_long[s] = (int32_t)std::min<int64_t>(sh.n_chunks[s], std::max<int64_t>(many, L.few_items));
-        slots += 2 * (sh.nnz / chunk) + 1;
+        slots += sh.nnz / cut + sh.nnz / (L.split_over + 1) + 1;
     }
     sh.n_slots = cap(slots);
     return sh;
@@ -578,7 +593,7 @@ hnv_status scratch_layout(int64_t nnz, int64_t rows, int64_t n_chunks, int tier_
 // Kept ahead of the per-level temporaries.
 struct LevelMeta {
     int32_t flags[4];
-    int32_t marks[kItemMarks][2], pad[2];
+    int32_t marks[kItemMarks][2], hubs, pad;
     int64_t counts[8];
 };
 size_t meta_bytes(int n_levels) { return ((size_t)n_levels * sizeof(LevelMeta) + 255) & ~size_t(255); }
@@ -746,8 +761,8 @@ hnv_status bin_sort(uint32_t *ka, int32_t *va, uint32_t *kb, int32_t *vb, int64_
 // The tier keys, sort and scan of the sides T (one or two); counts[4 * side
 // + 0..3] and S.n_chunks on the device.  `bad`: the level's check flags
 // (null: checked already).
-hnv_status tier_scan(const TierSides &T, int small_max, int chunk, const int *bad, Scratch &S, int64_t *counts,
-                     hipStream_t s)
+hnv_status tier_scan(const TierSides &T, int small_max, const TierCuts &C, const int *bad, Scratch &S,
+                     int64_t *counts, hipStream_t s)
 {
     if (T.total == 0) {
         k_fill<<<1, kThreads, 0, s>>>(reinterpret_cast<int32_t *>(counts), 16, 0);
@@ -758,7 +773,7 @@ hnv_status tier_scan(const TierSides &T, int small_max, int chunk, const int *ba
     if (n_keys > kBinsMax)
         return fail(HNV_EUNSUPPORTED, "small_max above the tier sort's key range");
     const TierArrays &A = S.tier;
-    k_tier_keys<<<grid_for(T.total), kThreads, 0, s>>>(T, small_max, chunk, bad, A.key_a, A.tc);
+    k_tier_keys<<<grid_for(T.total), kThreads, 0, s>>>(T, small_max, C, bad, A.key_a, A.tc);
     // the lane-group tier order of both sides: one counting pass, which
     // gives each entry's position in that order
     bool in_b = false;
@@ -776,16 +791,17 @@ hnv_status tier_scan(const TierSides &T, int small_max, int chunk, const int *ba
 // The work lists of the sides T after tier_scan, from the counts it left on
 // the device without reading them: grids cover the bounds (max_chunks
 // wavefront-tier items of both sides) and the kernels stop at the counts.
-hnv_status tier_emit(const TierSides &T, int chunk, int64_t max_chunks, const int *bad, Scratch &S,
+hnv_status tier_emit(const TierSides &T, const TierCuts &C, int64_t max_chunks, const int *bad, Scratch &S,
                      const int64_t *counts, const ItemMarks &marks, int32_t *n_marked, hipStream_t s)
 {
+    const int chunk = C.chunk;
     if (T.total == 0)
         return HNV_OK;
     const TierArrays &A = S.tier;
     k_small_items<<<grid_for(T.total), kThreads, 0, s>>>(T, A.pos, counts, bad);
     if (max_chunks > 0) {
-        k_chunk_items<<<grid_for(T.total), kThreads, 0, s>>>(T, chunk, chunk_shift(chunk), chunk_keys(chunk), A.tc,
-                                                             A.tpos, S.items, S.ckey_a, S.ids_a);
+        k_chunk_items<<<grid_for(T.total), kThreads, 0, s>>>(T, chunk, C.cut, chunk_shift(chunk), chunk_keys(chunk),
+                                                             A.tc, A.tpos, S.items, S.ckey_a, S.ids_a);
         // each side's longest first: a stable sort on the side and the length
         bool in_b = false;
         if (hnv_status st = bin_sort(S.ckey_a, S.ids_a, S.ckey_b, S.ids_b, max_chunks, S.n_chunks,
@@ -832,7 +848,8 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
     const hnv_map *m = C ? &maps[l] : nullptr;
     LevelPlan &L = p->lv[l];
     const int64_t nV = lv.n_nodes, nE = lv.n_edges, nnz = lv.nnz;
-    const int sm = L.small_max, chunk = p->opts.chunk;
+    // (a level whose split_over is the chunk needn't know whether it has hubs)
+    int32_t *hubs = L.split_over < L.chunk ? &M->hubs : nullptr;
     DevSide &S0 = L.side[0], &S1 = L.side[1];
     hnv_status st;
     // projection row map (first: the composed indices below read it)
@@ -841,7 +858,7 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
                                                         C->n_nodes, bad, L.rowmap, S.tier.row_ids);
     k_side0<<<grid_for(std::max(nnz, nE + 1)), kThreads, 0, s>>>(
         lv.edge_ptr, lv.edge_idx, lv.edge_w, C ? m->node_rep : nullptr, nE, nnz, bad, const_cast<int32_t *>(S0.ptr),
-        const_cast<int32_t *>(S0.idx), C ? const_cast<int32_t *>(S0.cidx) : nullptr, L.w);
+        const_cast<int32_t *>(S0.idx), C ? const_cast<int32_t *>(S0.cidx) : nullptr, L.w, L.chunk, hubs);
     // side 1: node -> hyperedges in ascending id (stable sort of incidences
     // by node; the offsets come from the sorted node ids)
     size_t tb = S.temp_bytes;
@@ -857,7 +874,7 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
                                                        C ? const_cast<int32_t *>(S1.cidx) : nullptr);
     }
     k_offsets_sorted<<<grid_for(nnz + 1), kThreads, 0, s>>>(reinterpret_cast<const uint32_t *>(S.keys_out), nnz, nV,
-                                                            bad, const_cast<int32_t *>(S1.ptr));
+                                                            bad, const_cast<int32_t *>(S1.ptr), L.chunk, hubs);
     // inverse map
     if (C) {
         const int64_t rows = nV + nE, rows_c = L.rows_coarse;
@@ -869,7 +886,7 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
                 return fail(HNV_EDEVICE, "sort of the inverse map");
         }
         k_offsets_sorted<<<grid_for(rows + 1), kThreads, 0, s>>>(reinterpret_cast<const uint32_t *>(S.keys_out),
-                                                                 rows, rows_c, bad, L.inv_ptr);
+                                                                 rows, rows_c, bad, L.inv_ptr, 0, nullptr);
     }
     if ((st = dev_check("plan arrays")) != HNV_OK)
         return st;
@@ -882,8 +899,9 @@ hnv_status build_level(hnv_plan *p, const hnv_level_dev *levels, const hnv_map *
     TS.s[0] = tier_side(S0, nE, 0, C ? L.rowmap : nullptr);
     TS.s[1] = tier_side(S1, nV, side1_offset(nE), C ? L.rowmap : nullptr);
     TS.total = side1_offset(nE) + nV;
-    if ((st = tier_scan(TS, sm, chunk, bad, S, M->counts, s)) != HNV_OK ||
-        (st = tier_emit(TS, chunk, (int64_t)S0.n_chunks + S1.n_chunks, bad, S, M->counts, item_marks(p, L),
+    const TierCuts cuts{L.chunk, L.split_over, L.cut, hubs};
+    if ((st = tier_scan(TS, L.small_max, cuts, bad, S, M->counts, s)) != HNV_OK ||
+        (st = tier_emit(TS, cuts, (int64_t)S0.n_chunks + S1.n_chunks, bad, S, M->counts, item_marks(p, L),
                         &M->marks[0][0], s)) != HNV_OK)
         return st;
     return dev_recompute_reciprocals(p, l, s);
@@ -916,7 +934,7 @@ hnv_status finish_level(hnv_plan *p, int l, const LevelMeta &M)
     if (L.n_long[0] > most_long[0] || L.n_long[1] > most_long[1])
         return fail(HNV_EDEVICE, "workgroup items exceed their bound");
     const int64_t slots = counts[3] + counts[7];
-    if (slots > p->max_slots)
+    if (slots * L.slot_pieces > p->max_slots)
         return fail(HNV_EDEVICE, "partial slots exceed their bound");
     L.n_slots = (int32_t)slots;
     settle_long_items(p, L);
@@ -1157,8 +1175,9 @@ extern "C" hnv_status hnv_score_plan_create_device(const int32_t *cand_ptr, cons
         TS.n = 1;
         TS.s[0] = tier_side(D, n_cand, 0, nullptr);
         TS.total = n_cand;
-        if ((st = tier_scan(TS, L.small_max, kScoreChunk, nullptr, S, S.counts, s)) != HNV_OK ||
-            (st = tier_emit(TS, kScoreChunk, L.n_chunks, nullptr, S, S.counts, ItemMarks{}, nullptr, s)) != HNV_OK ||
+        const TierCuts cuts{kScoreChunk, kScoreChunk, kScoreChunk, nullptr};
+        if ((st = tier_scan(TS, L.small_max, cuts, nullptr, S, S.counts, s)) != HNV_OK ||
+            (st = tier_emit(TS, cuts, L.n_chunks, nullptr, S, S.counts, ItemMarks{}, nullptr, s)) != HNV_OK ||
             (st = read_back(cnt, S.counts, sizeof(cnt), s)) != HNV_OK)
             return st;
         if (cnt[0] > L.n_small || cnt[1] > L.n_chunks || cnt[2] > L.n_splits || cnt[3] > L.n_slots)

@@ -54,11 +54,11 @@ void lane_layout(int cols, int elem, int *lanes, int *elems_per_lane)
 
 static constexpr int64_t kMaxI32 = std::numeric_limits<int32_t>::max();
 static constexpr int kDefaultSmallMax = 64;
-// Neighbours per wavefront-tier item.  Shorter ones need the finalize launch
-// in more levels and gain nothing, since long items take a workgroup: at 512,
-// 1,024 and 2,048 the refinement of 200K nodes with hubs takes 5.90, 5.80 and
-// 5.74 ms, of 150K nodes (BF16, edge-first) 4.25, 3.93 and 3.93 ms, of 2M
-// nodes (BF16) 154.2, 152.9 and 151.5 ms.
+// Neighbours of a row in one item of the wavefront tier; longer rows are cut.
+// Shorter ones need the finalize launch in more levels and gain nothing, since
+// long items take a workgroup: at 512, 1,024 and 2,048 the refinement of 150K
+// nodes (BF16, edge-first) takes 4.25, 3.93 and 3.93 ms, of 2M nodes (BF16)
+// 154.2, 152.9 and 151.5 ms.
 static constexpr int kDefaultChunk = 2048;
 // Neighbours per piece of an item in the order that serves gradients: a
 // wavefront each, so that a chunk is a workgroup's.
@@ -82,6 +82,17 @@ static_assert(kDefaultChunk == kWavesPerBlock * kDefaultPiece, "a piece per wave
 // a bound of 64 with a wavefront per 512 neighbours (1.10 at most), where
 // bounds by the number of rows took 0.80 (2.6 at most).  Given chunks keep the
 // bound of 64.
+//
+// Where a level has rows of more than a chunk, these set the time of a sweep that
+// gathers few bytes, and the finalize launch is there anyway: rows of more than
+// half a chunk are cut into items of 512 then (of a chunk in larger levels).  A
+// sweep in us with a wavefront per 512 neighbours, workgroups for up to 2,048, and
+// cut so:
+//   15K nodes / 10K hyperedges, rows of up to 7,371, FP32, d = 16     11.2, 14.4, 11.1
+//   23K / 12K, up to 8,947, BF16, d = 40                              17.6, 22.2, 15.5
+//   17K / 9K, up to 7,004, FP32, d = 64                               25.3, 28.2, 18.3
+//   94K / 34K, up to 26,360, BF16, d = 128                            36.5, 36.2, 24.3
+//   186K / 125K, up to 97,042, BF16, d = 40                           35.7, 30.5, 33.2
 static constexpr double kFewBytes = 40e6, kSomeBytes = 80e6, kManyBytes = 320e6;
 // Up to this many items (times panels) all take a workgroup (what launches from
 // LDS reproduce): 1.02 times the best at 512 to 1,024 of them, 1.14 at 2,048 to
@@ -93,6 +104,9 @@ static void default_tiers(LevelPlan &L, double bytes, int panels)
     const bool dense = 2 * L.nnz > 12 * L.rows;
     L.small_max = bytes <= kFewBytes ? 8 : bytes <= kSomeBytes || (bytes <= kManyBytes && !dense) ? 16 : kDefaultSmallMax;
     L.long_len = bytes <= kSomeBytes ? 64 : 256;
+    L.chunk = kDefaultChunk;
+    L.split_over = bytes <= kManyBytes ? kDefaultChunk / 2 : kDefaultChunk;
+    L.cut = bytes <= kManyBytes ? kDefaultPiece : kDefaultChunk;
     L.few_items = bytes <= kSomeBytes ? kFewItems / panels : 0;
 }
 
@@ -405,11 +419,11 @@ struct HostTier {
 
 // Rows with at most small_max neighbours: ordered by degree (descending,
 // then row) so that the rows sharing a wavefront have equal trip counts.
-// Longer rows: cut into chunks of at most `chunk` neighbours; a row of more
-// than one chunk gets consecutive partial slots.  Chunks are ordered longest
-// first so the heaviest work starts earliest.
-static void tier_side(const int32_t *ptr, int32_t n_rows, int small_max, int chunk, int32_t *slot_base,
-                      HostTier &t)
+// Longer rows: one item up to `split_over` (at most `chunk`) neighbours, else cut
+// into items of at most `cut`, which get consecutive partial slots.  Items are ordered longest first so
+// the heaviest work starts earliest.
+static void tier_side(const int32_t *ptr, int32_t n_rows, int small_max, int chunk, int split_over, int cut,
+                      int32_t *slot_base, HostTier &t)
 {
     std::vector<int32_t> count(small_max + 2, 0);
     int64_t n_small = 0;
@@ -431,15 +445,15 @@ static void tier_side(const int32_t *ptr, int32_t n_rows, int small_max, int chu
             t.small[count[small_max - deg]++] = Item{r, ptr[r], deg, 0};
             continue;
         }
-        const int32_t pieces = (deg + chunk - 1) / chunk;
-        if (pieces == 1) {
+        const int32_t pieces = (deg + cut - 1) / cut;
+        if (deg <= split_over) {
             t.chunks.push_back(Item{r, ptr[r], deg, -1});
             continue;
         }
         t.splits.push_back(Split{r, *slot_base, pieces, deg});
         for (int32_t k = 0; k < pieces; ++k) {
-            const int32_t s = ptr[r] + k * chunk;
-            t.chunks.push_back(Item{r, s, std::min(chunk, ptr[r + 1] - s), *slot_base + k});
+            const int32_t s = ptr[r] + k * cut;
+            t.chunks.push_back(Item{r, s, std::min(cut, ptr[r + 1] - s), *slot_base + k});
         }
         *slot_base += pieces;
     }
@@ -555,7 +569,7 @@ static hnv_status check_map(const hnv_level &f, const hnv_level &c, const hnv_ma
 // Builds the host arrays of one level (with_arrays = false: only what the
 // workspace size needs).
 static void build_level(const hnv_level *levels, const hnv_map *maps, int n_levels, int l, const hnv_options &o,
-                        int small_max, bool with_arrays, HostLevel &h)
+                        const LevelPlan &lp, bool with_arrays, HostLevel &h)
 {
     const hnv_level &L = levels[l];
     h.nV = L.n_nodes;
@@ -584,9 +598,14 @@ static void build_level(const hnv_level *levels, const hnv_map *maps, int n_leve
         count_by_node(&L, cnt, h.ptr[1]);
     }
 
+    int split_over = lp.chunk;
+    for (const auto &ptr : h.ptr)
+        for (size_t r = 0; r + 1 < ptr.size(); ++r)
+            if (ptr[r + 1] - ptr[r] > lp.chunk)
+                split_over = lp.split_over;
     int32_t slots = 0;
-    tier_side(h.ptr[0].data(), (int32_t)h.nE, small_max, o.chunk, &slots, h.tier[0]);
-    tier_side(h.ptr[1].data(), (int32_t)h.nV, small_max, o.chunk, &slots, h.tier[1]);
+    tier_side(h.ptr[0].data(), (int32_t)h.nE, lp.small_max, lp.chunk, split_over, lp.cut, &slots, h.tier[0]);
+    tier_side(h.ptr[1].data(), (int32_t)h.nV, lp.small_max, lp.chunk, split_over, lp.cut, &slots, h.tier[1]);
     h.n_slots = slots;
     if (!with_arrays)
         return;
@@ -732,7 +751,7 @@ void set_item_counts(const hnv_plan *p, const LevelPlan &L, const int32_t (&n_ch
 
 ItemMarks item_marks(const hnv_plan *p, const LevelPlan &L)
 {
-    const int chunk = p->opts.chunk;
+    const int chunk = L.chunk;
     return ItemMarks{{key_above(chunk, L.long_len), key_above(chunk, p->piece), key_above(chunk, p->lane_most)}};
 }
 
@@ -751,7 +770,7 @@ static LevelShape shape_of(const hnv_plan *p, int level, const HostLevel &h, boo
         sh.n_chunks[s] = (int32_t)h.tier[s].chunks.size();
         sh.n_splits[s] = (int32_t)h.tier[s].splits.size();
     }
-    const int chunk = p->opts.chunk;
+    const int chunk = p->lv[level].chunk;
     const ItemMarks m = item_marks(p, p->lv[level]);
     int32_t marks[kItemMarks][2] = {};
     for (int s = 0; s < 2; ++s)
@@ -809,7 +828,7 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base)
         }
         L.n_slots = h.n_slots;
         max_nodes = std::max(max_nodes, h.nV);
-        p->max_slots = std::max<int64_t>(p->max_slots, h.n_slots);
+        p->max_slots = std::max<int64_t>(p->max_slots, (int64_t)h.n_slots * L.slot_pieces);
         int64_t mb = 0, fb = 0;
         forward_geometry(p, L, &mb, &fb);
         p->max_resid_blocks = std::max(p->max_resid_blocks, mb + fb);
@@ -820,7 +839,7 @@ void carve(hnv_plan *p, const std::vector<LevelShape> &shape, char *base)
         }
     }
     p->zbuf = c.take<char>(p->lv[0].rows * p->d * (int64_t)elem);
-    p->partials = c.take<float>(p->max_slots * p->slot_pieces * p->pstride);
+    p->partials = c.take<float>(p->max_slots * p->pstride);
     p->resid_part = c.take<double>(kResidBatch * p->max_resid_blocks);
     p->resid_stage_len = blocks_for(p->max_resid_blocks, kBlock * 8) + 1;
     p->resid_stage = c.take<double>(2 * kResidBatch * p->resid_stage_len);
@@ -848,7 +867,6 @@ void init_plan_shape(hnv_plan *p, const std::vector<LevelShape> &shape, int d, h
     lane_layout(d, elem, &p->g_full, &p->epl_full);
     p->pstride = d + 8;
     p->piece = std::min(o.chunk, o.chunk == kDefaultChunk ? kDefaultPiece : o.chunk);
-    p->slot_pieces = (o.chunk + p->piece - 1) / p->piece;
     p->lane_most = std::min(o.small_max > 0 ? o.small_max : kDefaultSmallMax, kIdxRegs * p->g_fwd);
     p->lv.assign(n_levels, LevelPlan{});
     for (int l = 0; l < n_levels; ++l) {
@@ -864,6 +882,9 @@ void init_plan_shape(hnv_plan *p, const std::vector<LevelShape> &shape, int d, h
         if (o.small_max > 0 || o.chunk != kDefaultChunk)
             L.small_max = p->lane_most;
         L.small_max = std::min(L.small_max, p->lane_most);
+        if (o.chunk != kDefaultChunk)
+            L.chunk = L.split_over = L.cut = o.chunk;
+        L.slot_pieces = (L.cut + p->piece - 1) / p->piece;
     }
 }
 
@@ -936,7 +957,7 @@ extern "C" hnv_status hnv_plan_workspace_bytes(const hnv_level *levels, const hn
         init_plan_shape(&p, sh, d, dtype, o);
         for (int l = 0; l < n_levels; ++l) {
             HostLevel h;
-            build_level(levels, maps, n_levels, l, o, p.lv[l].small_max, false, h);
+            build_level(levels, maps, n_levels, l, o, p.lv[l], false, h);
             sh[l] = shape_of(&p, l, h, sh[l].unit_w);
         }
         carve(&p, sh, nullptr);
@@ -994,7 +1015,7 @@ extern "C" hnv_status hnv_plan_create(const hnv_level *levels, const hnv_map *ma
         {
             for (int l = 0; l < n_levels; ++l) {
                 HostLevel h;
-                build_level(levels, maps, n_levels, l, o, p->lv[l].small_max, false, h);
+                build_level(levels, maps, n_levels, l, o, p->lv[l], false, h);
                 sh[l] = shape_of(p, l, h, sh[l].unit_w);
             }
             carve(p, sh, nullptr);
@@ -1011,7 +1032,7 @@ extern "C" hnv_status hnv_plan_create(const hnv_level *levels, const hnv_map *ma
         // one level at a time: build host arrays, upload, wait, free
         for (int l = 0; l < n_levels; ++l) {
             HostLevel h;
-            build_level(levels, maps, n_levels, l, o, p->lv[l].small_max, true, h);
+            build_level(levels, maps, n_levels, l, o, p->lv[l], true, h);
             LevelPlan &L = p->lv[l];
             for (int sd = 0; sd < 2; ++sd) {
                 DevSide &S = L.side[sd];
@@ -1124,7 +1145,8 @@ static hnv_status score_layout(const int64_t *cand_ptr, int64_t n_cand, int d, h
         ptr32[c] = (int32_t)cand_ptr[c];
     int G = 1, E = 8;
     lane_layout(d, dtype == HNV_BF16 ? 2 : 4, &G, &E);
-    tier_side(ptr32.data(), (int32_t)n_cand, kIdxRegs * G, kScoreChunk, &L.slots, L.tier);
+    tier_side(ptr32.data(), (int32_t)n_cand, kIdxRegs * G, kScoreChunk, kScoreChunk, kScoreChunk, &L.slots,
+              L.tier);
     Carver c{nullptr};
     c.take<int32_t>(nnz);
     L.off_idx = 0;

@@ -95,6 +95,10 @@ struct LevelPlan {
     int small_max = 0;               // lane-group tier bound of the level
     int long_len = 0;                // items of more neighbours than this take a workgroup,
     int few_items = 0;               // or all of them if there are at most this many
+    int chunk = 0;                   // rows of more neighbours than this are cut,
+    int split_over = 0;              // than this if the level has a row of more than a chunk,
+    int cut = 0;                     // into items of this many
+    int slot_pieces = 1;             // pieces per such item in the order that serves gradients
     bool scales_ready = false;       // the reverse-mode scales (side[*].sn) hold the current weights
     DevSide side[2];
     float *r = nullptr;              // [rows] 1 / (row weight sum), 0 for rows without neighbours
@@ -135,12 +139,12 @@ struct hnv_plan {
     hnv_options opts{};
     std::vector<hnv::LevelPlan> lv;
     void *zbuf = nullptr;            // scratch embedding [rows of level 0 x d]
-    float *partials = nullptr;       // [max_slots x slot_pieces x pstride]
+    float *partials = nullptr;       // [max_slots x pstride]
     int32_t pstride = 0;             // floats per partial slot (d + 8)
     int64_t max_slots = 0;
     // the order that serves gradients: rows of up to lane_most neighbours one
-    // after another, longer ones in pieces, at most slot_pieces to a chunk
-    int lane_most = 0, piece = 0, slot_pieces = 1;
+    // after another, longer ones in pieces
+    int lane_most = 0, piece = 0;
     double *resid_part = nullptr;    // [kResidBatch x max_resid_blocks] per-block partials, one slot per sweep
     int64_t max_resid_blocks = 0;
     double *resid_stage = nullptr;   // [2 x kResidBatch x resid_stage_len] partial sums of the residual stages

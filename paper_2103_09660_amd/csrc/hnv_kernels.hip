@@ -1748,7 +1748,7 @@ static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp, bool piece
 {
     GatherArgs a{};
     a.piece = p->piece;
-    a.slot_pieces = p->slot_pieces;
+    a.slot_pieces = L.slot_pieces;
     a.side[0] = L.side[0];
     a.side[1] = L.side[1];
     if (L.unit_w)
