@@ -414,7 +414,9 @@ hnv_status hnv_sweep_adjoint_split(hnv_plan *plan, int level, const void *g_in, 
  * g_in (j = 0) or g_out[j - 1] and writes g_out[j], going back over the forward
  * sweep from states[n - 1 - j] to states[n - j].  states and g_out are HOST
  * arrays of n + 1 and n device matrices; an entry of g_out may appear again two
- * places later.  With dw_accum and node_accum the weight gradient is split as
+ * places later, but where weight gradients are formed it may not be a state that
+ * a later reverse sweep reads (states[0 .. n - 1 - j] after sweep j).  With
+ * dw_accum and node_accum the weight gradient is split as
  * hnv_sweep_adjoint_split has it, with neither none is formed (one without the
  * other is an error).  The same results as n calls. */
 hnv_status hnv_sweeps_adjoint(hnv_plan *plan, int level, const void *g_in, void *const *g_out,

@@ -40,7 +40,10 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <new>
 #include <string>
+#include <utility>
+#include <vector>
 
 #include "hnv_grid.h"
 #include "hnv_internal.h"
@@ -2234,15 +2237,19 @@ extern "C" hnv_status hnv_sweeps(hnv_plan *plan, int level, const void *z_in, vo
         return fail(HNV_EINVAL, "z_in / z_out / the last result is NULL, or no sweeps");
     if (!aligned16(z_in))
         return fail(HNV_EINVAL, "z_in must be 16-byte aligned");
-    const void *last = z_in;
-    for (int i = 0; i < n; ++i) {
-        if (!z_out[i])
-            continue;
-        if (!aligned16(z_out[i]))
-            return fail(HNV_EINVAL, "z_out must be 16-byte aligned");
-        if (z_out[i] == z_in || z_out[i] == last || z_out[i] == plan->zbuf)
+    try {
+        std::vector<const void *> used{z_in, plan->zbuf};
+        for (int i = 0; i < n; ++i) {
+            if (!aligned16(z_out[i]))
+                return fail(HNV_EINVAL, "z_out must be 16-byte aligned");
+            if (z_out[i])
+                used.push_back(z_out[i]);
+        }
+        std::sort(used.begin(), used.end());
+        if (std::adjacent_find(used.begin(), used.end()) != used.end())
             return fail(HNV_EINVAL, "an entry of z_out aliases z_in or another one");
-        last = z_out[i];
+    } catch (const std::bad_alloc &) {
+        return fail(HNV_ENOMEM, "host allocation failed in hnv_sweeps");
     }
     if (!(omega >= 0.0f && omega <= 1.0f))
         return fail(HNV_EINVAL, "omega must be in [0, 1]");
@@ -2654,6 +2661,22 @@ extern "C" hnv_status hnv_sweeps_adjoint(hnv_plan *plan, int level, const void *
         if ((st = check_adjoint_args(plan, level, j == 0 ? g_in : g_out[j - 1], g_out[j], states[n - 1 - j],
                                      states[n - j], omega)) != HNV_OK)
             return st;
+    // sweep j leaves states[0 .. n - 1 - j] to the sweeps after it
+    if (wgrad) {
+        try {
+            std::vector<std::pair<const void *, int>> at(n + 1);
+            for (int i = 0; i <= n; ++i)
+                at[i] = {states[i], i};
+            std::sort(at.begin(), at.end());
+            for (int j = 0; j + 1 < n; ++j) {
+                const auto f = std::lower_bound(at.begin(), at.end(), std::make_pair((const void *)g_out[j], 0));
+                if (f != at.end() && f->first == g_out[j] && f->second <= n - 1 - j)
+                    return fail(HNV_EINVAL, "an entry of g_out aliases a state that a later reverse sweep reads");
+            }
+        } catch (const std::bad_alloc &) {
+            return fail(HNV_ENOMEM, "host allocation failed in hnv_sweeps_adjoint");
+        }
+    }
     for (int j = 0; j < n; ++j)
         if ((st = run_adjoint(plan, level, j == 0 ? g_in : g_out[j - 1], g_out[j], states[n - 1 - j], states[n - j],
                               dw_accum, node_accum, omega, wgrad ? 2 : 0,
