@@ -1502,26 +1502,27 @@ __global__ __launch_bounds__(kThreads) void k_byte_scores_long(const int32_t *__
     const bool col_ok = gl * 16 < kp;
     for (uint64_t todo = __ballot(my_m > kByteSmall); todo; todo &= todo - 1) {   // the same in every wavefront
         const int w = __ffsll((long long)todo) - 1;
-        const int32_t a = __shfl(my_a, w), m = __shfl(my_m, w);
+        // (unsigned: a round may pass 2^31 - 1)
+        const uint32_t a = __shfl(my_a, w), m = __shfl(my_m, w);
         __syncthreads();
         for (int c = threadIdx.x; c < G * 16; c += kThreads)
             sum[c] = 0;
         __syncthreads();
-        auto load_rows = [&](uint4 (&r)[U], int32_t t) {   // members t + u P + p
+        auto load_rows = [&](uint4 (&r)[U], uint32_t t) {   // members t + u P + p
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int32_t j = t + u * P + p;
+                const uint32_t j = t + u * P + p;
                 r[u] = make_uint4(0, 0, 0, 0);
                 if (j < m && col_ok)
                     r[u] = *reinterpret_cast<const uint4 *>(x8 + (int64_t)idx[a + j] * kp + gl * 16);
             }
         };
         // at most 256 rows per lane group before its sums move to LDS
-        for (int32_t t0 = 0; t0 < m; t0 += 256 * P) {
+        for (uint32_t t0 = 0; t0 < m; t0 += 256 * P) {
             ByteSum s;
             s.zero();
-            const int32_t end = min(m, t0 + 256 * P);
-            for (int32_t t = t0; t < end; t += U * P) {
+            const uint32_t end = min(m, t0 + 256 * P);
+            for (uint32_t t = t0; t < end; t += U * P) {
                 uint4 r[U];
                 load_rows(r, t);
 #pragma unroll
@@ -1553,7 +1554,7 @@ __global__ __launch_bounds__(kThreads) void k_byte_scores_long(const int32_t *__
                               ((c[2] >> (8 * y)) & 255u) << 16 | ((c[3] >> (8 * y)) & 255u) << 24;
         }
         s2 = lanes_sum<G>(s2);
-        for (int32_t t = 0; t < m; t += U * P) {
+        for (uint32_t t = 0; t < m; t += U * P) {
             uint4 r[U];
             load_rows(r, t);
             int64_t d[4];
@@ -1563,14 +1564,14 @@ __global__ __launch_bounds__(kThreads) void k_byte_scores_long(const int32_t *__
                        ((int64_t)dot16(plane[2], r[u]) << 16) + ((int64_t)dot16(plane[3], r[u]) << 24);
             if constexpr (G >= 4) {
                 const int64_t v = lanes_sum4<G>(d, gl);
-                const int32_t j = t + slot_of<G>(gl) * P + p;
+                const uint32_t j = t + slot_of<G>(gl) * P + p;
                 if (gl < 4 && j < m)
                     put_score((int64_t)a + j, idx[a + j], v, s2, q, bestq);
             } else {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int64_t v = lanes_sum<G>(d[u]);
-                    const int32_t j = t + u * P + p;
+                    const uint32_t j = t + u * P + p;
                     if (gl == 0 && j < m)
                         put_score((int64_t)a + j, idx[a + j], v, s2, q, bestq);
                 }
@@ -1599,15 +1600,16 @@ __global__ __launch_bounds__(kThreads) void k_rowsum_bytes(const int32_t *__rest
 #pragma unroll
     for (int i = 0; i < NC; ++i)
         acc[i] = make_int4(0, 0, 0, 0);
-    for (int32_t j = a; j < b; j += U) {
+    for (uint32_t j = a; j < (uint32_t)b; j += U) {   // (unsigned: b may be 2^31 - 1)
         uint32_t w[U][NC];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t base = (j + u < b) ? (int64_t)idx[j + u] * kp4 : 0;
+            const bool ok = j + u < (uint32_t)b;
+            const int64_t base = ok ? (int64_t)idx[j + u] * kp4 : 0;
 #pragma unroll
             for (int i = 0; i < NC; ++i) {
                 const int c = lane + i * kWave;
-                w[u][i] = (j + u < b && c < kp4) ? x8[base + c] : 0u;
+                w[u][i] = (ok && c < kp4) ? x8[base + c] : 0u;
             }
         }
 #pragma unroll

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kThreads) void k_check_edge_map(const int32_t *__re
             const int of = __ffsll((unsigned long long)todo) - 1;
             todo &= todo - 1;
             const int32_t lo = __shfl(a, of, kWave), hi = __shfl(b, of, kWave), rep = __shfl(first, of, kWave);
-            for (int32_t j = lo + 1 + (int)(threadIdx.x % kWave); j < hi; j += kWave)
+            for (uint32_t j = lo + 1 + threadIdx.x % kWave; j < (uint32_t)hi; j += kWave)   // (hi may be 2^31 - 1)
                 if (node_rep[idx[j]] != rep)
                     bad = 1 << 7;
         }

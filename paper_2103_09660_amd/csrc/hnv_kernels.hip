@@ -47,6 +47,7 @@
 
 #include "hnv_grid.h"
 #include "hnv_internal.h"
+#include "hnv_weights.h"
 
 #define HNV_DEV __device__ __forceinline__
 
@@ -1512,28 +1513,6 @@ constexpr int kRecipLong = 64;
 constexpr int kRecipHuge = 2048;
 constexpr int kRecipRows = kBlock / kRecipLanes;   // nodes per block
 
-// The lane's share (positions first, first + step, ..) of the weights of the
-// star edges [j, end): written to wn, and their sum.
-HNV_DEV double sum_weights(const int32_t *__restrict__ idx, const float *__restrict__ w, int64_t n_nodes, int32_t j,
-                           int32_t end, int step, float *__restrict__ wn)
-{
-    constexpr int U = 8;   // gathers in flight
-    double t = 0.0;
-    for (; j < end; j += U * step) {
-        float x[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k)
-            x[k] = j + k * step < end ? w[idx[j + k * step] - n_nodes] : 0.0f;
-#pragma unroll
-        for (int k = 0; k < U; ++k)
-            if (j + k * step < end) {
-                wn[j + k * step] = x[k];
-                t += (double)x[k];
-            }
-    }
-    return t;
-}
-
 __global__ __launch_bounds__(kBlock) void k_recip_weighted(const int32_t *__restrict__ ptr,
                                                            const int32_t *__restrict__ idx,
                                                            const int32_t *__restrict__ edge_ptr,
@@ -1559,19 +1538,8 @@ __global__ __launch_bounds__(kBlock) void k_recip_weighted(const int32_t *__rest
     }
     const bool is_long = end - begin > kRecipLong;
     double s = 0.0;
-    if (!is_long) {
-        for (int32_t j = begin + gl; j < end; j += 2 * kRecipLanes) {   // (two gathers in flight)
-            const bool two = j + kRecipLanes < end;
-            const float w0 = w[idx[j] - n_nodes];
-            const float w1 = two ? w[idx[j + kRecipLanes] - n_nodes] : 0.0f;
-            wn[j] = w0;
-            s += (double)w0;
-            if (two) {
-                wn[j + kRecipLanes] = w1;
-                s += (double)w1;
-            }
-        }
-    }
+    if (!is_long)
+        s = sum_weights<2>(idx, w, n_nodes, begin + gl, end, kRecipLanes, wn);
 #pragma unroll
     for (int off = 1; off < kRecipLanes; off <<= 1)
         s += __shfl_xor(s, off, kWave);
@@ -1580,7 +1548,7 @@ __global__ __launch_bounds__(kBlock) void k_recip_weighted(const int32_t *__rest
     while (todo) {   // uniform
         const int of = __ffsll((unsigned long long)todo) - 1;
         todo &= todo - 1;
-        double t = sum_weights(idx, w, n_nodes, __shfl(begin, of, kWave) + lane, __shfl(end, of, kWave), kWave, wn);
+        double t = sum_weights<8>(idx, w, n_nodes, __shfl(begin, of, kWave) + lane, __shfl(end, of, kWave), kWave, wn);
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1)
             t += __shfl_xor(t, off, kWave);
@@ -1598,7 +1566,7 @@ __global__ __launch_bounds__(kBlock) void k_recip_weighted(const int32_t *__rest
     const int n = n_huge;
     for (int i = 0; i < n; ++i) {
         const int64_t u = node_of(huge[i]);
-        const double t = block_wave_sums(sum_weights(idx, w, n_nodes, ptr[u] + (int)threadIdx.x, ptr[u + 1], kBlock, wn));
+        const double t = block_wave_sums(sum_weights<8>(idx, w, n_nodes, ptr[u] + threadIdx.x, ptr[u + 1], kBlock, wn));
         if (threadIdx.x == 0)
             r[u] = (t > 0.0) ? (float)(1.0 / t) : 0.0f;
         __syncthreads();   // (the sums' LDS is free again)
