@@ -1,5 +1,5 @@
-// Stable counting sort by a digit of at most kBinsMax values, shared by the
-// GPU coarsening and the device-built plan.
+// Stable counting sort by keys of at most kBinsMax values, shared by the GPU
+// coarsening and the device-built plan.
 // Included by the .hip sources only; every symbol has internal linkage.
 #pragma once
 
@@ -14,18 +14,16 @@
 namespace hnv {
 namespace {
 
-// One pass of a stable counting sort of (key, value) pairs by the digit
-// (key >> shift) & mask, which is below n_bins <= kBinsMax: per-tile counts
-// of every digit, an exclusive scan of the counts laid out digit-major
-// (digit b of tile t at b * n_tiles + t), and a scatter in which each tile
-// places its elements in input order.  The degree tiers of both sides need
-// one pass (2 (small_max + 3) keys), the wavefront tier's chunk keys one pass
-// while both sides' keys (2 chunk_keys) fit in kBinsMax, else one per 10 bits,
-// the coarsening's hyperedge sizes one pass; the result equals a stable radix
-// sort's.  The number of pairs is n_max, or *n_dev when that is given (the
+// A stable counting sort of (key, value) pairs by the key, which is below
+// n_bins <= kBinsMax: per-tile counts of every key, an exclusive scan of the
+// counts laid out key-major (key b of tile t at b * n_tiles + t), and a scatter
+// in which each tile places its elements in input order.  It sorts the degree
+// tiers of both sides (2 (small_max + 3) keys), the wavefront tier's items
+// (2 chunk_keys, at most 1,024) and the coarsening's hyperedge sizes; the result
+// equals a stable radix sort's.  The number of pairs is n_max, or *n_dev when that is given (the
 // grid is sized for n_max).  Without input values a value is the element's
-// index; either output may be absent (null); a one-pass sort can also write
-// each input element's sorted position (pos_out).
+// index; either output may be absent (null); pos_out (or null): each input
+// element's sorted position.
 //
 // A tile is `rounds` rounds of 64 elements per wavefront, a wavefront's rounds
 // consecutive.  The scatter counts its tile once more, per wavefront, and then
@@ -35,7 +33,6 @@ namespace {
 // sorts of levels of 0.3M to 1.2M rows).  Short inputs take short tiles, so
 // that their few elements spread over the chip.
 constexpr int kBinsMax = 1024;
-constexpr int kBinBits = 10;   // digit width of the multi-pass form
 constexpr int kBinWaves = kThreads / kWave;
 
 inline int bin_rounds(int64_t n) { return n <= (int64_t(1) << 18) ? 4 : 16; }
@@ -57,8 +54,8 @@ __device__ inline int64_t pairs_of(int64_t n_max, const int64_t *n_dev)
 }
 
 __global__ __launch_bounds__(kThreads) void k_bin_count(const uint32_t *__restrict__ key, int64_t n_max,
-                                                        const int64_t *__restrict__ n_dev, int shift, uint32_t mask,
-                                                        int n_bins, int rounds, int64_t n_tiles,
+                                                        const int64_t *__restrict__ n_dev, int n_bins, int rounds,
+                                                        int64_t n_tiles,
                                                         int32_t *__restrict__ counts)
 {
     __shared__ int32_t h[kBinsMax];
@@ -70,7 +67,7 @@ __global__ __launch_bounds__(kThreads) void k_bin_count(const uint32_t *__restri
     for (int k = 0; k < rounds; ++k) {
         const int64_t i = base + (int64_t)k * kThreads + threadIdx.x;
         if (i < n)
-            atomicAdd(&h[(key[i] >> shift) & mask], 1);
+            atomicAdd(&h[key[i]], 1);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < n_bins; b += kThreads)
@@ -92,8 +89,8 @@ __device__ inline uint64_t same_key_lanes(uint32_t key, int bits, bool active)
 
 __global__ __launch_bounds__(kThreads) void k_bin_scatter(const uint32_t *__restrict__ key,
                                                           const int32_t *__restrict__ val, int64_t n_max,
-                                                          const int64_t *__restrict__ n_dev, int shift,
-                                                          uint32_t mask, int n_bins, int bits, int rounds,
+                                                          const int64_t *__restrict__ n_dev, int n_bins, int bits,
+                                                          int rounds,
                                                           int64_t n_tiles, const int32_t *__restrict__ offs,
                                                           uint32_t *__restrict__ key_out,
                                                           int32_t *__restrict__ val_out,
@@ -111,7 +108,7 @@ __global__ __launch_bounds__(kThreads) void k_bin_scatter(const uint32_t *__rest
     for (int k = 0; k < rounds; ++k) {
         const int64_t i = first + (int64_t)k * kWave;
         if (i < n)
-            atomicAdd(&next[wave][(key[i] >> shift) & mask], 1);
+            atomicAdd(&next[wave][key[i]], 1);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < n_bins; b += kThreads) {
@@ -129,12 +126,11 @@ __global__ __launch_bounds__(kThreads) void k_bin_scatter(const uint32_t *__rest
         if (__ballot(act) == 0)
             break;
         const uint32_t kv = act ? key[i] : 0u;
-        const uint32_t dg = (kv >> shift) & mask;
-        const uint64_t peers = same_key_lanes(dg, bits, act);
+        const uint64_t peers = same_key_lanes(kv, bits, act);
         const int leader = peers ? __ffsll((long long)peers) - 1 : lane;
         int32_t at = 0;
         if (act && lane == leader)
-            at = atomicAdd(&next[wave][dg], (int32_t)__popcll(peers));
+            at = atomicAdd(&next[wave][kv], (int32_t)__popcll(peers));
         at = __shfl(at, leader, kWave);
         if (act) {
             const int32_t pos = at + (int32_t)__popcll(peers & below);

@@ -1905,12 +1905,11 @@ hnv_status coarsen_device(int64_t n_nodes, int64_t n_edges, int64_t nnz, const i
         const int rounds = bin_rounds(n_edges);
         const int64_t tiles = bin_tiles(n_edges), last_bin = max_last_bin(n_nodes, nnz);
         S = SizeOrder{by_size, offs, tiles, n_edges};
-        k_bin_count<<<(unsigned)tiles, kThreads, 0, s>>>(size_key, n_edges, nullptr, 0, ~0u, kSizeBins, rounds, tiles,
-                                                         bins);
+        k_bin_count<<<(unsigned)tiles, kThreads, 0, s>>>(size_key, n_edges, nullptr, kSizeBins, rounds, tiles, bins);
         if (prim_exclusive_sum(temp, tb, bins, offs, tiles * kSizeBins, s) != hipSuccess)
             return fail(HNV_EDEVICE, "scan of the size counts");
         if (last_bin <= kBigMax) {
-            k_bin_scatter<<<(unsigned)tiles, kThreads, 0, s>>>(size_key, nullptr, n_edges, nullptr, 0, ~0u, kSizeBins,
+            k_bin_scatter<<<(unsigned)tiles, kThreads, 0, s>>>(size_key, nullptr, n_edges, nullptr, kSizeBins,
                                                                bits_for(kSizeBins), rounds, tiles, offs, nullptr,
                                                                by_size, size_rank);
             if (last_bin > 0) {

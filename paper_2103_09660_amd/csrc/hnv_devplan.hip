@@ -97,6 +97,27 @@ __global__ __launch_bounds__(kThreads) void k_check_edge_map(const int32_t *__re
         atomicOr(flag, bad);
 }
 
+// Candidate offsets (as k_check_level checks a level's, empty lists allowed) and
+// members' range: flag bits 0 and 1.
+__global__ __launch_bounds__(kThreads) void k_check_offsets(const int32_t *__restrict__ ptr, int64_t n, int64_t nnz,
+                                                            int *__restrict__ flag)
+{
+    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (e >= n)
+        return;
+    const int64_t a = ptr[e], b = ptr[e + 1];
+    if (a < 0 || b < a || b > nnz || (e == 0 && a != 0) || (e == n - 1 && b != nnz))
+        atomicOr(flag, 1);
+}
+
+__global__ __launch_bounds__(kThreads) void k_check_range(const int32_t *__restrict__ idx, int64_t n_ids, int64_t nnz,
+                                                          int *__restrict__ flag)
+{
+    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (j < nnz && (idx[j] < 0 || idx[j] >= n_ids))
+        atomicOr(flag, 2);
+}
+
 // A level without hyperedges: its offsets are the single 0 and it has no
 // incidences (flag bit 0 otherwise).
 __global__ void k_check_no_edges(const int32_t *__restrict__ ptr, int64_t nnz, int *__restrict__ flag)
@@ -720,41 +741,25 @@ hnv_status report_checks(int l, const int *flags, bool full)
     return HNV_OK;
 }
 
-// Stable sort of the pairs (ka, va) by key (every key below key_limit) with
-// the counting passes above: n_max pairs, or *n_dev of them.  The sorted
-// pairs end in (kb, vb) after an odd number of passes, else in (ka, va);
-// `in_b` tells which.  va and vb may both be null (keys only).  pos_out (one
-// pass only): pos_out[i] = the sorted position of input pair i.
-hnv_status bin_sort(uint32_t *ka, int32_t *va, uint32_t *kb, int32_t *vb, int64_t n_max, const int64_t *n_dev,
-                    int64_t key_limit, Scratch &S, hipStream_t s, bool &in_b, int32_t *pos_out = nullptr)
+// Stable counting sort of the pairs (ka, va) by key (every key below n_bins, at
+// most kBinsMax) into (kb, vb): n_max pairs, or *n_dev of them.  va and vb may
+// both be null (keys only).  pos_out (may be null): pos_out[i] = the sorted
+// position of input pair i.
+hnv_status bin_sort(const uint32_t *ka, const int32_t *va, uint32_t *kb, int32_t *vb, int64_t n_max,
+                    const int64_t *n_dev, int n_bins, Scratch &S, hipStream_t s, int32_t *pos_out = nullptr)
 {
-    in_b = false;
+    if (n_bins > kBinsMax)
+        return fail(HNV_EUNSUPPORTED, "keys above the counting sort's range");
     if (n_max == 0)
         return HNV_OK;
     const int rounds = bin_rounds(n_max);
     const int64_t tiles = bin_tiles(n_max);
-    const bool one = key_limit <= kBinsMax;
-    const int passes = one ? 1 : (bits_for(key_limit) + kBinBits - 1) / kBinBits;
-    const int n_bins = one ? (int)key_limit : kBinsMax;
-    if (pos_out && !one)
-        return fail(HNV_EUNSUPPORTED, "sorted positions from a multi-pass counting sort");
-    const uint32_t mask = one ? 0xffffffffu : (uint32_t)(kBinsMax - 1);
-    uint32_t *kin = ka, *kout = kb;
-    int32_t *vin = va, *vout = vb;
-    for (int pass = 0; pass < passes; ++pass) {
-        const int shift = pass * kBinBits;
-        k_bin_count<<<(unsigned)tiles, kThreads, 0, s>>>(kin, n_max, n_dev, shift, mask, n_bins, rounds, tiles,
-                                                         S.bin_counts);
-        size_t tb = S.temp_bytes;
-        if (prim_exclusive_sum(S.temp, tb, S.bin_counts, S.bin_offs, tiles * n_bins, s) != hipSuccess)
-            return fail(HNV_EDEVICE, "scan of a counting sort's digit counts");
-        k_bin_scatter<<<(unsigned)tiles, kThreads, 0, s>>>(kin, vin, n_max, n_dev, shift, mask, n_bins,
-                                                           bits_for(n_bins), rounds, tiles, S.bin_offs, kout,
-                                                           vin ? vout : nullptr, pos_out);
-        std::swap(kin, kout);
-        std::swap(vin, vout);
-        in_b = !in_b;
-    }
+    k_bin_count<<<(unsigned)tiles, kThreads, 0, s>>>(ka, n_max, n_dev, n_bins, rounds, tiles, S.bin_counts);
+    size_t tb = S.temp_bytes;
+    if (prim_exclusive_sum(S.temp, tb, S.bin_counts, S.bin_offs, tiles * n_bins, s) != hipSuccess)
+        return fail(HNV_EDEVICE, "scan of a counting sort's key counts");
+    k_bin_scatter<<<(unsigned)tiles, kThreads, 0, s>>>(ka, va, n_max, n_dev, n_bins, bits_for(n_bins), rounds, tiles,
+                                                       S.bin_offs, kb, vb, pos_out);
     return dev_check("counting sort");
 }
 
@@ -769,22 +774,19 @@ hnv_status tier_scan(const TierSides &T, int small_max, const TierCuts &C, const
         k_fill<<<1, kThreads, 0, s>>>(reinterpret_cast<int32_t *>(S.n_chunks), 2, 0);
         return dev_check("tier counts");
     }
-    const int64_t n_keys = (int64_t)T.n * (small_max + 3);
-    if (n_keys > kBinsMax)
-        return fail(HNV_EUNSUPPORTED, "small_max above the tier sort's key range");
     const TierArrays &A = S.tier;
     k_tier_keys<<<grid_for(T.total), kThreads, 0, s>>>(T, small_max, C, bad, A.key_a, A.tc);
     // the lane-group tier order of both sides: one counting pass, which
     // gives each entry's position in that order
-    bool in_b = false;
-    if (hnv_status st = bin_sort(A.key_a, nullptr, A.key_b, nullptr, T.total, nullptr, n_keys, S, s, in_b, A.pos);
+    if (hnv_status st = bin_sort(A.key_a, nullptr, A.key_b, nullptr, T.total, nullptr, T.n * (small_max + 3), S, s,
+                                 A.pos);
         st != HNV_OK)
         return st;
     size_t tb = S.temp_bytes;
     if (prim_exclusive_scan(S.temp, tb, A.tc, A.tpos, TierCount{0, 0, 0}, (int)T.total, TierCountPlus(), s) !=
         hipSuccess)
         return fail(HNV_EDEVICE, "scan of the tier counts");
-    k_tier_counts<<<1, 64, 0, s>>>(in_b ? A.key_b : A.key_a, A.tc, A.tpos, T, small_max, counts, S.n_chunks);
+    k_tier_counts<<<1, 64, 0, s>>>(A.key_b, A.tc, A.tpos, T, small_max, counts, S.n_chunks);
     return dev_check("tier keys");
 }
 
@@ -803,14 +805,12 @@ hnv_status tier_emit(const TierSides &T, const TierCuts &C, int64_t max_chunks, 
         k_chunk_items<<<grid_for(T.total), kThreads, 0, s>>>(T, chunk, C.cut, chunk_shift(chunk), chunk_keys(chunk),
                                                              A.tc, A.tpos, S.items, S.ckey_a, S.ids_a);
         // each side's longest first: a stable sort on the side and the length
-        bool in_b = false;
         if (hnv_status st = bin_sort(S.ckey_a, S.ids_a, S.ckey_b, S.ids_b, max_chunks, S.n_chunks,
-                                     (int64_t)T.n * chunk_keys(chunk), S, s, in_b);
+                                     T.n * chunk_keys(chunk), S, s);
             st != HNV_OK)
             return st;
-        k_gather_items<<<grid_for(max_chunks), kThreads, 0, s>>>(T, S.items, in_b ? S.ids_b : S.ids_a,
-                                                                 in_b ? S.ckey_b : S.ckey_a, counts, S.n_chunks,
-                                                                 chunk_keys(chunk), marks, n_marked);
+        k_gather_items<<<grid_for(max_chunks), kThreads, 0, s>>>(T, S.items, S.ids_b, S.ckey_b, counts,
+                                                                 S.n_chunks, chunk_keys(chunk), marks, n_marked);
     }
     k_split_items<<<grid_for(T.total), kThreads, 0, s>>>(T, A.tc, A.tpos, counts);
     return dev_check("work lists");
@@ -1141,10 +1141,9 @@ extern "C" hnv_status hnv_score_plan_create_device(const int32_t *cand_ptr, cons
     // ids in [0, z_rows); empty candidates are allowed (their rows are NaN)
     k_fill<<<1, kThreads, 0, s>>>(S.flag, 4, 0);
     if (n_cand > 0)
-        k_check_edges<<<grid_for(n_cand), kThreads, 0, s>>>(cand_ptr, nullptr, n_cand, n_members, 0, S.flag);
+        k_check_offsets<<<grid_for(n_cand), kThreads, 0, s>>>(cand_ptr, n_cand, n_members, S.flag);
     if (n_members > 0)
-        k_check_members<<<grid_for(n_members), kThreads, 0, s>>>(cand_ptr, cand_idx, nullptr, z_rows, n_cand,
-                                                                n_members, 0, S.flag);
+        k_check_range<<<grid_for(n_members), kThreads, 0, s>>>(cand_idx, z_rows, n_members, S.flag);
     if ((st = dev_check("candidate checks")) != HNV_OK)
         return st;
     int bad = 0;

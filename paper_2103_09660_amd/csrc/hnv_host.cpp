@@ -667,7 +667,7 @@ struct Carver {
 
 void forward_geometry(const hnv_plan *p, const LevelPlan &L, int64_t *main_blocks, int64_t *fin_blocks)
 {
-    const int64_t rows_per_block = kRowsPerGroup * kBlock / p->g_fwd;
+    const int64_t rows_per_block = kBlock / p->g_fwd;
     int64_t per_panel = 0;
     for (int s = 0; s < 2; ++s)
         per_panel += L.n_long[s] + blocks_for(L.n_chunks[s] - L.n_long[s], kWavesPerBlock) +

@@ -21,10 +21,6 @@ namespace hnv {
 constexpr int kBlock = 256;   // threads per workgroup (4 wavefronts of 64)
 constexpr int kWave = 64;
 constexpr int kWavesPerBlock = kBlock / kWave;
-#ifndef HNV_ROWS_PER_GROUP
-#define HNV_ROWS_PER_GROUP 1
-#endif
-constexpr int kRowsPerGroup = HNV_ROWS_PER_GROUP;   // lane-group tier rows a group handles in turn
 
 // A work item: `len` neighbours of side-local row `row` starting at `start`
 // in the side's neighbour array.

@@ -11,17 +11,15 @@
 //     access and a wavefront covers 64/G rows at once;
 //   - rows are tiered by neighbour count in the plan.  Rows with few
 //     neighbours get one lane group each (same-degree rows share a
-//     wavefront); longer rows get a whole wavefront per chunk of neighbours,
-//     the 64/G groups taking interleaved neighbours and being combined by a
-//     cross-lane butterfly; long chunks get a workgroup, a quarter per
-//     wavefront, added through LDS; rows longer than one chunk are split over
-//     several items whose FP32 partial sums a finalize pass adds in slot order;
+//     wavefront); longer rows get a whole wavefront, the 64/G groups taking
+//     interleaved neighbours and being combined by a cross-lane butterfly, long
+//     ones a workgroup, a quarter per wavefront, added through LDS; the longest
+//     are cut into several items whose FP32 partial sums a finalize pass adds in
+//     slot order;
 //   - a sweep over a small level takes as long as its longest chain of
 //     dependent gathers (about 0.35 us per batch of four on an idle chip,
-//     1 us on a busy one), which is what the long items, the tier bound by
-//     level size and the 2,048-neighbour chunks shorten (a sweep, FP32,
-//     d = 64: 8K nodes / 4K hyperedges 15.1 -> 7.4 us, 20K / 8K 16.6 -> 8.4,
-//     80K / 50K 44 -> 32, hub rows of 79K neighbours over 300K rows 60 -> 48);
+//     1 us on a busy one), which is what the workgroup items, the tier bounds by
+//     the bytes gathered and the cuts shorten;
 //   - latency is hidden by keeping the dependent-load chain short: a work
 //     item carries the row, its first neighbour and its degree (and, for the
 //     first sweep of a level, the coarser row it is projected from); a lane
@@ -869,50 +867,44 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
             }
         }
     } else {
-        for (int rr = 0; rr < kRowsPerGroup; ++rr) {
-            const int item = (b * kRowsPerGroup + rr) * (kBlock / G) + (int)(threadIdx.x / G);
-            const bool valid = item < n_lane_items;
-            Item it{0, 0, 0, 0};
-            int my_id = 0;   // lane gl < kInlineIds: the row's neighbour gl, loaded with the item
-            if (valid) {
-                it = lane_items[item];
-                if (gl < kInlineIds && G >= kInlineIds && listed)
-                    my_id = (FUSED ? Sd.small_cids : Sd.small_ids)[item].id[gl];
-            }
-            const int zrow = Sd.row_base + it.row;
-            Own<T, EPL> self{};
-            if (valid && col_ok) {
-                const int64_t srow = !(MODE == kFwd && (FUSED || a.self_mapped)) ? zrow
-                                     : listed                                    ? it.aux
-                                                                                 : a.rowmap[zrow];
-                load_own<T, EPL, MODE>(self, a, mats, it.row, zrow, srow, it.len, col);
-            }
-            if (rr > 0) {
-                zero(acc);
-                csum = 0.0f;
-            }
-            if (PIECES == 2 && !listed) {   // uniform over the block
-                if (use_scale)
-                    gather_deep<T, EPL, G, true, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
-                                                          g * G, acc, csum);
-                else
-                    gather_deep<T, EPL, G, false, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
-                                                           g * G, acc, csum);
-            } else if (use_scale)
-                gather_group<T, EPL, G, true, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
-                                                       g * G, my_id, acc, csum);
+        const int item = b * (kBlock / G) + (int)(threadIdx.x / G);
+        const bool valid = item < n_lane_items;
+        Item it{0, 0, 0, 0};
+        int my_id = 0;   // lane gl < kInlineIds: the row's neighbour gl, loaded with the item
+        if (valid) {
+            it = lane_items[item];
+            if (gl < kInlineIds && G >= kInlineIds && listed)
+                my_id = (FUSED ? Sd.small_cids : Sd.small_ids)[item].id[gl];
+        }
+        const int zrow = Sd.row_base + it.row;
+        Own<T, EPL> self{};
+        if (valid && col_ok) {
+            const int64_t srow = !(MODE == kFwd && (FUSED || a.self_mapped)) ? zrow
+                                 : listed                                    ? it.aux
+                                                                             : a.rowmap[zrow];
+            load_own<T, EPL, MODE>(self, a, mats, it.row, zrow, srow, it.len, col);
+        }
+        if (PIECES == 2 && !listed) {   // uniform over the block
+            if (use_scale)
+                gather_deep<T, EPL, G, true, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
+                                                      g * G, acc, csum);
             else
-                gather_group<T, EPL, G, false, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
-                                                        g * G, my_id, acc, csum);
-            if (MODE == kFwd) {
-                if (valid)
-                    r2 += epilogue_fwd<T, EPL>(a, mats.dst, zrow, it.len, col, col_ok, acc, self);
-            } else if (MODE == kAdjNode) {
-                epilogue_adj_node<T, EPL, G>(a, it.row, it.len, col, col_ok, acc, self, valid);
-            } else {
-                csum = group_sum<G>(csum);
-                epilogue_adj_edge<T, EPL, G>(a, it.row, it.len, col, col_ok, acc, csum, self, valid);
-            }
+                gather_deep<T, EPL, G, false, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
+                                                       g * G, acc, csum);
+        } else if (use_scale)
+            gather_group<T, EPL, G, true, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
+                                                   g * G, my_id, acc, csum);
+        else
+            gather_group<T, EPL, G, false, kScalar>(nb, sc, a.cvec, it.start, it.len, src, a.ld, col, col_ok, gl,
+                                                    g * G, my_id, acc, csum);
+        if (MODE == kFwd) {
+            if (valid)
+                r2 = epilogue_fwd<T, EPL>(a, mats.dst, zrow, it.len, col, col_ok, acc, self);
+        } else if (MODE == kAdjNode) {
+            epilogue_adj_node<T, EPL, G>(a, it.row, it.len, col, col_ok, acc, self, valid);
+        } else {
+            csum = group_sum<G>(csum);
+            epilogue_adj_edge<T, EPL, G>(a, it.row, it.len, col, col_ok, acc, csum, self, valid);
         }
     }
     if (MODE == kFwd)
@@ -1724,7 +1716,7 @@ static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp, bool piece
     a.side[1] = L.side[1];
     if (L.unit_w)
         a.side[1].wn = nullptr;  // unit weights: skip the per-edge multiply
-    const int rows_per_block = kRowsPerGroup * kBlock / G;
+    const int rows_per_block = kBlock / G;
     int32_t per_panel = 0;
     for (int s = 0; s < 2; ++s) {
         a.n_long[s] = pieces ? L.n_pieced[s] : L.n_long[s];
@@ -1957,7 +1949,8 @@ static hnv_status run_sweep(hnv_plan *p, int level, const void *src, void *dst, 
     return HNV_OK;
 }
 
-// Sweeps per launch from LDS without residuals (a launch stays below a millisecond).
+// Sweeps per launch from LDS without residuals (a launch takes 1.1 ms at the
+// largest levels that use_resident allows).
 constexpr int kResidentMost = 256;
 
 // Whether `sweeps` sweeps of a level in a row run from LDS: the level fits, and

@@ -30,27 +30,6 @@ __global__ __launch_bounds__(kThreads) void k_fill(int32_t *__restrict__ p, int6
         p[i] = v;
 }
 
-// Flag bits of the checks: 0 offsets, 1 member range, 2 member order,
-// 3 weights.  Per hyperedge: offsets (start at 0, end at nnz, never
-// decrease, stay in [0, nnz]); with `full` also no empty hyperedge and
-// weights finite and > 0.
-__global__ __launch_bounds__(kThreads) void k_check_edges(const int32_t *__restrict__ ptr,
-                                                          const float *__restrict__ w, int64_t n_edges,
-                                                          int64_t nnz, int full, int *__restrict__ flag)
-{
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= n_edges)
-        return;
-    const int64_t a = ptr[e], b = ptr[e + 1];
-    int bad = 0;
-    if (a < 0 || b < a || b > nnz || (e == 0 && a != 0) || (e == n_edges - 1 && b != nnz) || (full && a == b))
-        bad |= 1;
-    if (full && w && !(w[e] > 0.0f && w[e] < INFINITY))
-        bad |= 8;
-    if (bad)
-        atomicOr(flag, bad);
-}
-
 // A wavefront's window of `per` (at most 64) consecutive hyperedges, one per
 // lane: the incidences [begin, end) of the window are walked 64 at a time
 // whatever their hyperedges, so that reads and writes per incidence are in
@@ -186,8 +165,11 @@ __global__ __launch_bounds__(kThreads) void k_inc_edge(const int32_t *__restrict
         });
 }
 
-// All checks of a level in one pass over its hyperedges: k_check_edges' of the
-// offsets and weights, and every member's range and (full) order.  Every
+// Flag bits of the checks: 0 offsets, 1 member range, 2 member order,
+// 3 weights.  All checks of a level in one pass over its hyperedges: the offsets
+// (start at 0, end at nnz, never decrease, stay in [0, nnz]) and every member's
+// range; with `full` also no empty hyperedge, ascending members, and weights
+// finite and > 0.  Every
 // access stays in the arrays whatever the offsets are; members that no window
 // reaches are not looked at, but then the offsets are bad.  With inc_edge also
 // the hyperedge of every incidence (gaps and wrong ones with bad offsets); with
@@ -239,31 +221,6 @@ __global__ __launch_bounds__(kThreads) void k_check_level(const int32_t *__restr
             if (inc_edge)
                 inc_edge[j] = (int32_t)(e0 + l);
         });
-    if (bad)
-        atomicOr(flag, bad);
-}
-
-// Member range per incidence; with `full` also strictly ascending members
-// (inc_edge is only meaningful when the offsets are valid; every read stays
-// in bounds either way).
-__global__ __launch_bounds__(kThreads) void k_check_members(const int32_t *__restrict__ ptr,
-                                                            const int32_t *__restrict__ idx,
-                                                            const int32_t *__restrict__ inc_edge, int64_t n_nodes,
-                                                            int64_t n_edges, int64_t nnz, int full,
-                                                            int *__restrict__ flag)
-{
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (j >= nnz)
-        return;
-    const int32_t v = idx[j];
-    int bad = 0;
-    if (v < 0 || v >= n_nodes) {
-        bad = 2;
-    } else if (full && j > 0) {
-        const int32_t e = inc_edge[j];
-        if (e >= 0 && e < n_edges && j > ptr[e] && idx[j - 1] >= v)
-            bad = 4;
-    }
     if (bad)
         atomicOr(flag, bad);
 }

@@ -278,7 +278,6 @@ HNV_DEV void resident_side(const unsigned char *nb_rows, const unsigned char *ow
 template <typename T, int G>
 __global__ __launch_bounds__(kResidentThreads) void k_resident(ResidentArgs a)
 {
-    static_assert(kRowsPerGroup == 1, "a lane-group tier row per lane group");
     static_assert(kWavesPerBlock == 4 && 4 * (kWave / G) <= kWave, "a row's quarters, in one wavefront");
     __shared__ __align__(16) unsigned char lds[kResidentLds];
     const uint32_t *src = static_cast<const uint32_t *>(a.src) + blockIdx.x;   // this workgroup's word of row 0
