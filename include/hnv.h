@@ -443,7 +443,9 @@ hnv_status hnv_logweight_grad(hnv_plan *plan, int level, const float *dw, float 
  *   HNV_PROF_FUSED     forward sweep fused with the projection
  *   HNV_PROF_ADJ_NODE  reverse sweep, node rows
  *   HNV_PROF_ADJ_EDGE  reverse sweep, hyperedge rows
- * enable = 0 stops recording and discards what was recorded. */
+ * enable = 0 stops recording and discards what was recorded.  While enabled,
+ * hnv_refine runs every sweep in launches of its own, also at small levels
+ * whose sweeps it otherwise runs many to a launch: same results, longer. */
 #define HNV_PROF_SWEEP 0
 #define HNV_PROF_FUSED 1
 #define HNV_PROF_ADJ_NODE 2
