@@ -40,6 +40,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -182,6 +183,7 @@ struct GatherArgs {
     int32_t blocks_per_panel;
     int32_t n_long[2];        // leading items per side that a whole workgroup takes
     int32_t n_wide[2];        // items from here on take a lane group (the order that serves gradients; else none)
+    int32_t wide_waves[2];    // wavefronts of a block that take an item of the others
     int32_t pieces;           // the order that serves gradients (k_gather's PIECES)
     int32_t piece;            // neighbours per piece there
     int32_t slot_pieces;      // partial slots per item there
@@ -315,8 +317,9 @@ HNV_DEV void gather_group(const int32_t *__restrict__ nb, const float *__restric
     }
 }
 
-// Bytes of neighbour rows a lane has in flight in gather_deep.
-constexpr int kDeepBytes = 256;
+// Neighbour rows a lane group has in flight in gather_deep (with 8 of 32 bytes a
+// lane, the reverse sweeps of 5K nodes / 4K hyperedges, d = 128, take 5% longer).
+constexpr int kDeepRows = 16;
 
 // gather_group's sum, with more rows in flight (and no first ids at hand): for
 // levels that don't fill the chip.  Loads past the row's end take its first
@@ -327,7 +330,7 @@ HNV_DEV void gather_deep(const int32_t *__restrict__ nb, const float *__restrict
                          int col, bool col_ok, int gl, int gbase, float (&acc)[EPL], float &csum)
 {
     using S = Slice<T, EPL>;
-    constexpr int U = kDeepBytes / (int)sizeof(typename S::Raw);
+    constexpr int U = kDeepRows;
     int ix[kIdxRegs];
     float sv[kIdxRegs];
 #pragma unroll
@@ -349,25 +352,31 @@ HNV_DEV void gather_deep(const int32_t *__restrict__ nb, const float *__restrict
     }
     const int first = __shfl(ix[0], gbase, kWave);
     const T *base = src + (col_ok ? col : 0);
-    for (int j = 0; j < deg; j += U) {
-        typename S::Raw raw[U];
-        float s[U];
+    auto of = [](auto (&x)[kIdxRegs], int r) { return (r == 0) ? x[0] : (r == 1) ? x[1] : (r == 2) ? x[2] : x[3]; };
+    // n (a constant) neighbours from j, a multiple of n
+    auto batch = [&](int j, auto n) {
+        constexpr int N = decltype(n)::value;
+        typename S::Raw raw[N];
+        float s[N];
+        const int xj = of(ix, j / G);   // (with N <= G, theirs)
+        const float sj = of(sv, j / G);
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int q = j + k;
-            const int r = q / G;
-            const int xr = (r == 0) ? ix[0] : (r == 1) ? ix[1] : (r == 2) ? ix[2] : ix[3];
-            const float sr = (r == 0) ? sv[0] : (r == 1) ? sv[1] : (r == 2) ? sv[2] : sv[3];
-            const int lane_src = gbase + (q & (G - 1));
-            const int v = __shfl(xr, lane_src, kWave);
-            s[k] = SCALE ? __shfl(sr, lane_src, kWave) : 1.0f;
+        for (int k = 0; k < N; ++k) {
+            const int q = j + k, lane_src = gbase + (q & (G - 1));
+            const int v = __shfl(N <= G ? xj : of(ix, q / G), lane_src, kWave);
+            s[k] = SCALE ? __shfl(N <= G ? sj : of(sv, q / G), lane_src, kWave) : 1.0f;
             raw[k] = S::load(base + (int64_t)(q < deg ? v : first) * ld);
         }
 #pragma unroll
-        for (int k = 0; k < U; ++k)
+        for (int k = 0; k < N; ++k)
             if (j + k < deg)
                 accumulate<SCALE, T, EPL>(acc, s[k], raw[k]);
-    }
+    };
+    int j = 0;
+    for (; j + U / 2 < deg; j += U)
+        batch(j, std::integral_constant<int, U>());
+    if (j < deg)
+        batch(j, std::integral_constant<int, U / 2>());
 }
 
 // A whole wavefront gathers `len` neighbours: group g takes neighbours
@@ -795,7 +804,7 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
     bool listed = true;   // a lane group's item of the lane-group tier: its first ids and coarse row are known
     if constexpr (PIECES == 2) {
         const int n_long = a.n_long[side], n_wide = a.n_wide[side];
-        const int wide_blocks = n_long + (n_wide - n_long + kWavesPerBlock - 1) / kWavesPerBlock;
+        const int wide_blocks = n_long + (n_wide - n_long + a.wide_waves[side] - 1) / a.wide_waves[side];
         if (tier == 0 && b >= wide_blocks) {
             tier = 1;
             b -= wide_blocks;
@@ -812,8 +821,13 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
         // a wavefront each.
         const int n_long = a.n_long[side];
         const bool whole_block = b < n_long;   // uniform over the block
-        const int item = whole_block ? b : n_long + (b - n_long) * kWavesPerBlock + wave;
-        const bool valid = item < (PIECES ? a.n_wide[side] : Sd.n_chunks);   // uniform over the wavefront
+        const int n_items = PIECES ? a.n_wide[side] : Sd.n_chunks;
+        int item = whole_block ? b : n_long + (b - n_long) * kWavesPerBlock + wave;
+        if (PIECES && !whole_block) {   // (dealt out, so that a block has one of the longest)
+            const int waves = a.wide_waves[side];
+            item = wave < waves ? b + wave * ((n_items - n_long + waves - 1) / waves) : n_items;
+        }
+        const bool valid = item < n_items;   // uniform over the wavefront
         Item c{0, 0, 0, 0};
         if (valid)
             c = Sd.chunks[item];
@@ -1707,6 +1721,11 @@ static hnv_status ensure_reverse_scales(hnv_plan *p, int level, hipStream_t s)
     return st;
 }
 
+// Items of a wavefront each are spread over at least this many blocks, with fewer
+// of them in a block (the order that serves gradients): a compute unit's cache
+// bounds the gathers of several long rows.
+constexpr int kSpreadBlocks = 512;
+
 static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp, bool pieces)
 {
     GatherArgs a{};
@@ -1721,7 +1740,11 @@ static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp, bool piece
     for (int s = 0; s < 2; ++s) {
         a.n_long[s] = pieces ? L.n_pieced[s] : L.n_long[s];
         a.n_wide[s] = pieces ? L.n_wide[s] : L.n_chunks[s];
-        a.nb_chunk[s] = a.n_long[s] + (int32_t)blocks_for(a.n_wide[s] - a.n_long[s], kWavesPerBlock) +
+        const int32_t n_waves = a.n_wide[s] - a.n_long[s];
+        a.wide_waves[s] = kWavesPerBlock;
+        while (pieces && a.wide_waves[s] > 1 && blocks_for(n_waves, a.wide_waves[s]) < kSpreadBlocks)
+            a.wide_waves[s] /= 2;
+        a.nb_chunk[s] = a.n_long[s] + (int32_t)blocks_for(n_waves, a.wide_waves[s]) +
                         (int32_t)blocks_for(L.n_chunks[s] - a.n_wide[s], kBlock / G);
         a.nb_small[s] = (int32_t)blocks_for(L.n_small[s], rows_per_block);
         a.nb_split[s] = (int32_t)blocks_for(L.n_splits[s], kWavesPerBlock);
