@@ -94,13 +94,21 @@ static_assert(kDefaultChunk == kWavesPerBlock * kDefaultPiece, "a piece per wave
 //   94K / 34K, up to 26,360, BF16, d = 128                            36.5, 36.2, 24.3
 //   186K / 125K, up to 97,042, BF16, d = 40                           35.7, 30.5, 33.2
 static constexpr double kFewBytes = 40e6, kSomeBytes = 80e6, kManyBytes = 320e6;
+// Levels whose sweeps move up to this (the rows' own values too) don't fill the
+// chip: in the order that serves gradients, a lane group's item has 16 rows in
+// flight there, 4 in others (a training step of 30K nodes / 13K hyperedges, FP32,
+// d = 96, 90 MB: 568 us, with 4 683; of 337K / 264K, d = 40, 475 MB: 2,394, with
+// 4 1,894).
+static constexpr double kDeepBytes = 160e6;
 // Up to this many items (times panels) all take a workgroup (what launches from
 // LDS reproduce): 1.02 times the best at 512 to 1,024 of them, 1.14 at 2,048 to
 // 4,096.
 static constexpr int kFewItems = 1024;
 
-static void default_tiers(LevelPlan &L, double bytes, int panels)
+static void default_tiers(LevelPlan &L, double row_bytes, int panels)
 {
+    const double bytes = 2.0 * (double)L.nnz * row_bytes;
+    L.deep = bytes + 2.0 * (double)L.rows * row_bytes <= kDeepBytes;
     const bool dense = 2 * L.nnz > 12 * L.rows;
     L.small_max = bytes <= kFewBytes ? 8 : bytes <= kSomeBytes || (bytes <= kManyBytes && !dense) ? 16 : kDefaultSmallMax;
     L.long_len = bytes <= kSomeBytes ? 64 : 256;
@@ -878,7 +886,7 @@ void init_plan_shape(hnv_plan *p, const std::vector<LevelShape> &shape, int d, h
         L.has_coarse = (l + 1 < n_levels);
         L.rows_coarse = L.has_coarse ? shape[l + 1].nV + shape[l + 1].nE : 0;
         L.unit_w = shape[l].unit_w;
-        default_tiers(L, 2.0 * (double)L.nnz * d * elem, p->panels);
+        default_tiers(L, (double)d * elem, p->panels);
         if (o.small_max > 0 || o.chunk != kDefaultChunk)
             L.small_max = p->lane_most;
         L.small_max = std::min(L.small_max, p->lane_most);

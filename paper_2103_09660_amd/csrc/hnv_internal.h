@@ -95,6 +95,7 @@ struct LevelPlan {
     int split_over = 0;              // than this if the level has a row of more than a chunk,
     int cut = 0;                     // into items of this many
     int slot_pieces = 1;             // pieces per such item in the order that serves gradients
+    bool deep = false;               // the level doesn't fill the chip: more loads in flight there
     bool scales_ready = false;       // the reverse-mode scales (side[*].sn) hold the current weights
     DevSide side[2];
     float *r = nullptr;              // [rows] 1 / (row weight sum), 0 for rows without neighbours

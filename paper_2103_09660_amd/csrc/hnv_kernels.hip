@@ -742,9 +742,10 @@ HNV_DEV void block_resid(const GatherArgs &a, double r2, int64_t lb)
 // lane group, longer ones by a wavefront, 512 neighbours (a piece) at a time, and
 // their pieces as sum_pieces and k_finalize do.  The lists are the level's, cut
 // by length: items of more than a piece take a workgroup, a piece per wavefront,
-// items of up to lane_most neighbours a lane group each, as lane-group rows do, but
-// with all 64 neighbours' loads in four batches (levels with such items don't fill
-// the chip; PIECES = 1 is for levels without).
+// items of up to lane_most neighbours a lane group each, as lane-group rows do.
+// PIECES = 2 loads 16 of their rows at a time (gather_deep), for levels that don't
+// fill the chip; its registers cost occupancy in others (a sweep of 337K nodes /
+// 264K hyperedges, d = 40: 77 us, with it 119).
 // Against a wavefront per item of any length in that order, a training step with
 // hubs (8K nodes / 4K hyperedges, FP32, d = 128, 4 sweeps at each of six levels)
 // takes 2,470 us instead of 6,120, without (36K / 25K, d = 256, 7 sweeps at each
@@ -802,7 +803,7 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
     const Item *lane_items = Sd.small;
     int n_lane_items = Sd.n_small;
     bool listed = true;   // a lane group's item of the lane-group tier: its first ids and coarse row are known
-    if constexpr (PIECES == 2) {
+    if constexpr (PIECES != 0) {
         const int n_long = a.n_long[side], n_wide = a.n_wide[side];
         const int wide_blocks = n_long + (n_wide - n_long + a.wide_waves[side] - 1) / a.wide_waves[side];
         if (tier == 0 && b >= wide_blocks) {
@@ -887,8 +888,12 @@ __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
         int my_id = 0;   // lane gl < kInlineIds: the row's neighbour gl, loaded with the item
         if (valid) {
             it = lane_items[item];
-            if (gl < kInlineIds && G >= kInlineIds && listed)
-                my_id = (FUSED ? Sd.small_cids : Sd.small_ids)[item].id[gl];
+            if (gl < kInlineIds && G >= kInlineIds) {
+                if (listed)
+                    my_id = (FUSED ? Sd.small_cids : Sd.small_ids)[item].id[gl];
+                else if (PIECES == 1 && gl < it.len)
+                    my_id = nb[it.start + gl];
+            }
         }
         const int zrow = Sd.row_base + it.row;
         Own<T, EPL> self{};
@@ -1750,7 +1755,7 @@ static GatherArgs base_args(hnv_plan *p, LevelPlan &L, int G, int dp, bool piece
         a.nb_split[s] = (int32_t)blocks_for(L.n_splits[s], kWavesPerBlock);
         per_panel += a.nb_chunk[s] + a.nb_small[s];
     }
-    a.pieces = !pieces ? 0 : L.n_wide[0] < L.n_chunks[0] || L.n_wide[1] < L.n_chunks[1] ? 2 : 1;
+    a.pieces = !pieces ? 0 : L.deep ? 2 : 1;
     a.blocks_per_panel = per_panel;
     a.dp = dp;
     a.ld = p->d;
