@@ -74,10 +74,10 @@ static_assert(kDefaultChunk == kWavesPerBlock * kDefaultPiece, "a piece per wave
 // fill the chip from 80 MB on, where most of them would leave the lane-group
 // tier.  A sweep in us with lane-group bound / workgroup items of more than
 // 8/64, 16/64, 16/256 and 64/256 neighbours:
-//   12K rows, 0.20M incidences, FP32, d = 128 (200 MB)       26, 26, 26, 31
+//   30K rows, 0.20M incidences, FP32, d = 128 (207 MB)       26, 26, 26, 31
 //   66K rows, 0.85M incidences, FP32, d = 16 (108 MB)        26, 26, 26, 26
 //   90K rows, 0.87M incidences, FP32, d = 256 (1.8 GB)       200, 203, 203, 166
-//   17K rows, 0.27M incidences, BF16, d = 256 (278 MB)       47, 45, 43, 37
+//   18K rows, 0.27M incidences, BF16, d = 256 (274 MB)       47, 45, 43, 37
 // and over 587 levels of 300 to 400K rows these bounds take 0.72 of the time of
 // a bound of 64 with a wavefront per 512 neighbours (1.10 at most), where
 // bounds by the number of rows took 0.80 (2.6 at most).  Given chunks keep the

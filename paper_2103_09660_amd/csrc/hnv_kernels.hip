@@ -173,7 +173,14 @@ enum Mode : int {
     kAdjNode = 1,   // reverse sweep, node rows
     kAdjEdge = 2,   // reverse sweep, hyperedge rows, summing the per-node scalars of their members
     kAdjEdgeNoSum = 3,   // reverse sweep, hyperedge rows, without that sum
+    kPieces = 8,    // added to kFwd: the order of sums that the reverse modes have too
+    kDeep = 16,     // added to any: that order with more rows in flight
 };
+// k_gather's PIECES of a mode with these added
+constexpr int pieces_of(int modes)
+{
+    return (modes & kDeep) ? 2 : (modes & kPieces) || (modes & 7) != kFwd ? 1 : 0;
+}
 
 struct GatherArgs {
     DevSide side[2];
@@ -318,7 +325,7 @@ HNV_DEV void gather_group(const int32_t *__restrict__ nb, const float *__restric
 }
 
 // Neighbour rows a lane group has in flight in gather_deep (with 8 of 32 bytes a
-// lane, the reverse sweeps of 5K nodes / 4K hyperedges, d = 128, take 5% longer).
+// lane, a training step of 5K nodes / 4K hyperedges, d = 128, takes 4% longer).
 constexpr int kDeepRows = 16;
 
 // gather_group's sum, with more rows in flight (and no first ids at hand): for
@@ -734,11 +741,11 @@ HNV_DEV void block_resid(const GatherArgs &a, double r2, int64_t lb)
 // ---------------------------------------------------------------------------
 
 // PIECES (1 and 2): the order of sums of the calls that serve gradients
-// (hnv_sweeps and the reverse sweeps).  The log-weight gradients of a small hierarchy's finest
-// level are differences of nearly equal sums, once the coarser levels have
-// smoothed the embedding: their FP32 error is 2e-4 to 4e-4, and another order
-// alone moves them by 2e-5 to 8e-5.  So this one doesn't depend on a level's
-// tiers: rows of up to lane_most (64) neighbours are added one after another by a
+// (hnv_sweeps and the reverse sweeps).  The log-weight gradients of a small
+// hierarchy's finest level are differences of nearly equal sums, once the coarser
+// levels have smoothed the embedding: their FP32 error is 2e-4 to 4e-4, and
+// another order alone moves them by 2e-5 to 8e-5.  So this one doesn't depend on
+// a level's tiers: rows of up to lane_most (64) neighbours are added one after another by a
 // lane group, longer ones by a wavefront, 512 neighbours (a piece) at a time, and
 // their pieces as sum_pieces and k_finalize do.  The lists are the level's, cut
 // by length: items of more than a piece take a workgroup, a piece per wavefront,
@@ -748,11 +755,12 @@ HNV_DEV void block_resid(const GatherArgs &a, double r2, int64_t lb)
 // 264K hyperedges, d = 40: 77 us, with it 119).
 // Against a wavefront per item of any length in that order, a training step with
 // hubs (8K nodes / 4K hyperedges, FP32, d = 128, 4 sweeps at each of six levels)
-// takes 2,470 us instead of 6,120, without (36K / 25K, d = 256, 7 sweeps at each
-// of three) 3,950 instead of 6,760.
-template <typename T, int EPL, int G, int MODE, bool FUSED, bool CTL, int PIECES>
+// takes 2,420 us instead of 6,120, without (36K / 25K, d = 256, 7 sweeps at each
+// of three) 3,900 instead of 6,760.
+template <typename T, int EPL, int G, int MODES, bool FUSED, bool CTL>
 __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a)
 {
+    constexpr int MODE = MODES & 7, PIECES = pieces_of(MODES);
     const int64_t lb = linear_block();
     if (lb >= a.n_blocks)
         return;
@@ -1821,7 +1829,9 @@ static void launch_pair(const GatherArgs &a, int panels, hipStream_t s, ProfScop
     if (main_blocks) {
         GatherArgs m = a;
         m.n_blocks = main_blocks;
-        k_gather<T, EPL, G, MODE, FUSED, CTL, PIECES><<<fold_grid(main_blocks), kBlock, 0, s>>>(m);
+        constexpr int MODES = MODE | (PIECES == 2 ? kDeep : PIECES == 1 && MODE == kFwd ? kPieces : 0);
+        static_assert(pieces_of(MODES) == PIECES, "a kernel per mode and order");
+        k_gather<T, EPL, G, MODES, FUSED, CTL><<<fold_grid(main_blocks), kBlock, 0, s>>>(m);
     }
     if (ps)
         ps->end();
